@@ -377,19 +377,45 @@ int build_view(Ctx* c, Lane* L, AlphaView& v, double alpha) {
   level_table(c->mode, (int64_t)c->wmin, (int64_t)c->wmax, c->abar, alpha, lut.data());
   RAKS_TRY(dev_alloc(c, c->lut, span));
   HIP_OK(hipMemcpyAsync(c->lut.p, lut.data(), span, hipMemcpyHostToDevice, s));
+  SortInput in = {};
   if (c->mode == RAKS_ACT_EDGE) {
-    launch_act_edge(g, P<uint32_t>(c->cweight), P<uint8_t>(c->lut), c->wmin, P<uint8_t>(v.act), s);
+    in.c = P<uint32_t>(c->cweight);
+    in.lut = P<uint8_t>(c->lut);
+    in.cmin = (uint32_t)c->wmin;
   } else {
     // node levels by original id (they give the per-arc levels), then by internal id
     RAKS_TRY(dev_alloc(c, c->node_tmp, (size_t)c->n));
     launch_act_node(g, P<uint8_t>(c->nw), P<uint8_t>(c->lut), (uint32_t)c->wmin,
-                    P<uint8_t>(c->node_tmp), P<uint8_t>(v.act), s);
+                    P<uint8_t>(c->node_tmp), s);
     launch_to_internal_u8(g, P<uint8_t>(c->node_tmp), P<uint8_t>(v.act_node), s);
+    in.node_lv = P<uint8_t>(c->node_tmp);
   }
-  launch_sort_rows(g, P<int32_t>(v.col_s), P<uint8_t>(v.act_s), P<uint32_t>(v.eid_s),
-                   P<uint8_t>(v.row_amax), P<uint32_t>(v.bnd), c->nbnd, s);
-  HIP_OK(hipGetLastError());
-  HIP_OK(hipStreamSynchronize(s));
+  in.act = P<uint8_t>(v.act);
+  in.col_s = P<int32_t>(v.col_s);
+  in.act_s = P<uint8_t>(v.act_s);
+  in.eid_s = P<uint32_t>(v.eid_s);
+  in.row_amax = P<uint8_t>(v.row_amax);
+  in.bnd = P<uint32_t>(v.bnd);
+  in.n_big = c->n_big;
+  in.n_mid = c->n_mid;
+  in.big_arcs = c->big_arcs;
+  // levels never exceed Round(2 * a_bar) (x <= 1 in Eqs. 1-3); one more for
+  // the last digit of the quotient at x = 1
+  in.nlev = (int32_t)std::min(256.0, std::floor(2.0 * c->abar + 0.5) + 2.0);
+  DevBuf cursor;
+  const size_t words = (size_t)c->n_big * in.nlev;
+  if (words <= c->A - c->big_arcs) {
+    in.cursor = in.eid_s + c->big_arcs;   // filled with the other rows' arcs afterwards
+  } else {
+    RAKS_TRY(dev_alloc(c, cursor, words * 4));
+    in.cursor = P<uint32_t>(cursor);
+  }
+  launch_sort_rows(g, in, s);
+  const hipError_t err = hipGetLastError();
+  const hipError_t done = hipStreamSynchronize(s);
+  dev_free(c, cursor);
+  HIP_OK(err);
+  HIP_OK(done);
   v.alpha = alpha;
   return RAKS_OK;
 }
@@ -1699,8 +1725,15 @@ int raks_load_graph(raks_ctx* c, const raks_graph_desc* g) {
       int_id[v] = (int32_t)u;
     }
     rpi[0] = 0;
-    for (int64_t u = 0; u < n; ++u)
-      rpi[u + 1] = rpi[u] + (uint32_t)(g->row_ptr[orig_id[u] + 1] - g->row_ptr[orig_id[u]]);
+    // rows of the traversal copy's size classes (largest first)
+    c->n_big = c->n_mid = 0;
+    for (int64_t u = 0; u < n; ++u) {
+      const uint32_t d = (uint32_t)(g->row_ptr[orig_id[u] + 1] - g->row_ptr[orig_id[u]]);
+      rpi[u + 1] = rpi[u] + d;
+      c->n_big += d > kBigRow;
+      c->n_mid += d > kMidRow;
+    }
+    c->big_arcs = rpi[c->n_big];
   }
   RAKS_TRY(dev_alloc(c, c->row_ptr, (n + 1) * 4));
   RAKS_TRY(dev_alloc(c, c->row_ptr_o, (n + 1) * 4));

@@ -71,16 +71,6 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
   }
 }
 
-// Activation level of every arc: a lookup of its label count c in the table
-// of levels the host built for c in [cmin, cmax] (Eqs. 1-3 evaluated once per
-// count, on the host).
-__global__ __launch_bounds__(kBlock) void k_act_edge(const uint32_t* c, uint32_t A,
-                                                     const uint8_t* lut, uint64_t cmin,
-                                                     uint8_t* act) {
-  for (uint32_t e = blockIdx.x * kBlock + threadIdx.x; e < A; e += gridDim.x * kBlock)
-    act[e] = lut[c[e] - cmin];
-}
-
 __global__ __launch_bounds__(kBlock) void k_node_weight_range(const uint8_t* nw, int32_t n,
                                                               Status* st) {
   uint32_t mn = 255, mx = 0;
@@ -108,69 +98,298 @@ __global__ __launch_bounds__(kBlock) void k_act_node(const uint8_t* nw, int32_t 
     act_node[v] = lut[nw[v] - wmin];
 }
 
-__global__ __launch_bounds__(kBlock) void k_act_gather(const uint8_t* act_node,
-                                                       const int32_t* col, uint32_t A,
-                                                       uint8_t* act) {
-  for (uint32_t e = blockIdx.x * kBlock + threadIdx.x; e < A; e += gridDim.x * kBlock)
-    act[e] = act_node[col[e]];
+// Traversal copy of the graph: each row's arcs ordered by activation level, the
+// row's largest level and its entries of the level-major level table.  At
+// level l a frontier's arcs with level <= l form a row prefix.  The level of
+// an arc is looked up on the way (EDGE: its label count in the host's table,
+// NODE: the level of its target), so the levels need no pass of their own.
+//
+// Internal rows are in order of degree, so rows of one size class are
+// neighbours and each class gets the split that fills the machine (the order
+// of the arcs of one level within a row is free: no result depends on it):
+//   <= 64 arcs       k_sort_small: a group of 1 to 64 lanes per row, one arc
+//                    per lane, positions from ballots; a workgroup takes 128
+//                    neighbouring rows, whose arcs are contiguous in the copy,
+//                    and writes their level-table entries as whole lines;
+//   <= kBigRow arcs  k_sort_mid: one wavefront per row, two passes;
+//   larger           k_big_hist, k_big_prefix, k_big_scatter: tiles of
+//                    kBigTile arcs over all workgroups, so that a hub's row is
+//                    not one wavefront's work.
+// Memory traffic bounds it: per arc 8 bytes read and 10 written plus the
+// gathers of the target's id and the count's level.  On 2M nodes and 40M arcs
+// (largest row 1.3M arcs) the three classes take 0.25, 0.18 and 0.22 ms; with
+// one wavefront per row for every row it was 17.0 ms, all but about 1 ms of it
+// in the largest row, plus 0.08 ms for the separate pass over the levels.
+constexpr int kSmallRows = 128;     // rows per workgroup of k_sort_small
+
+struct SortView {
+  DevGraphView g;
+  const uint32_t* c;      // EDGE: label count per arc (original CSR order)
+  const uint8_t* lut;     // EDGE: level of count c at lut[c - cmin]
+  uint32_t cmin;
+  const uint8_t* node_lv; // NODE: level per node, original ids
+  uint8_t* act;           // levels in original CSR order
+  int32_t* col_s;
+  uint8_t* act_s;
+  uint32_t* eid_s;
+  uint8_t* row_amax;
+  uint32_t* bnd;
+  int32_t n_big, n_mid;   // rows [0, n_big) exceed kBigRow arcs, [n_big, n_mid) exceed 64
+  uint32_t big_arcs;      // arcs of the big rows
+  uint32_t* cursor;       // [n_big][nlev]
+  int32_t nlev;           // levels are below this
+};
+
+__device__ inline uint32_t arc_level(const SortView& v, uint32_t e) {
+  return v.g.mode ? v.node_lv[v.g.col[e]] : v.lut[v.c[e] - v.cmin];
 }
 
-// Traversal copy of the graph: each row's arcs re-ordered by activation level
-// (counting sort per row, one wavefront per row), plus the row's largest
-// level and its entries of the level-major level table.  At level l a
-// frontier's arcs with level <= l form a row prefix.
-__global__ __launch_bounds__(kBlock) void k_sort_rows(const uint32_t* row_ptr_o,
-                                                      const uint32_t* row_ptr,
-                                                      const int32_t* orig_id, const int32_t* int_id,
-                                                      const int32_t* col, const uint8_t* act,
-                                                      int32_t n, int32_t* col_s, uint8_t* act_s,
-                                                      uint32_t* eid_s, uint8_t* row_amax,
-                                                      uint32_t* bnd, int32_t nbnd) {
+template <int G>
+__device__ void sort_small_rows(const SortView& v, int32_t u0, int rows, const uint32_t* s_rs,
+                                const uint32_t* s_ro, uint32_t (*s_cnt)[kSmallRows],
+                                uint32_t* s_am) {
+  constexpr int kPer = kBlock / G;   // rows at a time
+  const int q = threadIdx.x & (G - 1);
+  const int gl = lane_id() & ~(G - 1);                       // first lane of the group
+  const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1);
+  const uint64_t before = (1ull << q) - 1;
+  const DevGraphView& g = v.g;
+  for (int r0 = 0; r0 < rows; r0 += kPer) {
+    const int r = r0 + (int)threadIdx.x / G;
+    const bool live = r < rows && (uint32_t)q < s_rs[r + 1] - s_rs[r];
+    uint32_t a = 0, e = 0;
+    int32_t to = 0;
+    if (live) {
+      e = s_ro[r] + q;
+      a = arc_level(v, e);
+      to = g.int_id[g.col[e]];
+    }
+    // one round per distinct level of the wavefront
+    uint32_t pos = 0, amax = 0;
+    uint64_t pend = __ballot(live);
+    while (pend) {
+      const uint32_t x = __shfl(a, __ffsll((unsigned long long)pend) - 1, kWave);
+      const bool mine = live && a == x;
+      const uint64_t eq = __ballot(mine);
+      pend &= ~eq;
+      const uint64_t in = (eq >> gl) & gmask;
+      const uint32_t k = __popcll(in);
+      if (mine) pos += __popcll(in & before);
+      else if (a > x) pos += k;
+      if (q == 0 && k) {
+        amax = x > amax ? x : amax;
+        if ((int)x < g.nbnd) s_cnt[x][r] = k;
+      }
+    }
+    if (live) {
+      v.act[e] = (uint8_t)a;
+      const uint32_t p = s_rs[r] + pos;
+      v.col_s[p] = to;
+      v.act_s[p] = (uint8_t)a;
+      v.eid_s[p] = e;
+    }
+    if (q == 0 && r < rows) s_am[r] = amax;
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_sort_small(SortView v) {
+  __shared__ uint32_t s_rs[kSmallRows + 1], s_ro[kSmallRows], s_am[kSmallRows];
+  __shared__ uint32_t s_cnt[16][kSmallRows];   // arcs of each level below nbnd
+  const DevGraphView& g = v.g;
+  const int32_t u0 = v.n_mid + (int32_t)blockIdx.x * kSmallRows;
+  const int rows = min(kSmallRows, g.n - u0);
+  for (int i = threadIdx.x; i <= rows; i += kBlock) {
+    s_rs[i] = g.row_ptr[u0 + i];
+    if (i < rows) s_ro[i] = g.row_ptr_o[g.orig_id[u0 + i]];
+  }
+  for (int i = threadIdx.x; i < 16 * kSmallRows; i += kBlock) (&s_cnt[0][0])[i] = 0;
+  __syncthreads();
+  const uint32_t dmax = s_rs[1] - s_rs[0];   // rows are in order of degree
+  if (dmax <= 1) sort_small_rows<1>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else if (dmax <= 2) sort_small_rows<2>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else if (dmax <= 4) sort_small_rows<4>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else if (dmax <= 8) sort_small_rows<8>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else if (dmax <= 16) sort_small_rows<16>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else if (dmax <= 32) sort_small_rows<32>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  else sort_small_rows<64>(v, u0, rows, s_rs, s_ro, s_cnt, s_am);
+  __syncthreads();
+  if ((int)threadIdx.x < rows) {
+    const int r = threadIdx.x;
+    uint32_t acc = 0;
+    for (int l = 0; l < g.nbnd; ++l) {   // arcs with level <= l
+      acc += s_cnt[l][r];
+      v.bnd[(size_t)l * g.n + u0 + r] = acc;
+    }
+    v.row_amax[u0 + r] = (uint8_t)s_am[r];
+  }
+}
+
+// Adds the lanes' levels (lanes with `live` set) to the histogram in LDS, one
+// atomic per distinct level of the wavefront; returns the lane's rank in its
+// level's run of slots.
+__device__ inline uint32_t wave_level_rank(uint32_t* hist, bool live, uint32_t a) {
+  uint32_t rank = 0;
+  uint64_t pend = __ballot(live);
+  while (pend) {
+    const int lead = __ffsll((unsigned long long)pend) - 1;
+    const uint32_t x = __shfl(a, lead, kWave);
+    const bool mine = live && a == x;
+    const uint64_t eq = __ballot(mine);
+    pend &= ~eq;
+    uint32_t base = 0;
+    if (lane_id() == lead) base = atomicAdd(&hist[x], (uint32_t)__popcll(eq));
+    base = __shfl(base, lead, kWave);
+    if (mine) rank = base + __popcll(eq & ((1ull << lane_id()) - 1));
+  }
+  return rank;
+}
+
+__global__ __launch_bounds__(kBlock) void k_sort_mid(SortView v) {
   __shared__ uint32_t s_hist[kBlock / kWave][256];
   uint32_t* hist = s_hist[wave_id()];
   const int lane = lane_id();
-  const int waves = gridDim.x * (kBlock / kWave);
-  for (int32_t u = blockIdx.x * (kBlock / kWave) + wave_id(); u < n; u += waves) {
-    // internal row u holds original row v's arcs
-    const int32_t v = orig_id[u];
-    const uint32_t rs_o = row_ptr_o[v], re_o = row_ptr_o[v + 1];
-    const uint32_t rs = row_ptr[u];
-    for (int b = lane; b < 256; b += kWave) hist[b] = 0;
-    __builtin_amdgcn_wave_barrier();
-    uint32_t amax = 0;
-    for (uint32_t e = rs_o + lane; e < re_o; e += kWave) {
-      const uint32_t a = act[e];
-      atomicAdd(&hist[a], 1u);
+  const DevGraphView& g = v.g;
+  const int32_t u = v.n_big + (int32_t)blockIdx.x * (kBlock / kWave) + wave_id();
+  if (u >= v.n_mid) return;
+  const uint32_t rs_o = g.row_ptr_o[g.orig_id[u]];
+  const uint32_t rs = g.row_ptr[u], d = g.row_ptr[u + 1] - rs;
+  for (int b = lane; b < 256; b += kWave) hist[b] = 0;
+  __builtin_amdgcn_wave_barrier();
+  uint32_t amax = 0;
+  for (uint32_t k0 = 0; k0 < d; k0 += kWave) {
+    const uint32_t k = k0 + lane;
+    uint32_t a = 0;
+    if (k < d) {
+      a = arc_level(v, rs_o + k);
+      v.act[rs_o + k] = (uint8_t)a;
       amax = a > amax ? a : amax;
     }
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-      const uint32_t o = __shfl_xor(amax, d, kWave);
-      amax = o > amax ? o : amax;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // exclusive prefix over the 256 bins: lane owns bins 4*lane .. 4*lane+3
-    uint32_t c0 = hist[4 * lane], c1 = hist[4 * lane + 1], c2 = hist[4 * lane + 2], c3 = hist[4 * lane + 3];
-    const uint32_t tot = c0 + c1 + c2 + c3;
-    const uint32_t ex = wave_inclusive_scan(tot) - tot;
-    hist[4 * lane] = ex;
-    hist[4 * lane + 1] = ex + c0;
-    hist[4 * lane + 2] = ex + c0 + c1;
-    hist[4 * lane + 3] = ex + c0 + c1 + c2;
-    __builtin_amdgcn_wave_barrier();
-    // arcs with level <= l = start of level l + 1
-    if (lane < nbnd) bnd[(size_t)lane * n + u] = hist[lane + 1];
-    __builtin_amdgcn_wave_barrier();
-    for (uint32_t e = rs_o + lane; e < re_o; e += kWave) {
-      const uint32_t a = act[e];
-      const uint32_t pos = rs + atomicAdd(&hist[a], 1u);
-      col_s[pos] = int_id[col[e]];
-      act_s[pos] = (uint8_t)a;
-      eid_s[pos] = e;
-    }
-    if (lane == 0) row_amax[u] = (uint8_t)amax;
-    __builtin_amdgcn_wave_barrier();
+    (void)wave_level_rank(hist, k < d, a);
   }
+#pragma unroll
+  for (int s = kWave / 2; s > 0; s >>= 1) {
+    const uint32_t o = __shfl_xor(amax, s, kWave);
+    amax = o > amax ? o : amax;
+  }
+  __builtin_amdgcn_wave_barrier();
+  // exclusive prefix over the 256 bins: lane owns bins 4*lane .. 4*lane+3
+  const uint32_t c0 = hist[4 * lane], c1 = hist[4 * lane + 1], c2 = hist[4 * lane + 2],
+                 c3 = hist[4 * lane + 3];
+  const uint32_t tot = c0 + c1 + c2 + c3;
+  const uint32_t ex = wave_inclusive_scan(tot) - tot;
+  hist[4 * lane] = ex;
+  hist[4 * lane + 1] = ex + c0;
+  hist[4 * lane + 2] = ex + c0 + c1;
+  hist[4 * lane + 3] = ex + c0 + c1 + c2;
+  __builtin_amdgcn_wave_barrier();
+  // arcs with level <= l = start of level l + 1
+  if (lane < g.nbnd) v.bnd[(size_t)lane * g.n + u] = hist[lane + 1];
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t k0 = 0; k0 < d; k0 += kWave) {
+    const uint32_t k = k0 + lane;
+    const uint32_t a = k < d ? v.act[rs_o + k] : 0u;   // written by this thread
+    const uint32_t p = rs + wave_level_rank(hist, k < d, a);
+    if (k < d) {
+      v.col_s[p] = g.int_id[g.col[rs_o + k]];
+      v.act_s[p] = (uint8_t)a;
+      v.eid_s[p] = rs_o + k;
+    }
+  }
+  if (lane == 0) v.row_amax[u] = (uint8_t)amax;
+}
+
+// Big rows: workgroup t takes arcs [t * kBigTile, (t + 1) * kBigTile) of the
+// copy, which belong to at most kBigTile / kBigRow + 2 rows.  f(u, k0, k1)
+// runs for every row u and its arcs k0..k1 of the tile.
+template <typename F>
+__device__ inline void big_tile(const SortView& v, F f) {
+  const uint32_t t0 = blockIdx.x * kBigTile, t1 = min(v.big_arcs, t0 + kBigTile);
+  for (int32_t u = upper_index<uint32_t>(v.g.row_ptr, 0, v.n_big, t0); u < v.n_big; ++u) {
+    const uint32_t rs = v.g.row_ptr[u], re = v.g.row_ptr[u + 1];
+    if (rs >= t1) break;
+    f(u, max(rs, t0) - rs, min(re, t1) - rs);
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_big_zero(SortView v) {
+  const uint32_t total = (uint32_t)v.n_big * (uint32_t)v.nlev;
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock) v.cursor[i] = 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_big_hist(SortView v) {
+  __shared__ uint32_t s_hist[256];
+  const DevGraphView& g = v.g;
+  big_tile(v, [&](int32_t u, uint32_t k0, uint32_t k1) {
+    s_hist[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t rs_o = g.row_ptr_o[g.orig_id[u]];
+    for (uint32_t b = k0; b < k1; b += kBlock) {
+      const uint32_t k = b + threadIdx.x;
+      uint32_t a = 0;
+      if (k < k1) {
+        a = arc_level(v, rs_o + k);
+        v.act[rs_o + k] = (uint8_t)a;
+      }
+      (void)wave_level_rank(s_hist, k < k1, a);
+    }
+    __syncthreads();
+    if (s_hist[threadIdx.x])
+      atomicAdd(&v.cursor[(size_t)u * v.nlev + threadIdx.x], s_hist[threadIdx.x]);
+    __syncthreads();
+  });
+}
+
+// One thread per big row: level counts to level starts.
+__global__ __launch_bounds__(kBlock) void k_big_prefix(SortView v) {
+  const int32_t u = blockIdx.x * kBlock + threadIdx.x;
+  if (u >= v.n_big) return;
+  uint32_t acc = 0, amax = 0;
+  for (int l = 0; l < max(v.nlev, v.g.nbnd); ++l) {
+    if (l < v.nlev) {
+      uint32_t* c = &v.cursor[(size_t)u * v.nlev + l];
+      const uint32_t k = *c;
+      *c = v.g.row_ptr[u] + acc;
+      acc += k;
+      if (k) amax = (uint32_t)l;
+    }
+    if (l < v.g.nbnd) v.bnd[(size_t)l * v.g.n + u] = acc;
+  }
+  v.row_amax[u] = (uint8_t)amax;
+}
+
+__global__ __launch_bounds__(kBlock) void k_big_scatter(SortView v) {
+  __shared__ uint32_t s_hist[256], s_base[256];
+  const DevGraphView& g = v.g;
+  big_tile(v, [&](int32_t u, uint32_t k0, uint32_t k1) {
+    constexpr int kIt = kBigTile / kBlock;
+    s_hist[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t rs_o = g.row_ptr_o[g.orig_id[u]];
+    uint32_t a[kIt], rank[kIt];
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+      const uint32_t k = k0 + i * kBlock + threadIdx.x;
+      a[i] = k < k1 ? v.act[rs_o + k] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kIt; ++i)
+      rank[i] = wave_level_rank(s_hist, k0 + i * kBlock + threadIdx.x < k1, a[i]);
+    __syncthreads();
+    const uint32_t cnt = s_hist[threadIdx.x];
+    if (cnt) s_base[threadIdx.x] = atomicAdd(&v.cursor[(size_t)u * v.nlev + threadIdx.x], cnt);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+      const uint32_t k = k0 + i * kBlock + threadIdx.x;
+      if (k < k1) {
+        const uint32_t p = s_base[a[i]] + rank[i];
+        v.col_s[p] = g.int_id[g.col[rs_o + k]];
+        v.act_s[p] = (uint8_t)a[i];
+        v.eid_s[p] = rs_o + k;
+      }
+    }
+    __syncthreads();
+  });
 }
 
 __global__ __launch_bounds__(kBlock) void k_to_internal_u8(const int32_t* orig_id, int32_t n,
@@ -186,11 +405,37 @@ __global__ __launch_bounds__(kBlock) void k_map_ids(const int32_t* int_id, int32
     ids[i] = int_id[ids[i]];
 }
 
-void launch_sort_rows(const DevGraphView& g, int32_t* col_s, uint8_t* act_s, uint32_t* eid_s,
-                      uint8_t* row_amax, uint32_t* bnd, int32_t nbnd, hipStream_t s) {
-  const unsigned grid = (unsigned)std::min<int64_t>(16384, ((int64_t)g.n + 3) / 4);
-  k_sort_rows<<<grid, kBlock, 0, s>>>(g.row_ptr_o, g.row_ptr, g.orig_id, g.int_id, g.col, g.act,
-                                      g.n, col_s, act_s, eid_s, row_amax, bnd, nbnd);
+void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s) {
+  SortView v;
+  v.g = g;
+  v.c = in.c;
+  v.lut = in.lut;
+  v.cmin = in.cmin;
+  v.node_lv = in.node_lv;
+  v.act = in.act;
+  v.col_s = in.col_s;
+  v.act_s = in.act_s;
+  v.eid_s = in.eid_s;
+  v.row_amax = in.row_amax;
+  v.bnd = in.bnd;
+  v.n_big = in.n_big;
+  v.n_mid = in.n_mid;
+  v.big_arcs = in.big_arcs;
+  v.cursor = in.cursor;
+  v.nlev = in.nlev;
+  // the big rows first: their cursors may lie in the part of eid_s that the
+  // other rows fill afterwards
+  if (v.n_big > 0) {
+    const unsigned tiles = (v.big_arcs + kBigTile - 1) / kBigTile;
+    k_big_zero<<<64, kBlock, 0, s>>>(v);
+    k_big_hist<<<tiles, kBlock, 0, s>>>(v);
+    k_big_prefix<<<(v.n_big + kBlock - 1) / kBlock, kBlock, 0, s>>>(v);
+    k_big_scatter<<<tiles, kBlock, 0, s>>>(v);
+  }
+  const int mid = v.n_mid - v.n_big, small = g.n - v.n_mid;
+  constexpr int kRows = kBlock / kWave;
+  if (mid > 0) k_sort_mid<<<(mid + kRows - 1) / kRows, kBlock, 0, s>>>(v);
+  if (small > 0) k_sort_small<<<(small + kSmallRows - 1) / kSmallRows, kBlock, 0, s>>>(v);
 }
 
 __global__ void k_status_reset_minmax(Status* st) {
@@ -215,11 +460,6 @@ void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc
                                                         arc_src, rev, st);
 }
 
-void launch_act_edge(const DevGraphView& g, const uint32_t* c_tmp, const uint8_t* lut,
-                     uint64_t cmin, uint8_t* act, hipStream_t s) {
-  if (g.A > 0) k_act_edge<<<grid_for(g.A), kBlock, 0, s>>>(c_tmp, g.A, lut, cmin, act);
-}
-
 void launch_node_weight_range(const DevGraphView& g, const uint8_t* nw, Status* st,
                               hipStream_t s) {
   k_status_reset_minmax<<<1, 1, 0, s>>>(st);
@@ -235,9 +475,8 @@ void launch_map_ids(const int32_t* int_id, int32_t* ids, uint64_t count, hipStre
 }
 
 void launch_act_node(const DevGraphView& g, const uint8_t* nw, const uint8_t* lut, uint32_t wmin,
-                     uint8_t* act_node, uint8_t* act, hipStream_t s) {
+                     uint8_t* act_node, hipStream_t s) {
   k_act_node<<<grid_for(g.n), kBlock, 0, s>>>(nw, g.n, lut, wmin, act_node);
-  if (g.A > 0) k_act_gather<<<grid_for(g.A), kBlock, 0, s>>>(act_node, g.col, g.A, act);
 }
 
 }  // namespace raks

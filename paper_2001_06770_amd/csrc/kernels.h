@@ -248,11 +248,29 @@ void launch_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp, const uint64_
 void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc_src, uint32_t* rev,
                             Status* st,
                             hipStream_t s);
-// act[e] = lut[c[e] - cmin] (lut: levels of the label counts, built on the host)
-void launch_act_edge(const DevGraphView& g, const uint32_t* c_tmp, const uint8_t* lut,
-                     uint64_t cmin, uint8_t* act, hipStream_t s);
-void launch_sort_rows(const DevGraphView& g, int32_t* col_s, uint8_t* act_s, uint32_t* eid_s,
-                      uint8_t* row_amax, uint32_t* bnd, int32_t nbnd, hipStream_t s);
+// Size classes of the traversal copy's rows (internal rows are in order of
+// degree): rows above kMidRow arcs take a wavefront each, rows above kBigRow
+// are split into tiles of kBigTile arcs over many workgroups.
+constexpr uint32_t kMidRow = 64, kBigRow = 2048, kBigTile = 4096;
+// Levels and traversal copy: inputs (label counts and the host's table, or the
+// nodes' levels by original id) and outputs (see DevGraphView).
+struct SortInput {
+  const uint32_t* c;
+  const uint8_t* lut;
+  uint32_t cmin;
+  const uint8_t* node_lv;
+  uint8_t* act;
+  int32_t* col_s;
+  uint8_t* act_s;
+  uint32_t* eid_s;
+  uint8_t* row_amax;
+  uint32_t* bnd;
+  int32_t n_big, n_mid;     // rows with more than kBigRow / kMidRow arcs
+  uint32_t big_arcs;        // arcs of the first n_big rows
+  uint32_t* cursor;         // scratch [n_big][nlev], may be eid_s + big_arcs
+  int32_t nlev;             // levels are below this
+};
+void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s);
 // out[u] = in[orig_id[u]] for every internal id u (per-node arrays to internal order)
 void launch_to_internal_u8(const DevGraphView& g, const uint8_t* in, uint8_t* out, hipStream_t s);
 // ids[i] = int_id[ids[i]] (original node ids to internal ones, in place)
@@ -260,9 +278,9 @@ void launch_map_ids(const int32_t* int_id, int32_t* ids, uint64_t count, hipStre
 // node weight range into st->cmin / st->cmax (NODE mode, once per graph)
 void launch_node_weight_range(const DevGraphView& g, const uint8_t* nw, Status* st,
                               hipStream_t s);
-// act_node[v] = lut[nw[v] - wmin]; act[e] = act_node[col[e]]
+// act_node[v] = lut[nw[v] - wmin]
 void launch_act_node(const DevGraphView& g, const uint8_t* nw, const uint8_t* lut, uint32_t wmin,
-                     uint8_t* act_node, uint8_t* act, hipStream_t s);
+                     uint8_t* act_node, hipStream_t s);
 
 void launch_run_init(const RunView& r, int TP, int32_t n, const int32_t* kw_nodes,
                      const SeedList& seeds, hipStream_t s);

@@ -174,6 +174,8 @@ struct Ctx {
   DevBuf row_ptr, col, label, nw, kw_nodes, arc_src;
   // internal (degree-ordered) node numbering: original row starts, both id maps
   DevBuf row_ptr_o, orig_id, int_id, node_tmp;
+  int32_t n_big = 0, n_mid = 0;   // internal rows above kBigRow / kMidRow arcs
+  uint32_t big_arcs = 0;          // arcs of the first n_big rows
   DevBuf rev;            // CSR position of every arc's reverse arc
   DevBuf cweight;        // EDGE: label count c of every arc, kept for other alphas
   DevBuf wstat;          // Status holding the c (or node weight) range of the graph

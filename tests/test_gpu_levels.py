@@ -1,0 +1,56 @@
+"""Traversal copy (rows ordered by activation level) at the edges of its row
+size classes: hubs whose degrees sit around the group, wavefront and tile
+sizes, in both activation modes and with more levels than the level table
+holds.  The activation levels, every result and every work counter equal the
+reference implementation's."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import graphs
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+DEGREES = (1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 4095,
+           4096, 4097, 9001)
+
+
+def hub_graph(seed):
+    """One hub per degree, its edges going to a shared pool of leaves and to
+    the other hubs' leaves; labels of very different counts."""
+    rng = np.random.default_rng(seed)
+    hubs, leaves = len(DEGREES), 10_000
+    n = hubs + leaves + 7   # some isolated nodes
+    edges = set()
+    for h, d in enumerate(DEGREES):
+        for v in rng.choice(leaves, size=d, replace=False):
+            edges.add((h, hubs + int(v), int(min(rng.geometric(0.3), 12))))
+    keywords = [sorted(set(int(x) for x in rng.integers(0, n, size=k))) for k in (3, 5, 9, 40, 200, 2)]
+    weight = rng.integers(0, 200, size=n).astype(np.uint8)
+    return graphs.build(n, edges, keywords, node_weight=weight)
+
+
+@pytest.mark.parametrize("abar_x100", [305, 4000])
+@pytest.mark.parametrize("mode", [0, 1], ids=["edge", "node"])
+def test_row_size_classes(mode, abar_x100):
+    import paper_2001_06770_amd as raks
+    g = hub_graph(abar_x100 + mode)
+    g.abar_x100 = abar_x100
+    o = oracle.Oracle(g)
+    with raks.Context(0, poison=0xA5) as ctx:
+        ctx.load_graph(g, alpha=0.4, mode=mode)
+        for alpha in (0.4, 0.7):
+            if alpha != 0.4:
+                ctx.set_alpha(alpha)
+            act = o.activation(g.abar, alpha, mode)
+            act = act[0] if mode else act
+            np.testing.assert_array_equal(ctx.activations(), act)
+            for q in (synth.Query((0, 1), (2, 3), 5, 9, 60), synth.Query((4, 5), (), 7, 7, 60),
+                      synth.Query((3,), (4, 0, 1), 4, 20, 60)):
+                got = ctx.query(q)
+                for key in ("device_ms", "host_ms", "queue_ms"):
+                    got.pop(key)
+                assert got == o.query(act, q), (alpha, q)
