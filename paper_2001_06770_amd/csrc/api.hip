@@ -332,6 +332,8 @@ int check_graph(Ctx* c, Lane* L) {
                          st, s);
   HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
+  // some arc is nobody's reverse
+  if (!L->h_status->err && 2 * L->h_status->pairs != c->A) L->h_status->err = 8;
   if (L->h_status->err) {
     char msg[160];
     snprintf(msg, sizeof msg,

@@ -53,7 +53,7 @@ struct Status {
   int32_t err;           // graph contract violation bits (load)
   uint64_t cmin, cmax;   // label-count extremes (load)
   uint32_t out_nodes, out_arcs;  // output arena use
-  uint32_t pad[2];
+  uint64_t pairs;        // arcs that searched for their reverse (load)
 };
 
 // Per-workgroup totals of the frontier scan.

@@ -15,46 +15,105 @@
 
 namespace raks {
 
-// number of arcs in row x with label lab
-__device__ inline uint32_t label_run(const uint32_t* row_ptr, const uint16_t* label, uint32_t x,
+// Number of arcs of row [lo, hi) that share arc e's label: the ends of e's run
+// of that label (labels ascend along a row), found by doubling steps from e.
+// Most runs hold one or two arcs, which the neighbours tell.
+__device__ inline uint32_t label_run(const uint16_t* label, uint32_t lo, uint32_t hi, uint32_t e,
                                      uint16_t lab) {
-  uint32_t lo = row_ptr[x], hi = row_ptr[x + 1];
-  uint32_t a = lo, b = hi;
-  while (a < b) { uint32_t m = (a + b) >> 1; if (label[m] < lab) a = m + 1; else b = m; }
-  const uint32_t first = a;
-  b = hi;
-  while (a < b) { uint32_t m = (a + b) >> 1; if (label[m] <= lab) a = m + 1; else b = m; }
-  return a - first;
+  uint32_t first = e, last = e;   // known members of the run
+  uint32_t step = 1;
+  while (first >= lo + step && label[first - step] == lab) { first -= step; step <<= 1; }
+  for (step = min(step, first - lo); step; step >>= 1)
+    while (first >= lo + step && label[first - step] == lab) first -= step;
+  step = 1;
+  while (last + step < hi && label[last + step] == lab) { last += step; step <<= 1; }
+  for (; step; step >>= 1)
+    while (last + step < hi && label[last + step] == lab) last += step;
+  return last - first + 1;
 }
 
-// Checks every arc against the input contract and computes its label count c.
+// Checks every arc against the input contract and computes its label count c
+// and its reverse's position.  An arc and its reverse are found together, by
+// the arc whose target has fewer arcs (ties: the smaller id), so a pair costs
+// one search of the smaller of its two rows; both get the sum of the runs of
+// their label around the two positions.  Every arc has a reverse exactly when
+// each searching arc finds one and half of the arcs search.  A workgroup takes
+// tiles of kCheckTile consecutive arcs; the rows that start in a tile mark
+// their first arc and a block max-scan gives every arc its row.  The random
+// reads of the searches bound it.  24.7M arcs on 1.5M nodes: 6.9 ms with a
+// search per arc in its target's row (a hub's, mostly) and one of all row
+// starts, 2.4 ms now.
+constexpr int kCheckTile = 1024;
+
 __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_ptr,
                                                             const int32_t* col,
                                                             const uint16_t* label, int32_t n,
                                                             uint32_t A, uint32_t* c_out,
                                                             int32_t* arc_src, uint32_t* rev,
                                                             Status* st) {
-  uint32_t err = 0;
+  constexpr int IPT = kCheckTile / kBlock;
+  __shared__ uint32_t s_own[kCheckTile];
+  __shared__ uint32_t s_scan[kBlock / kWave + 1];
+  __shared__ int32_t s_row[2];
+  uint32_t err = 0, found = 0;   // searching arcs
   uint64_t cmin = ~0ull, cmax = 0;
-  for (uint32_t e = blockIdx.x * kBlock + threadIdx.x; e < A; e += gridDim.x * kBlock) {
-    const uint32_t i = row_of(row_ptr, n, e);
-    arc_src[e] = (int32_t)i;
-    const int32_t j = col[e];
-    const uint16_t lab = label[e];
-    if (j < 0 || j >= n) { err |= 1; c_out[e] = 0; rev[e] = kEmpty; continue; }
-    if ((uint32_t)j == i) err |= 2;
-    if (e > row_ptr[i]) {
-      const uint16_t pl = label[e - 1];
-      const int32_t pc = col[e - 1];
-      if (pl > lab || (pl == lab && pc >= j)) err |= 4;
+  const uint32_t tiles = (A - 1) / kCheckTile + 1;   // A > 0
+  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const uint32_t e0 = t * kCheckTile;
+    const uint32_t cnt = min((uint32_t)kCheckTile, A - e0);
+    if (wave_id() < 2) {   // rows of the tile's first and last arc
+      const int r = wave_search(row_ptr, n + 1, wave_id() == 0 ? e0 : e0 + cnt - 1);
+      if (lane_id() == 0) s_row[wave_id()] = r;
     }
-    const uint32_t r = find_arc_dev(row_ptr, col, label, j, lab, (int32_t)i);
-    rev[e] = r;
-    if (r == kEmpty) err |= 8;
-    const uint64_t c = (uint64_t)label_run(row_ptr, label, i, lab) + label_run(row_ptr, label, j, lab);
-    c_out[e] = (uint32_t)c;
-    cmin = c < cmin ? c : cmin;
-    cmax = c > cmax ? c : cmax;
+    for (int i = threadIdx.x; i < kCheckTile; i += kBlock) s_own[i] = 0;
+    __syncthreads();
+    const int r0 = s_row[0], r1 = s_row[1];
+    // of rows with the same start all but the last are empty
+    for (int r = r0 + 1 + (int)threadIdx.x; r <= r1; r += kBlock)
+      atomicMax(&s_own[row_ptr[r] - e0], (uint32_t)(r - r0));
+    __syncthreads();
+    uint32_t loc[IPT], m = 0;
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const uint32_t o = s_own[threadIdx.x * IPT + k];
+      m = o > m ? o : m;
+      loc[k] = m;
+    }
+    const uint32_t pre = block_exclusive_max(m, s_scan);
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) s_own[threadIdx.x * IPT + k] = pre > loc[k] ? pre : loc[k];
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < IPT; ++k) {
+      const uint32_t q = k * kBlock + threadIdx.x;
+      if (q >= cnt) continue;
+      const uint32_t e = e0 + q;
+      const uint32_t i = (uint32_t)r0 + s_own[q];
+      arc_src[e] = (int32_t)i;
+      const int32_t j = col[e];
+      const uint16_t lab = label[e];
+      if (j < 0 || j >= n) { err |= 1; continue; }
+      if ((uint32_t)j == i) { err |= 2; continue; }
+      const uint32_t lo = row_ptr[i], hi = row_ptr[i + 1];
+      const uint32_t jlo = row_ptr[j], jhi = row_ptr[j + 1];
+      if (e > lo) {
+        const uint16_t pl = label[e - 1];
+        const int32_t pc = col[e - 1];
+        if (pl > lab || (pl == lab && pc >= j)) err |= 4;
+      }
+      if (jhi - jlo > hi - lo || (jhi - jlo == hi - lo && (uint32_t)j > i)) continue;
+      ++found;
+      const uint32_t r = find_arc_dev(jlo, jhi, col, label, lab, (int32_t)i);
+      if (r == kEmpty) { err |= 8; continue; }
+      rev[e] = r;
+      rev[r] = e;
+      const uint64_t c = (uint64_t)label_run(label, lo, hi, e, lab) + label_run(label, jlo, jhi, r, lab);
+      c_out[e] = (uint32_t)c;
+      c_out[r] = (uint32_t)c;
+      cmin = c < cmin ? c : cmin;
+      cmax = c > cmax ? c : cmax;
+    }
+    __syncthreads();
   }
   // wave reductions, then one atomic per wave
 #pragma unroll
@@ -63,8 +122,10 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
     cmin = a < cmin ? a : cmin;
     cmax = b > cmax ? b : cmax;
     err |= __shfl_xor(err, d, kWave);
+    found += __shfl_xor(found, d, kWave);
   }
   if (lane_id() == 0) {
+    if (found) atomicAdd((unsigned long long*)&st->pairs, (unsigned long long)found);
     if (err) atomicOr(&st->err, (int32_t)err);
     atomicMin((unsigned long long*)&st->cmin, (unsigned long long)cmin);
     atomicMax((unsigned long long*)&st->cmax, (unsigned long long)cmax);
@@ -441,6 +502,7 @@ void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s)
 __global__ void k_status_reset_minmax(Status* st) {
   st->cmin = ~0ull;
   st->cmax = 0;
+  st->pairs = 0;
   st->err = 0;
 }
 
@@ -456,8 +518,8 @@ void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc
                             Status* st, hipStream_t s) {
   k_status_reset_minmax<<<1, 1, 0, s>>>(st);
   if (g.A > 0)
-    k_check_and_count<<<grid_for(g.A), kBlock, 0, s>>>(g.row_ptr_o, g.col, g.label, g.n, g.A, c_tmp,
-                                                        arc_src, rev, st);
+    k_check_and_count<<<grid_for((g.A - 1) / 4 + 1), kBlock, 0, s>>>(
+        g.row_ptr_o, g.col, g.label, g.n, g.A, c_tmp, arc_src, rev, st);
 }
 
 void launch_node_weight_range(const DevGraphView& g, const uint8_t* nw, Status* st,

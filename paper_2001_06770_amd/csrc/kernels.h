@@ -223,22 +223,16 @@ struct FinalizeView {
   Status* gst;
 };
 
-// Position of arc (src -> dst, lab) in row src (rows sorted by (label, dst)),
-// or kEmpty when absent.
-__device__ inline uint32_t find_arc_dev(const uint32_t* row_ptr, const int32_t* col,
-                                        const uint16_t* label, int32_t src, uint16_t lab,
-                                        int32_t dst) {
-  uint32_t a = row_ptr[src], b = row_ptr[src + 1];
-  const uint32_t hi = b;
+// Position of the arc to `dst` with label `lab` in the row [lo, hi) (sorted by
+// (label, dst)), or kEmpty when absent.
+__device__ inline uint32_t find_arc_dev(uint32_t lo, uint32_t hi, const int32_t* col,
+                                        const uint16_t* label, uint16_t lab, int32_t dst) {
+  uint32_t a = lo, b = hi;
   while (a < b) {
-    uint32_t m = (a + b) >> 1;
+    const uint32_t m = a + ((b - a) >> 1);
     if (label[m] < lab || (label[m] == lab && col[m] < dst)) a = m + 1; else b = m;
   }
   return (a < hi && label[a] == lab && col[a] == dst) ? a : kEmpty;
-}
-
-__device__ inline uint32_t row_of(const uint32_t* row_ptr, int32_t n, uint32_t e) {
-  return (uint32_t)upper_index<uint32_t>(row_ptr, 0, n + 1, e);
 }
 
 // max_sel: an upper bound of the device-side nsel (one workgroup per CG)

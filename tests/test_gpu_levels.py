@@ -54,3 +54,29 @@ def test_row_size_classes(mode, abar_x100):
                 for key in ("device_ms", "host_ms", "queue_ms"):
                     got.pop(key)
                 assert got == o.query(act, q), (alpha, q)
+
+
+@pytest.mark.parametrize("drop", ["hub_to_leaf", "leaf_to_hub", "leaf_to_leaf", "both_sides"])
+def test_missing_reverse_arc_rejected(drop):
+    """A graph with one arc's reverse taken out breaks the contract, whichever
+    end has the larger row; so does one that lacks as many arcs on either side."""
+    import paper_2001_06770_amd as raks
+    g = graphs.build(1200, [(0, v, v % 3) for v in range(1, 1101)] + [(1150, 1151, 2), (1, 2, 0)],
+                     [[0], [1]])
+
+    def without(src, dst):
+        e = int(g.row_ptr[src]) + int(np.nonzero(g.col[g.row_ptr[src]:g.row_ptr[src + 1]] == dst)[0][0])
+        g.col, g.label = np.delete(g.col, e), np.delete(g.label, e)
+        g.row_ptr = g.row_ptr - (np.arange(g.row_ptr.shape[0]) > src)
+
+    with raks.Context(0) as ctx:
+        ctx.load_graph(g, alpha=0.5)
+        if drop in ("hub_to_leaf", "both_sides"):
+            without(0, 700)
+        if drop in ("leaf_to_hub", "both_sides"):
+            without(801, 0)
+        if drop == "leaf_to_leaf":
+            without(1151, 1150)
+        with pytest.raises(raks.RaksError) as e:
+            ctx.load_graph(g, alpha=0.5)
+        assert e.value.code == -1
