@@ -139,8 +139,7 @@ DevGraphView graph_view(const Lane* L) { return graph_view(L->ctx, *L->view); }
 
 std::vector<DevBuf*> lane_buffers(Lane* L) {
   std::vector<DevBuf*> v = {
-      &L->Hc, &L->Hm, &L->Hq, &L->R, &L->tot, &L->sb, &L->q_off, &L->q_rs, &L->q_lo,
-      &L->q_mask, &L->tile_first, &L->cand, &L->s_item, &L->s_cand, &L->sel_node, &L->sel_sc,
+      &L->Hc, &L->Hm, &L->Hq, &L->R, &L->tot, &L->brief, &L->cand, &L->s_item, &L->s_cand, &L->sel_node, &L->sel_sc,
       &L->sel_sumh, &L->has_rpg, &L->sm, &L->key, &L->dmin, &L->ranked, &L->vc_cnt,
       &L->vc_tmp, &L->vc_off, &L->vc_nodes, &L->hpool, &L->nl, &L->al, &L->items, &L->sort_a,
       &L->sort_b, &L->cg_nodes, &L->cg_arcs, &L->cg_cnt, &L->hdr, &L->out_nodes, &L->out_arcs,
@@ -560,15 +559,10 @@ int ensure_node_buffers(Lane* L) {
   L->cpw = (chunks + kScanGroups - 1) / kScanGroups;
   L->nblocks = (chunks + L->cpw - 1) / L->cpw;
   const size_t np = (size_t)L->n_pad;
-  RAKS_TRY(dev_alloc(c, L->R, np * 2));
+  RAKS_TRY(dev_alloc(c, L->R, np * 4));   // up to 2 bytes per node for each run
   RAKS_TRY(dev_alloc(c, L->tot, (size_t)L->nblocks * sizeof(ScanTot)));
-  RAKS_TRY(dev_alloc(c, L->sb, (size_t)2 * kSupers * 3 * 4));
-  RAKS_TRY(dev_alloc(c, L->q_off, (np + 1) * 4));
-  RAKS_TRY(dev_alloc(c, L->q_rs, np * 4));
-  RAKS_TRY(dev_alloc(c, L->q_lo, np * 4));
-  RAKS_TRY(dev_alloc(c, L->q_mask, np * 4));
-  RAKS_TRY(dev_alloc(c, L->tile_first, ((size_t)c->A / kExpandTile + 2) * 4));
-  RAKS_TRY(dev_alloc(c, L->cand, np * 8));
+  RAKS_TRY(dev_alloc(c, L->brief, (size_t)L->nblocks * (sizeof(uint2) + 4)));
+  RAKS_TRY(dev_alloc(c, L->cand, (size_t)kMaxW * 8));
   RAKS_TRY(dev_alloc(c, L->s_item, np * 16));
   RAKS_TRY(dev_alloc(c, L->s_cand, np * 8));
   return ensure_small_buffers(L);
@@ -595,20 +589,16 @@ RunView run_view(Lane* L, int kind, int T, DevBuf& H, const QueryPlan& p) {
   r.tmask = (T >= 32) ? 0xFFFFFFFFu : ((1u << T) - 1);
   r.block_rule = (kind == RUN_CENTRAL) ? 1 : (T >= 2 ? 1 : 0);
   r.H = P<uint8_t>(H);
-  r.R = L->R.p;
+  r.R = P<uint8_t>(L->R) + (kind == RUN_MARGINAL ? (size_t)L->n_pad * 2 : 0);
   r.n_pad = L->n_pad;
   r.st = &P<Status>(L->status)->run[kind];
   r.tot = P<ScanTot>(L->tot);
-  r.sb = P<uint32_t>(L->sb);
+  r.brief = P<uint2>(L->brief);
+  r.ncand = reinterpret_cast<uint32_t*>(r.brief + L->nblocks);
   r.nblocks = L->nblocks;
   r.cpw = L->cpw;
   r.s_item = P<uint4>(L->s_item);
   r.s_cand = P<uint64_t>(L->s_cand);
-  r.q_lo = P<uint32_t>(L->q_lo);
-  r.q_off = P<uint32_t>(L->q_off);
-  r.q_rs = P<uint32_t>(L->q_rs);
-  r.q_mask = P<uint32_t>(L->q_mask);
-  r.tile_first = P<uint32_t>(L->tile_first);
   r.cand = P<uint64_t>(L->cand);
   r.max_level = p.L;
   r.w = p.w;
@@ -630,6 +620,7 @@ RunView run_view(Lane* L, int kind, int T, DevBuf& H, const QueryPlan& p) {
 
 __global__ void k_query_reset(Status* st) {
   st->nsel = 0;
+  st->sel_ticket = 0;
   st->nres = 0;
   st->overflow = 0;
   st->out_nodes = 0;
@@ -666,40 +657,29 @@ int wait_status(Lane* L, int slot, uint64_t want) {
 // l+1 before it waits for the status of level l, so the GPU never idles on
 // the host's decision; the kernels of a level after the run's end return at
 // once.  Returns the run's final status in *last.
-int run_levels(Lane* L, RunView& r, int TP, const std::vector<int32_t>& kws, int T,
-               RunStatus* last) {
+int run_levels(Lane* L, RunView& r, int TP, int T, RunStatus* last) {
   Ctx* c = L->ctx;
   hipStream_t s = L->stream;
   const DevGraphView g = graph_view(L);
-  const SeedList seeds = seeds_for(c, kws);
-  {
-    Timed t(L, 4);
-    launch_run_init(r, TP, c->n, P<int32_t>(c->kw_nodes), seeds, s);
-  }
-  const int grid = c->num_cu * 8;
   // The control step writes the level's status into the pinned slot and
   // then stamps it with the launch's number, so the host learns the decision
-  // while the level's enqueue and expansion still run, without an event
+  // while the level's expansion still runs, without an event
   // (an event record after every control launch costs the stream several
   // microseconds per level).
   uint64_t want[2] = {0, 0};
   auto enqueue = [&](int level, int slot) -> int {
     {
       Timed t(L, 1, level, r.kind);
-      launch_front_count(r, TP, g, level, s);
+      launch_front_scan(r, TP, g, level, s);
     }
-    {
-      Timed t(L, 2, level, r.kind);
-      want[slot] = ++L->ctl_seq;
-      launch_front_enqueue(r, TP, level, &L->d_run[slot], want[slot], s);
-    }
+    want[slot] = ++L->ctl_seq;
     if (timing_mask(L) & 1u) {
       // expansion timing: the launch itself stamps the two events
       hipEvent_t a = next_event(L), b = next_event(L);
-      launch_expand(r, TP, g, level, grid, s, a, b);
+      launch_expand(r, TP, g, level, c->num_cu, &L->d_run[slot], want[slot], s, a, b);
       if (a && b) L->pending.push_back({a, b, 0, 0.0, level, r.kind});
     } else {
-      launch_expand(r, TP, g, level, grid, s);
+      launch_expand(r, TP, g, level, c->num_cu, &L->d_run[slot], want[slot], s);
     }
     HIP_OK(hipGetLastError());
     return RAKS_OK;
@@ -1134,18 +1114,42 @@ int big_finalize(Lane* L, int ph, const QueryPlan& p, int n_res, const uint8_t* 
   return RAKS_OK;
 }
 
+// Initial state of both runs (or of the marginal run alone, for a repeat).
+int stage_init(Lane* L, const QueryPlan& p, bool central) {
+  Timed t(L, 4);
+  const RunView rc = run_view(L, RUN_CENTRAL, p.C, L->Hc, p);
+  RunView rm = {};
+  SeedList sm = {};
+  if (p.M > 0) {
+    rm = run_view(L, RUN_MARGINAL, p.M, L->Hm, p);
+    sm = seeds_for(L->ctx, p.marginal);
+  }
+  launch_query_init(P<Status>(L->status), rc, p.TPc, seeds_for(L->ctx, p.central), rm, p.TPm, sm,
+                    central, P<int32_t>(L->ctx->kw_nodes), L->stream);
+  HIP_OK(hipGetLastError());
+  return RAKS_OK;
+}
+
 // Central run and top-w selection.
 int stage_central(Lane* L, const QueryPlan& p, QueryRun& q) {
   hipStream_t s = L->stream;
   Status* st = P<Status>(L->status);
   HIP_OK(hipEventRecord(L->q_start, s));
-  k_query_reset<<<1, 1, 0, s>>>(st);
+  RAKS_TRY(stage_init(L, p, true));
   RunView r1 = run_view(L, RUN_CENTRAL, p.C, L->Hc, p);
-  RAKS_TRY(run_levels(L, r1, p.TPc, p.central, p.C, &q.s1));
+  RAKS_TRY(run_levels(L, r1, p.TPc, p.C, &q.s1));
   q.top1 = std::max(0, q.s1.levels - 1);   // central levels are at most this
-  SelectView sv;
+  SelectView sv = {};
   sv.int_id = P<int32_t>(L->ctx->int_id);
   sv.cand = P<uint64_t>(L->cand);
+  sv.ncand = r1.ncand;
+  sv.s_cand = r1.s_cand;
+  sv.nblocks = r1.nblocks;
+  sv.cpw = r1.cpw;
+  // the staged entries are done with: scratch of the selection's parts (only
+  // graphs whose entries hold more than that have several)
+  sv.part_keys = reinterpret_cast<uint64_t*>(r1.s_item);
+  sv.part_n = reinterpret_cast<uint32_t*>(sv.part_keys + (size_t)kSelParts * kMaxW);
   sv.st = r1.st;
   sv.gst = st;
   sv.w = p.w;
@@ -1173,7 +1177,8 @@ int stage_cg_recovery(Lane* L, const QueryPlan& p, const QueryRun& q) {
       const char* lay0 = static_cast<const char*>(L->ph[0].layout.p);
       launch_pack_vc(P<uint32_t>(L->vc_cnt), P<int32_t>(L->vc_tmp),
                      reinterpret_cast<const uint64_t*>(lay0 + L->ph[0].lay_cg_noff), &st->nsel,
-                     P<uint32_t>(L->vc_off), P<int32_t>(L->vc_nodes), p.w, s);
+                     P<uint32_t>(L->vc_off), P<int32_t>(L->vc_nodes), p.w,
+                     &st->run[RUN_MARGINAL], s);
     }
   }
   HIP_OK(hipGetLastError());
@@ -1187,8 +1192,9 @@ int stage_marginal(Lane* L, const QueryPlan& p, QueryRun& q) {
   q.top2 = 0;
   if (p.M > 0) {
     RunView r2 = run_view(L, RUN_MARGINAL, p.M, L->Hm, p);
-    RAKS_TRY(run_levels(L, r2, p.TPm, p.marginal, p.M, &q.s2));
-    q.top2 = std::max(0, q.s2.levels - 1);
+    RAKS_TRY(run_levels(L, r2, p.TPm, p.M, &q.s2));
+    // the RPGs start at V_C nodes at distance D_j <= S^m
+    q.top2 = std::min(std::max(0, q.s2.levels - 1), q.s2.max_sm);
   }
   (void)st;
   Timed t(L, 2);
@@ -1454,6 +1460,7 @@ int query_plan_on_lane(Lane* L, const QueryPlan& p, raks_results** out, raks_res
     RAKS_TRY(ensure_recovery(L, p));
     k_retry_reset<<<1, 1, 0, L->stream>>>(P<Status>(L->status));
     if (redo_cg) {
+      if (p.M > 0) RAKS_TRY(stage_init(L, p, false));
       RAKS_TRY(stage_cg_recovery(L, p, qr));
       RAKS_TRY(stage_marginal(L, p, qr));
     }
@@ -1536,12 +1543,11 @@ void serve_worker(Ctx* c, Lane* L) {
 }
 
 // Device bytes one lane holds on this graph: per node the two H matrices for
-// up to 16 keywords per run, the reached masks, the expansion queue, the
-// candidate keys and the scan's staging; the tile map; a recovery allowance.
+// up to 16 keywords per run, the reached masks and the scan's staging; a
+// recovery allowance.
 size_t lane_bytes_estimate(const Ctx* c) {
   const size_t np = (size_t)c->n + kScanNodes;
-  return np * (16 + 16 + 2 + 16 + 8 + 16 + 8) + ((size_t)c->A / kExpandTile + 2) * 4 +
-         ((size_t)64 << 20);
+  return np * (16 + 16 + 4 + 16 + 8) + ((size_t)64 << 20);
 }
 
 // Drains the queue: queries already submitted still run; their results are

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace raks {
 
 constexpr int kWave = 64;          // CDNA wavefront width
@@ -13,9 +15,7 @@ constexpr int kBlock = 256;        // threads per workgroup for most kernels
 constexpr int kScanPer = 4;        // nodes per frontier-scan thread
 constexpr int kScanNodes = 1024;   // nodes per frontier-scan chunk (kBlock * kScanPer)
 constexpr int kScanGroups = 2048;  // at most this many frontier-scan workgroups
-constexpr int kSuper = 64;         // scan workgroups per superblock of the enqueue prefix
-constexpr int kSupers = kScanGroups / kSuper;
-constexpr int kExpandTile = 1024;  // arcs per expansion tile
+constexpr int kWaveTile = 256;     // arcs per expansion tile, one wavefront's
 constexpr int kMaxKw = 16;         // keywords per run
 constexpr int kMaxW = 256;         // beam width limit
 constexpr uint8_t kInf = 0xFF;     // "not reached" in the node-keyword matrix
@@ -28,18 +28,20 @@ enum EndReason : int { END_NONE = 0, END_EXHAUSTED = 1, END_STOP = 2, END_LEVEL_
                        END_EMPTY_KEYWORD = 4 };
 
 // Device-resident state of one run (central or marginal), updated by the
-// control step (workgroup 0 of the enqueue launch) at every level.
+// control step (workgroup 0 of the expansion launch) at every level.
 struct RunStatus {
   int32_t end_level;     // level at which the run ended; INT32_MAX while running
   int32_t end_reason;
   int32_t expand_on;     // 1 if the expansion of the current level runs
   int32_t levels;        // identification passes made
   uint32_t nfront;       // |frontier| of the current level
-  uint32_t nactive;      // queue entries (frontiers with arcs to examine at this level)
+  uint32_t nactive;      // staged entries (frontiers with arcs to examine at this level)
   uint32_t W;            // arcs examined by the expansion of this level
   uint32_t ncand_level;  // central nodes identified at the current level
   uint32_t ncand_total;  // central nodes identified so far
   uint32_t nrpg;         // CGs with an RPG so far (marginal run)
+  int32_t rpg_stop;      // the RPG check of the current level asks for the end
+  int32_t max_sm;        // largest S^m of the RPGs so far
   uint32_t cand_base[2]; // [l & 1]: central nodes identified before level l
   uint64_t frontier_sum, e_arc, e_alg, gate_pass, h_writes;
   uint64_t seq;          // host mirror only: number of the control launch that wrote it
@@ -54,21 +56,18 @@ struct Status {
   uint64_t cmin, cmax;   // label-count extremes (load)
   uint32_t out_nodes, out_arcs;  // output arena use
   uint64_t pairs;        // arcs that searched for their reverse (load)
+  uint32_t sel_ticket;   // workgroups of the selection that are done; 0 between selections
+  uint32_t pad;
 };
 
-// Per-workgroup totals of the frontier scan.
+// Per-workgroup totals of the frontier scan that the level's record sums up.
 struct ScanTot {
-  uint32_t nfront;       // flagged nodes
-  uint32_t nq;           // queue entries (nodes with arcs to examine at this level)
-  uint32_t ncand;        // central nodes identified
-  uint32_t work;         // arcs the GPU examines (sum of queue entry ranges)
+  uint32_t nfront;       // frontier nodes
   uint32_t hw;           // hitting levels written by the previous expansion
-  uint32_t pad;
   uint64_t deg;          // sum of degrees of expanding frontiers (Algorithm 1 scans)
   uint64_t degk;         // sum of degree * expanding keywords
   uint64_t gate;         // arcs with level <= l of expanding frontiers
 };
-
 
 // Output header of one result.
 struct ResultHdr {
@@ -84,56 +83,50 @@ struct ResultHdr {
 __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ inline int wave_id() { return threadIdx.x / kWave; }
 
+// Lane moves of the wavefront scans: a DPP move costs one vector instruction,
+// a shuffle through the LDS unit some sixty cycles of latency per step.  Lanes
+// without a source get 0.  Controls: 0x110 + n row_shr:n, 0x138 wave_shr:1,
+// 0x142 row_bcast:15, 0x143 row_bcast:31.
+template <int Ctrl, int RowMask>
+__device__ inline uint32_t dpp_move(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xF, false);
+}
+template <int Ctrl, int RowMask>
+__device__ inline uint64_t dpp_move(uint64_t v) {
+  return ((uint64_t)dpp_move<Ctrl, RowMask>((uint32_t)(v >> 32)) << 32) |
+         dpp_move<Ctrl, RowMask>((uint32_t)v);
+}
+
+// Inclusive scan over the wavefront by `op` (0 is neutral): within rows of 16
+// lanes by shifts of 1, 2, 4 and 8, then row ends broadcast to the next row
+// (row_bcast:15) and lane 31 to the upper half (row_bcast:31).
+template <typename T, typename Op>
+__device__ inline T wave_scan_op(T v, Op op) {
+  v = op(v, dpp_move<0x111, 0xF>(v));
+  v = op(v, dpp_move<0x112, 0xF>(v));
+  v = op(v, dpp_move<0x114, 0xF>(v));
+  v = op(v, dpp_move<0x118, 0xF>(v));
+  v = op(v, dpp_move<0x142, 0xA>(v));
+  v = op(v, dpp_move<0x143, 0xC>(v));
+  return v;
+}
+
 template <typename T>
 __device__ inline T wave_inclusive_scan(T v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    T o = __shfl_up(v, d, kWave);
-    if (lane >= d) v += o;
-  }
-  return v;
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "integer scans");
+  using U = typename std::conditional<sizeof(T) == 4, uint32_t, uint64_t>::type;
+  return (T)wave_scan_op((U)v, [](U a, U b) { return a + b; });
 }
 
-template <typename T>
-__device__ inline T wave_sum(T v) {
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-
-// Exclusive scan over a block of NT threads (NT multiple of 64, <= 1024);
-// `scratch` holds NT/64 + 1 elements of T in LDS.  Returns the exclusive
-// prefix; *total receives the block total.  Contains __syncthreads.
-template <typename T, int NT>
-__device__ inline T block_exclusive_scan(T v, T* scratch, T* total) {
-  constexpr int NW = NT / kWave;
-  T inc = wave_inclusive_scan(v);
-  if (lane_id() == kWave - 1) scratch[wave_id()] = inc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    T acc = 0;
-    for (int w = 0; w < NW; ++w) { T t = scratch[w]; scratch[w] = acc; acc += t; }
-    scratch[NW] = acc;
-  }
-  __syncthreads();
-  T res = scratch[wave_id()] + inc - v;
-  *total = scratch[NW];
-  __syncthreads();
-  return res;
-}
-
-template <typename T, int NT>
-__device__ inline T block_sum(T v, T* scratch) {
-  T tot;
-  (void)block_exclusive_scan<T, NT>(v, scratch, &tot);
-  return tot;
+__device__ inline uint32_t wave_last(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1); }
+__device__ inline uint64_t wave_last(uint64_t v) {
+  return ((uint64_t)wave_last((uint32_t)(v >> 32)) << 32) | wave_last((uint32_t)v);
 }
 
 // Exclusive scans of N values at once over a block of NT threads: one LDS
-// exchange (two barriers) for all of them.  `scratch` holds (NT/64 + 1) * N
-// 64-bit words.  v[] is replaced by the exclusive prefixes, tot[] gets the
-// block totals.
+// exchange for all of them (every thread adds up the totals of the wavefronts
+// before its own).  `scratch` holds (NT/64 + 1) * N values.  v[] is replaced by
+// the exclusive prefixes, tot[] gets the block totals.
 template <int N, int NT, typename T = uint64_t>
 __device__ inline void block_exclusive_scan_multi(T (&v)[N], T (&tot)[N], T* scratch) {
   constexpr int NW = NT / kWave;
@@ -144,44 +137,76 @@ __device__ inline void block_exclusive_scan_multi(T (&v)[N], T (&tot)[N], T* scr
 #pragma unroll
     for (int k = 0; k < N; ++k) scratch[wave_id() * N + k] = inc[k];
   __syncthreads();
-  if (threadIdx.x < N) {
-    const int k = threadIdx.x;
-    T acc = 0;
-    for (int w = 0; w < NW; ++w) { const T t = scratch[w * N + k]; scratch[w * N + k] = acc; acc += t; }
-    scratch[NW * N + k] = acc;
-  }
-  __syncthreads();
+  const int wv = wave_id();
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    const T x = v[k];
-    v[k] = scratch[wave_id() * N + k] + inc[k] - x;
-    tot[k] = scratch[NW * N + k];
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const T t = scratch[w * N + k];
+      if (w < wv) before += t;
+      all += t;
+    }
+    v[k] = before + inc[k] - v[k];
+    tot[k] = all;
   }
   __syncthreads();
+}
+
+// Block totals of N values over NT threads in scratch[0 .. N), from LDS after
+// the call; `scratch` holds (NT/64 + 1) * N values.
+template <int N, int NT, typename T>
+__device__ inline void block_totals(const T (&v)[N], T* scratch) {
+  constexpr int NW = NT / kWave;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const T inc = wave_inclusive_scan(v[k]);
+    if (lane_id() == kWave - 1) scratch[(wave_id() + 1) * N + k] = inc;
+  }
+  __syncthreads();
+  if (threadIdx.x < N) {
+    T acc = 0;
+#pragma unroll 1
+    for (int w = 1; w <= NW; ++w) acc += scratch[w * N + threadIdx.x];
+    scratch[threadIdx.x] = acc;
+  }
+  __syncthreads();
+}
+
+// Exclusive scan over a block of NT threads (NT multiple of 64, <= 1024);
+// `scratch` holds NT/64 + 1 elements of T in LDS.  Returns the exclusive
+// prefix; *total receives the block total.  Contains __syncthreads.
+template <typename T, int NT>
+__device__ inline T block_exclusive_scan(T v, T* scratch, T* total) {
+  T x[1] = {v}, t[1];
+  block_exclusive_scan_multi<1, NT, T>(x, t, scratch);
+  *total = t[0];
+  return x[0];
+}
+
+template <typename T, int NT>
+__device__ inline T block_sum(T v, T* scratch) {
+  T tot;
+  (void)block_exclusive_scan<T, NT>(v, scratch, &tot);
+  return tot;
 }
 
 // Exclusive max-scan over a block of kBlock threads of non-negative values;
 // `scratch` holds kBlock/64 + 1 words of LDS.  Contains __syncthreads.
 __device__ inline uint32_t block_exclusive_max(uint32_t v, uint32_t* scratch) {
-  const int lane = lane_id();
-  uint32_t inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t o = __shfl_up(inc, d, kWave);
-    if (lane >= d) inc = inc > o ? inc : o;
-  }
-  if (lane == kWave - 1) scratch[wave_id()] = inc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t acc = 0;
-    for (int w = 0; w < kBlock / kWave; ++w) { const uint32_t t = scratch[w]; scratch[w] = acc; acc = acc > t ? acc : t; }
-  }
+  const uint32_t inc = wave_scan_op(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+  if (lane_id() == kWave - 1) scratch[wave_id()] = inc;
   __syncthreads();
   uint32_t ex = __shfl_up(inc, 1, kWave);
-  if (lane == 0) ex = 0;
-  const uint32_t w = scratch[wave_id()];
+  if (lane_id() == 0) ex = 0;
+  const int wv = wave_id();
+#pragma unroll
+  for (int w = 0; w < kBlock / kWave; ++w) {
+    const uint32_t t = scratch[w];
+    if (w < wv) ex = ex > t ? ex : t;
+  }
   __syncthreads();
-  return ex > w ? ex : w;
+  return ex;
 }
 
 // Last index j in [0, n) with a[j] <= x (a non-decreasing, a[0] <= x), found

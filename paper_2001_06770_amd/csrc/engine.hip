@@ -525,9 +525,14 @@ int enqueue_cg(Engine& E, CoQuery* q) {
   cv.st = P<RunStatus>(E.cst);
   cv.orig_id = P<int32_t>(c->orig_id);
   launch_co_cand(cv, E.v, s);
-  SelectView sv;
+  SelectView sv = {};
   sv.int_id = P<int32_t>(c->int_id);
   sv.cand = P<uint64_t>(E.cand);
+  sv.nblocks = E.v.nblocks;
+  sv.cpw = E.v.cpw;
+  // between levels the staged entries are done with: scratch, as on the single path
+  sv.part_keys = reinterpret_cast<uint64_t*>(E.v.stage);
+  sv.part_n = reinterpret_cast<uint32_t*>(sv.part_keys + (size_t)kSelParts * kMaxW);
   sv.st = P<RunStatus>(E.cst);
   sv.gst = st;
   sv.w = q->p.w;
@@ -543,7 +548,7 @@ int enqueue_cg(Engine& E, CoQuery* q) {
     const char* lay0 = static_cast<const char*>(L->ph[0].layout.p);
     launch_pack_vc(P<uint32_t>(L->vc_cnt), P<int32_t>(L->vc_tmp),
                    reinterpret_cast<const uint64_t*>(lay0 + L->ph[0].lay_cg_noff), &st->nsel,
-                   P<uint32_t>(L->vc_off), P<int32_t>(L->vc_nodes), q->p.w, s);
+                   P<uint32_t>(L->vc_off), P<int32_t>(L->vc_nodes), q->p.w, nullptr, s);
   }
   q->cg_seq = ++E.cg_no;
   launch_co_cg_done(E.v, q->slot, st, q->cg_seq, s);

@@ -1,27 +1,29 @@
 // explore.hip -- exploration phase (Section 4.2) on gfx950.
 //
-// One level of a run is three launches:
-//   k_front_count   frontier scan: every workgroup takes a run of 1024-node
+// One level of a run is two launches:
+//   k_front_scan    frontier scan: every workgroup takes a run of 1024-node
 //                   chunks (4 nodes per thread), reads their H rows and row
 //                   levels in node order, decides frontier membership from
 //                   them, inspects every frontier node once (complete row ->
 //                   central node / PTC block, keywords with h <= level, level
-//                   slice of the row), stages its queue entry and central-node
-//                   key in node order and refreshes its reached mask; then
-//                   writes its totals;
-//   k_front_enqueue workgroup 0 sums the totals, applies the run's
-//                   identification and termination rules (Theorem identifyCG,
-//                   >= w CGs; the RPG check over each CG's V_C rows and
-//                   Theorem 4) and decides whether this level expands; the
-//                   other workgroups, one per scan workgroup, do Frontier
-//                   Enqueue: they copy the staged entries to the expansion
-//                   queue (node order, arc prefix) and the central nodes to
-//                   the candidate list;
+//                   slice of the row), stages its expansion entry and
+//                   central-node key in node order in its own range and
+//                   refreshes its reached mask; then writes its totals.  In a
+//                   marginal run one more workgroup checks the RPGs beside it
+//                   (the check over each CG's V_C rows and Theorem 4 need
+//                   nothing of the scan);
 //   k_expand        Algorithm 1 for every (frontier, arc) pair, balanced by
-//                   arcs: each workgroup takes tiles of 1024 consecutive arcs
-//                   of the concatenated frontier rows, so a hub's arcs spread
-//                   over many workgroups; one H-row gather serves all keywords
-//                   of the frontier at once.
+//                   arcs: each wavefront takes runs of tiles of 256 consecutive
+//                   arcs of the scan workgroups' staged slices, so a hub's arcs
+//                   spread over many wavefronts; one mask gather serves all
+//                   keywords of the frontier at once.  Every workgroup derives
+//                   from the scan's totals whether the run ends at this level
+//                   (Theorem identifyCG, >= w CGs, the RPG check's answer) and
+//                   where its tile's entries lie; workgroup 0 is the control
+//                   step that records the level and tells the host.
+// A launch of its own between the two (control step and a copy of the staged
+// entries into one queue) took 9 to 14 us per level, up to 31 us when a hub's
+// tiles were mapped, on a loop whose levels take 20 us on small graphs.
 // Writes need no atomics (Theorem "lockfree"): every H write of a level
 // stores level+1 into a byte that was INF.  Neither the frontier flags nor
 // the joining flag array is stored, both are implied by H: a node is blocked
@@ -43,21 +45,9 @@ template <> struct RowVec<16> { using T = uint4; };
 
 // Per-node mask of the keywords whose hitting level is finite: 4 bits per
 // node for up to 4 keywords (two nodes per byte, so the array that every
-// expansion gathers from is half as large), 8 or 16 bits otherwise.  W holds
-// the masks of the kScanPer consecutive nodes of one scan thread.
-template <int TP> struct RMask { using T = uint8_t; };
-template <> struct RMask<16> { using T = uint16_t; };
-template <int TP> using RMaskT = typename RMask<TP>::T;
-
-template <int Bits> struct UintOf;
-template <> struct UintOf<8> { using T = uint8_t; };
-template <> struct UintOf<16> { using T = uint16_t; };
-template <> struct UintOf<32> { using T = uint32_t; };
-template <> struct UintOf<64> { using T = uint64_t; };
-
+// expansion gathers from is half as large), 8 or 16 bits otherwise.
 template <int TP> struct RBits {
-  static constexpr int kBits = TP == 4 ? 4 : (TP == 8 ? 8 : 16);   // bits per node
-  using W = typename UintOf<kBits * kScanPer>::T;
+  static constexpr int kBits = r_bits(TP);   // bits per node
   __device__ static uint32_t get(const void* R, int64_t v) {
     if constexpr (kBits == 4)
       return (reinterpret_cast<const uint8_t*>(R)[v >> 1] >> ((v & 1) * 4)) & 0xFu;
@@ -66,18 +56,16 @@ template <int TP> struct RBits {
     else
       return reinterpret_cast<const uint16_t*>(R)[v];
   }
-  // the word of node v's scan thread (v a multiple of kScanPer)
-  __device__ static W* group(void* R, int64_t v) {
-    return reinterpret_cast<W*>(reinterpret_cast<uint8_t*>(R) + v * kBits / 8);
-  }
-  __device__ static uint32_t unpack(W w, int k) {
-    return (uint32_t)(w >> (kBits * k)) & ((1u << kBits) - 1u);
-  }
-  __device__ static W pack(const uint32_t (&m)[kScanPer]) {
-    W w = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) w |= (W)(m[k] & ((1u << kBits) - 1u)) << (kBits * k);
-    return w;
+  // stores the masks of a wavefront's nodes v = first + lane (first even)
+  __device__ static void put(void* R, int64_t v, uint32_t m) {
+    if constexpr (kBits == 4) {
+      const uint32_t odd = dpp_move<0xF5, 0xF>(m);   // quad_perm(1,1,3,3): the odd neighbour's
+      if ((v & 1) == 0) reinterpret_cast<uint8_t*>(R)[v >> 1] = (uint8_t)(m | (odd << 4));
+    } else if constexpr (kBits == 8) {
+      reinterpret_cast<uint8_t*>(R)[v] = (uint8_t)m;
+    } else {
+      reinterpret_cast<uint16_t*>(R)[v] = (uint16_t)m;
+    }
   }
 };
 
@@ -88,42 +76,82 @@ __device__ inline void load_row(const uint8_t* H, int64_t v, uint8_t (&b)[TP]) {
   __builtin_memcpy(b, &x, TP);
 }
 
-// ------------------------------------------------------------- run init ---
+// ----------------------------------------------------------- query init ---
 
-// A run with a keyword that has no node ends before level 0; the marginal
-// run does not run at all when the central run selected no CG.
-__global__ void k_run_reset(RunStatus* st, int32_t empty, const int32_t* nsel, uint32_t* sb) {
-  for (int i = 0; i < 2 * kSupers * 3; ++i) sb[i] = 0;
-  RunStatus s = {};
-  const bool skip = nsel != nullptr && *nsel == 0;
-  s.end_level = (skip || empty) ? -1 : INT32_MAX;
-  s.end_reason = skip ? END_NONE : (empty ? END_EMPTY_KEYWORD : END_NONE);
-  *st = s;
-}
+// One run's matrix and reached masks, as words.
+struct InitRun {
+  uint32_t* H;
+  uint64_t words;        // words of H (0: no such run)
+  uint32_t pat[4];       // row pattern: INF for the run's keywords, 0 padding
+  uint32_t row_words;    // 1, 2 or 4
+  uint32_t* R;
+  uint64_t r_words;
+};
 
-template <int TP>
-__global__ __launch_bounds__(kBlock) void k_init_rows(uint8_t* H, RMaskT<TP>* R, int32_t n,
-                                                      int32_t n_pad, int32_t T) {
-  uint8_t b[TP];
+struct InitView {
+  InitRun run[2];
+  Status* gst;
+  int32_t empty[2];      // a keyword of the run has no node: it ends before level 0
+  int32_t central;       // 0: the marginal run alone (the rest is kept)
+  int32_t* has_rpg;
+  int32_t* sm;
+  int64_t* key;
+};
+
+// Everything a query starts from, for both runs, in one launch (they were
+// eight, about 2.5 us each).
+__global__ __launch_bounds__(kBlock) void k_query_init(InitView v) {
+  const uint64_t tid = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
 #pragma unroll
-  for (int i = 0; i < TP; ++i) b[i] = i < T ? kInf : 0;
-  typename RowVec<TP>::T pat;
-  __builtin_memcpy(&pat, b, TP);
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n_pad; v += stride) {
-    reinterpret_cast<typename RowVec<TP>::T*>(H)[v] = pat;
-    R[v] = 0;
+  for (int k = 0; k < 2; ++k) {
+    const InitRun& r = v.run[k];
+    const uint4 pat = r.row_words == 1   ? make_uint4(r.pat[0], r.pat[0], r.pat[0], r.pat[0])
+                      : r.row_words == 2 ? make_uint4(r.pat[0], r.pat[1], r.pat[0], r.pat[1])
+                                         : make_uint4(r.pat[0], r.pat[1], r.pat[2], r.pat[3]);
+    for (uint64_t i = tid; i < r.words / 4; i += stride) reinterpret_cast<uint4*>(r.H)[i] = pat;
+    for (uint64_t i = tid; i < r.r_words / 4; i += stride)
+      reinterpret_cast<uint4*>(r.R)[i] = make_uint4(0, 0, 0, 0);
+  }
+  if (blockIdx.x != 0) return;
+  for (int i = threadIdx.x; i < kMaxW; i += kBlock) {
+    v.has_rpg[i] = 0;
+    v.sm[i] = 0;
+    v.key[i] = 0;
+  }
+  if (threadIdx.x < 2 && (threadIdx.x == 1 || v.central)) {
+    RunStatus s = {};
+    const bool empty = v.empty[threadIdx.x];
+    s.end_level = empty ? -1 : INT32_MAX;
+    s.end_reason = empty ? END_EMPTY_KEYWORD : END_NONE;
+    v.gst->run[threadIdx.x] = s;
+  }
+  if (threadIdx.x == 0 && v.central) {
+    v.gst->nsel = 0;
+    v.gst->sel_ticket = 0;
+    v.gst->nres = 0;
+    v.gst->overflow = 0;
+    v.gst->out_nodes = 0;
+    v.gst->out_arcs = 0;
   }
 }
 
-template <int TP>
-__global__ __launch_bounds__(kBlock) void k_seed(uint8_t* H, const int32_t* kw_nodes, SeedList s) {
-  const uint32_t total = s.prefix[s.T];
-  for (uint32_t p = blockIdx.x * kBlock + threadIdx.x; p < total; p += gridDim.x * kBlock) {
+struct SeedView {
+  uint8_t* H[2];
+  int32_t TP[2];
+  SeedList s[2];
+};
+
+// Keyword nodes are at distance 0: the first frontier.
+__global__ __launch_bounds__(kBlock) void k_seed(SeedView v, const int32_t* kw_nodes) {
+  const uint64_t t0 = v.s[0].prefix[v.s[0].T], total = t0 + v.s[1].prefix[v.s[1].T];
+  for (uint64_t x = blockIdx.x * kBlock + threadIdx.x; x < total; x += gridDim.x * kBlock) {
+    const int k = x >= t0;
+    const SeedList& s = v.s[k];
+    const uint32_t p = (uint32_t)(k ? x - t0 : x);
     int i = 0;
     while (p >= s.prefix[i + 1]) ++i;
-    const int32_t v = kw_nodes[s.start[i] + (p - s.prefix[i])];
-    H[(int64_t)v * TP + i] = 0;   // keyword nodes are at distance 0: the first frontier
+    const int32_t n = kw_nodes[s.start[i] + (p - s.prefix[i])];
+    v.H[k][(int64_t)n * v.TP[k] + i] = 0;
   }
 }
 
@@ -146,271 +174,282 @@ __global__ __launch_bounds__(kBlock) void k_seed(uint8_t* H, const int32_t* kw_n
 // levels, and blocking (a complete row) never ends.  All of this is in the H
 // row and row_amax, which the scan reads in node order.
 
-// What one H row says at level l.
-struct RowState {
-  uint32_t mn, mo, rm;   // keywords with h == l / h < l / h finite
-  uint32_t mx, sum;      // largest finite h and sum of finite h
-  bool complete;         // every byte finite (padding bytes are 0)
-};
-
+// What one H row says at level l: the keywords with h == l in the low 16 bits,
+// those with h < l in the high ones.  The levels written so far are at most l,
+// so the two together are the keywords that have reached the node.
 template <int TP>
-__device__ inline RowState row_state(const uint8_t (&b)[TP], uint32_t tmask, int level) {
-  RowState st;
-  st.complete = true;
-  uint32_t mn = 0, mo = 0, mx = 0, sum = 0, rm = 0;
+__device__ inline uint32_t row_masks(const uint8_t (&b)[TP], uint32_t tmask, uint32_t level) {
+  uint32_t m = 0;
 #pragma unroll
-  for (int i = 0; i < TP; ++i) {
-    const uint32_t h = b[i];
-    const bool inf = h == kInf;
-    st.complete &= !inf;
-    rm |= (inf ? 0u : 1u) << i;
-    if (h == (uint32_t)level) mn |= 1u << i;
-    if (h < (uint32_t)level) mo |= 1u << i;
-    mx = (!inf && h > mx) ? h : mx;
-    sum += inf ? 0u : h;
-  }
-  st.mn = mn & tmask;
-  st.mo = mo & tmask;
-  st.rm = rm & tmask;
-  st.mx = mx;
-  st.sum = sum;
-  return st;
+  for (int i = 0; i < TP; ++i) m |= (b[i] == level ? 1u << i : 0u) | (b[i] < level ? 0x10000u << i : 0u);
+  return m & (tmask | (tmask << 16));
 }
 
-__device__ inline bool in_frontier(const RowState& st, uint32_t tmask, uint32_t amax, int level,
+// mn / mo: keywords with h == l / h < l.
+__device__ inline bool in_frontier(uint32_t mn, uint32_t mo, uint32_t tmask, uint32_t amax, int level,
                                    int block_rule) {
-  if (st.mn) return true;   // reached at level l
+  if (mn) return true;   // reached at level l
   // reached before l, not complete by l-1 where blocking applies, and an arc
   // of level > l-1 left
-  return st.mo != 0 && (int)amax > level - 1 && !(block_rule && st.mo == tmask);
+  return mo != 0 && (int)amax > level - 1 && !(block_rule && mo == tmask);
 }
 
-struct NodeInfo {
-  uint32_t mask_new, mask_old;  // keywords with h == level / h < level
-  uint32_t deg;                 // row degree if the node expands (Algorithm 1 scans it)
-  uint32_t rs, lo, hi, start;   // row start; arcs of level < l end at lo, <= l end at hi
-  uint32_t work;                // hi - start if the node expands
-  uint32_t hw;                  // entries written at the previous level
-  uint32_t reached;             // keywords with a finite hitting level
-  bool active, cand;
-  uint64_t key;
-};
-
-// A frontier node at level l: central-node test, block rule and the slice of
-// its row that the expansion examines.
-__device__ inline NodeInfo inspect_node(const RunView& r, const DevGraphView& g, int32_t v,
-                                        const RowState& st, uint32_t amax, int level) {
-  NodeInfo o;
-  o.mask_new = st.mn;
-  o.mask_old = st.mo;
-  o.reached = st.rm;
-  o.hw = level >= 1 ? __popc(o.mask_new) : 0;
-  const bool blocked = r.block_rule && st.complete;
-  // the row bounds and both level-table entries in one round of loads (the
-  // table entries are in bounds whenever their level is below nbnd)
-  const int xl = level - 1, xh = level;
-  const uint32_t blo = (xl >= 0 && xl < g.nbnd) ? g.bnd[(size_t)xl * g.n + v] : 0u;
-  const uint32_t bhi = (xh < g.nbnd) ? g.bnd[(size_t)xh * g.n + v] : 0u;
-  o.rs = g.row_ptr[v];
-  const uint32_t d = g.row_ptr[v + 1] - o.rs;
-  o.active = !blocked && (o.mask_new | o.mask_old) != 0 && d > 0;
-  o.deg = o.active ? d : 0;
-  o.cand = (r.kind == RUN_CENTRAL) && st.complete && st.mx == (uint32_t)level;
-  o.key = ((uint64_t)st.mx << 48) | ((uint64_t)st.sum << 32) | (uint32_t)g.orig_id[v];
-  o.lo = o.hi = o.start = o.work = 0;
-  if (o.active) {
-    // arcs of level <= x: none below 0, the whole row from its largest level
-    // on, else the level table (or a search of the row past the table)
-    o.lo = xl < 0 ? 0u : (xl >= (int)amax ? d : (xl < g.nbnd ? blo : count_le(g, v, xl)));
-    o.hi = xh >= (int)amax ? d : (xh < g.nbnd ? bhi : count_le(g, v, xh));
-    o.start = o.mask_new ? 0 : o.lo;
-    o.work = o.hi - o.start;
+// Last staged entry whose arc prefix (x) is <= w, by one wavefront.
+__device__ inline int wave_search_items(const uint4* items, int n, uint32_t w) {
+  int lo = 0, hi = n;
+  const int lane = lane_id();
+  while (hi - lo > 1) {
+    const int step = (hi - lo + kWave - 1) / kWave;
+    const int idx = lo + lane * step;
+    const bool ok = idx < hi && items[idx].x <= w;
+    const int L = 63 - __clzll((long long)__ballot(ok));
+    lo += L * step;
+    hi = min(hi, lo + step);
   }
-  return o;
+  return lo;
 }
 
-// Every workgroup takes cpw consecutive chunks of kScanNodes nodes (kScanPer
-// per thread), reads their H rows and levels in node order, inspects each
-// frontier node once and, in node order, stages its queue entry and its
-// central-node key in the workgroup's own slots of the staging arrays
-// (slot = first node of the workgroup + local index).  It also refreshes the
-// reached mask R of every frontier node: every node whose H row changed in
-// the previous expansion is a frontier now, so R stays equal to H's finite
-// set.
+// LDS of the RPG check, sized by the query's beam and keywords at launch.
+__host__ __device__ inline size_t rpg_lds_bytes(int w, int M) {
+  return (size_t)w * 8 + ((size_t)w * M + 3 * (size_t)w + w + 1) * 4;
+}
+
 template <int TP>
-__global__ __launch_bounds__(kBlock) void k_front_count(RunView r, DevGraphView g, int level) {
+__device__ void rpg_check(const RunView& r, int level, int64_t* lds);
+
+// Every workgroup takes cpw consecutive chunks of kScanNodes nodes; a wavefront
+// takes 256 consecutive nodes of a chunk, kScanPer per lane 64 apart, so that
+// all its reads are whole lines.  It reads their H rows and row levels, inspects
+// the frontier nodes (row bounds and level-table entries of all its nodes in one
+// round of loads) and stages their entries and central-node keys in the
+// workgroup's own slots of the staging arrays (from slot "first node of the
+// workgroup" on), 64 nodes at a time: a wave scan gives the lanes' places and one
+// LDS atomic reserves entries and arcs together, so entries' arc prefixes ascend
+// in slot order and wavefronts never wait for each other.  It also refreshes the
+// reached masks of its nodes: every node whose H row changed in the previous
+// expansion is a frontier now, so R stays equal to H's finite set.  A wavefront
+// without frontier nodes (most of them in the first and last levels) only reads.
+// Bytes bound it (rows, levels, per frontier node 16 read and 16 written), and
+// before that the wavefronts in flight: 64 registers keep all workgroups of a
+// level resident at once.  An average level of a query takes 9.8 us on 2M nodes
+// (20.5 with 4 neighbouring nodes per lane, block scans and 81 registers) and
+// 93 us on 20M (121).
+// InTable: the level table holds the level's counts (levels past it search the
+// rows, which takes registers).
+template <int TP, bool Central, bool InTable>
+__global__ __launch_bounds__(kBlock, TP == 4 ? 8 : (TP == 8 ? 6 : 5)) void k_front_scan(RunView r, DevGraphView g,
+                                                                        int level) {
+  extern __shared__ int64_t s_dyn[];
   if (level > r.st->end_level) return;
-  __shared__ uint64_t s_multi[(kBlock / kWave + 1) * 5];
-  __shared__ uint32_t s_m32[(kBlock / kWave + 1) * 3];
-  const int64_t wg0 = (int64_t)blockIdx.x * r.cpw * kScanNodes;
-  const int64_t wg1 = min(wg0 + (int64_t)r.cpw * kScanNodes, (int64_t)r.n_pad);
-  uint32_t cq = 0, cc = 0, cw = 0;   // block-uniform running counts of the workgroup
-  uint32_t nf = 0, hw = 0;
-  uint64_t dg = 0, dk = 0, gt = 0;
-  // the next chunk's rows and levels are loaded while this chunk is inspected
-  using AmW = typename UintOf<8 * kScanPer>::T;   // the row levels of a thread's nodes
-  uint8_t nrows[kScanPer][TP];
-  uint32_t nam2 = 0;
-  {
-    const int64_t b0 = wg0 + threadIdx.x * kScanPer;
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) load_row<TP>(r.H, b0 + k, nrows[k]);
-    nam2 = *reinterpret_cast<const AmW*>(g.row_amax + b0);
+  int wg = blockIdx.x;
+  if constexpr (!Central) {
+    if (wg == 0) {
+      rpg_check<TP>(r, level, s_dyn);
+      return;
+    }
+    --wg;
   }
+  __shared__ uint64_t s_sum[(kBlock / kWave + 1) * 5];
+  __shared__ unsigned long long s_res;   // entries << 32 | arcs reserved so far
+  __shared__ uint32_t s_nc;              // central nodes staged so far
+  if (threadIdx.x == 0) {
+    s_res = 0;
+    s_nc = 0;
+  }
+  __syncthreads();
+  const int64_t wg0 = (int64_t)wg * r.cpw * kScanNodes;
+  const int64_t wg1 = min(wg0 + (int64_t)r.cpw * kScanNodes, (int64_t)r.n_pad);
+  const int lane = lane_id();
+  uint32_t nf = 0, hw = 0, dg = 0, gt = 0;   // arcs of distinct rows fit 32 bits
+  uint64_t dk = 0;
+  const int xl = level - 1, xh = level;
 #pragma unroll 1
-  for (int64_t c0 = wg0; c0 < wg1; c0 += kScanNodes) {
-    const int64_t base = c0 + threadIdx.x * kScanPer;
-    uint8_t rows[kScanPer][TP];
-    __builtin_memcpy(rows, nrows, sizeof(rows));
-    const uint32_t am2 = nam2;
-    if (c0 + kScanNodes < wg1) {
-#pragma unroll
-      for (int k = 0; k < kScanPer; ++k) load_row<TP>(r.H, base + kScanNodes + k, nrows[k]);
-      nam2 = *reinterpret_cast<const AmW*>(g.row_amax + base + kScanNodes);
-    }
-    uint32_t fw = 0;   // frontier bit per node
-    // what the staging step needs of each node, kept across the block scan
-    uint4 item[kScanPer];        // examined arcs (0: no queue entry), slice start, split, masks
-    uint64_t key[kScanPer];
-    uint32_t bits[kScanPer];     // reached mask | central node << 17
-    uint32_t v[3] = {0, 0, 0};   // queue entries, central nodes, examined arcs
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-      item[k] = make_uint4(0, 0, 0, 0);
-      key[k] = 0;
-      bits[k] = 0;
-      const RowState st = row_state<TP>(rows[k], r.tmask, level);
-      const uint32_t amax = (am2 >> (8 * k)) & 0xFFu;
-      if (!in_frontier(st, r.tmask, amax, level, r.block_rule)) continue;
-      fw |= 1u << k;
-      const NodeInfo o = inspect_node(r, g, (int32_t)(base + k), st, amax, level);
-      ++nf;
-      hw += o.hw;
-      if (o.active) {
-        dg += o.deg;
-        dk += (uint64_t)o.deg * __popc(o.mask_new | o.mask_old);
-        gt += o.hi;
-      }
-      item[k] = make_uint4(o.work, o.rs + o.start, o.rs + o.lo, o.mask_new | (o.mask_old << 16));
-      key[k] = o.key;
-      bits[k] = o.reached | (o.cand ? 1u << 17 : 0u);
-      v[0] += o.work != 0;
-      v[1] += o.cand;
-      v[2] += o.work;
-    }
-    uint32_t t[3];
-    block_exclusive_scan_multi<3, kBlock, uint32_t>(v, t, s_m32);
-    if (fw) {
-      using RB = RBits<TP>;
-      typename RB::W* rp = RB::group(r.R, base);
-      const typename RB::W cur = *rp;
-      uint32_t mk[kScanPer];
-#pragma unroll
-      for (int k = 0; k < kScanPer; ++k) mk[k] = RB::unpack(cur, k);
-      uint32_t q = cq + (uint32_t)v[0], cd = cc + (uint32_t)v[1], wk = cw + (uint32_t)v[2];
+  for (int64_t c0 = wg0 + wave_id() * (kScanPer * kWave); c0 < wg1; c0 += kScanNodes) {
+    uint32_t am[kScanPer], mm[kScanPer];   // row level, masks (see row_masks)
+    uint32_t fw = 0;                       // frontier bit per node
+    {
+      uint8_t rows[kScanPer][TP];
 #pragma unroll
       for (int k = 0; k < kScanPer; ++k) {
-        if (!((fw >> k) & 1u)) continue;
-        mk[k] = bits[k] & 0xFFFFu;
-        if (item[k].x) {
-          const uint32_t work = item[k].x;
-          item[k].x = wk;
-          r.s_item[wg0 + q] = item[k];
-          ++q;
-          wk += work;
-        }
-        if (bits[k] & (1u << 17)) r.s_cand[wg0 + cd++] = key[k];
+        load_row<TP>(r.H, c0 + k * kWave + lane, rows[k]);
+        am[k] = g.row_amax[c0 + k * kWave + lane];
       }
-      *rp = RB::pack(mk);
+#pragma unroll
+      for (int k = 0; k < kScanPer; ++k) {
+        mm[k] = row_masks<TP>(rows[k], r.tmask, (uint32_t)level);
+        if (in_frontier(mm[k] & 0xFFFFu, mm[k] >> 16, r.tmask, am[k], level, r.block_rule)) fw |= 1u << k;
+      }
     }
-    cq += (uint32_t)t[0];
-    cc += (uint32_t)t[1];
-    cw += (uint32_t)t[2];
+    if (__ballot(fw != 0) == 0) continue;
+    uint32_t rs[kScanPer], re[kScanPer], blo[kScanPer], bhi[kScanPer];
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      rs[k] = re[k] = blo[k] = bhi[k] = 0;
+      if ((fw >> k) & 1u) {
+        const int64_t v = c0 + k * kWave + lane;
+        rs[k] = g.row_ptr[v];
+        re[k] = g.row_ptr[v + 1];
+        if constexpr (InTable) {
+          if (xl >= 0) blo[k] = g.bnd[(size_t)xl * g.n + v];
+          bhi[k] = g.bnd[(size_t)xh * g.n + v];
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      const int64_t v = c0 + k * kWave + lane;
+      const bool fr = (fw >> k) & 1u;
+      const uint32_t mn = mm[k] & 0xFFFFu, mo = mm[k] >> 16;
+      const bool complete = (mn | mo) == r.tmask;
+      if (__ballot(fr)) RBits<TP>::put(r.R, v, mn | mo);
+      uint32_t work = 0, start = 0, lo = 0;
+      if (fr) {
+        ++nf;
+        if (level >= 1) hw += __popc(mn);
+        const uint32_t d = re[k] - rs[k];
+        if (!(r.block_rule && complete) && d > 0) {
+          // the row slice the expansion examines: arcs of level <= x are none
+          // below 0, the whole row from its largest level on, else the level
+          // table's (or a search of the row past the table)
+          const int a = (int)am[k];
+          uint32_t hi;
+          if constexpr (InTable) {
+            lo = xl < 0 ? 0u : (xl >= a ? d : blo[k]);
+            hi = xh >= a ? d : bhi[k];
+          } else {
+            lo = count_le(g, (int32_t)v, xl);
+            hi = count_le(g, (int32_t)v, xh);
+          }
+          start = mn ? 0 : lo;
+          work = hi - start;
+          dg += d;
+          dk += (uint64_t)d * __popc(mn | mo);
+          gt += hi;
+        }
+      }
+      const uint64_t any = __ballot(work != 0);
+      if (any) {
+        const uint32_t inc = wave_inclusive_scan(work);
+        unsigned long long at = 0;
+        if (lane == 0)
+          at = atomicAdd(&s_res, ((unsigned long long)__popcll(any) << 32) | wave_last(inc));
+        at = __shfl(at, 0, kWave);
+        if (work)
+          r.s_item[wg0 + (uint32_t)(at >> 32) + __popcll(any & ((1ull << lane) - 1))] =
+              make_uint4((uint32_t)at + inc - work, rs[k] + start, rs[k] + lo, mm[k]);
+      }
+      // central node: complete, identified at the level of its row maximum
+      if constexpr (Central) {
+        const bool cand = fr && complete && mn != 0;
+        const uint64_t cb = __ballot(cand);
+        if (!cb) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_nc, (uint32_t)__popcll(cb));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (cand) {
+          uint8_t b[TP];   // read again: few nodes get here
+          load_row<TP>(r.H, v, b);
+          uint32_t sum = 0;
+#pragma unroll
+          for (int i = 0; i < TP; ++i) sum += i < r.T ? b[i] : 0u;
+          r.s_cand[wg0 + at + __popcll(cb & ((1ull << lane) - 1))] =
+              ((uint64_t)(uint32_t)level << 48) | ((uint64_t)sum << 32) | (uint32_t)g.orig_id[v];
+        }
+      }
+    }
   }
-  uint64_t v5[5] = {nf, hw, dg, dk, gt}, t5[5];
-  block_exclusive_scan_multi<5, kBlock>(v5, t5, s_multi);
+  const uint64_t v5[5] = {nf, hw, dg, dk, gt};
+  const uint64_t* t5 = s_sum;
+  const bool any = __syncthreads_or((int)nf);
+  if (any) block_totals<5, kBlock>(v5, s_sum);
   if (threadIdx.x == 0) {
-    ScanTot t;
-    t.nfront = (uint32_t)t5[0];
-    t.nq = cq;
-    t.ncand = cc;
-    t.work = cw;
-    t.hw = (uint32_t)t5[1];
-    t.pad = 0;
-    t.deg = t5[2];
-    t.degk = t5[3];
-    t.gate = t5[4];
-    r.tot[blockIdx.x] = t;
-    // superblock sums, so that every copying workgroup of the enqueue finds
-    // its offsets with at most kSupers + kSuper loads
-    uint32_t* sb = r.sb + ((level & 1) * kSupers + blockIdx.x / kSuper) * 3;
-    if (t.nq) atomicAdd(&sb[0], t.nq);
-    if (t.work) atomicAdd(&sb[1], t.work);
-    if (t.ncand) atomicAdd(&sb[2], t.ncand);
+    r.brief[wg] = make_uint2((uint32_t)s_res, (uint32_t)(s_res >> 32) | (any ? kHasFront : 0u));
+    r.ncand[wg] = s_nc;
+    if (any) {   // without frontier nodes nothing reads the rest
+      ScanTot t;
+      t.nfront = (uint32_t)t5[0];
+      t.hw = (uint32_t)t5[1];
+      t.deg = t5[2];
+      t.degk = t5[3];
+      t.gate = t5[4];
+      r.tot[wg] = t;
+    }
   }
 }
-
-constexpr int kCtl = 1024;
-constexpr uint32_t kTileAtEntry = 0x80000000u;   // tile_first: the tile starts with the entry
 
 // Marginal run identification (Section 4.2.3): for every selected CG without
 // an RPG, D_j = min over its central-keyword nodes of h_j; all finite -> RPG
 // with S^m = max_j D_j (Eq. 5) and key gamma_num*S^c + (gamma_den-gamma_num)*S^m
 // (Eq. 6 scaled by gamma_den).  Then the stop rules: every CG has an RPG, or
 // Theorem 4 with the k-th RPG in (key, S^c, CG rank) order.
+//
+// One workgroup beside the scan of level `level`: the hitting levels up to
+// `level` are all written.  Without frontier nodes nothing changed since the
+// last level's check, so its answer does not depend on the scan's either.
 template <int TP>
-__device__ int rpg_identify(const RunView& r, uint32_t* nrpg_io, int level) {
-  __shared__ uint32_t s_dm[kMaxW * kMaxKw];
-  __shared__ int32_t s_has[kMaxW], s_sm[kMaxW], s_sc[kMaxW];
-  __shared__ uint32_t s_vc[kMaxW + 1];
-  __shared__ int64_t s_key[kMaxW];
-  __shared__ int32_t s_new, s_nrpg, s_kth, s_minsc, s_stop;
-  const int nsel = *r.nsel, M = r.T;
-  const int64_t gn = r.gamma_num, gd = r.gamma_den;
-  for (int i = threadIdx.x; i < nsel * kMaxKw; i += kCtl) s_dm[i] = kInf;
-  for (int i = threadIdx.x; i < nsel; i += kCtl) {
+__device__ void rpg_check(const RunView& r, int level, int64_t* lds) {
+  const int M = r.T;
+  int64_t* s_key = lds;                                        // [w]
+  uint32_t* s_dm = reinterpret_cast<uint32_t*>(s_key + r.w);   // [w][M]
+  int32_t* s_has = reinterpret_cast<int32_t*>(s_dm + r.w * M); // [w]
+  int32_t* s_sm = s_has + r.w;
+  int32_t* s_sc = s_sm + r.w;
+  uint32_t* s_vc = reinterpret_cast<uint32_t*>(s_sc + r.w);    // [w + 1]
+  __shared__ int32_t s_nrpg, s_kth, s_minsc, s_stop, s_max;
+  // everything the check reads in one round of loads: entries past nsel are
+  // unset or stale and not used
+  for (int i = threadIdx.x; i < r.w; i += kBlock) {
     s_has[i] = r.has_rpg[i]; s_sm[i] = r.sm[i]; s_key[i] = r.key[i]; s_sc[i] = r.sel_sc[i];
   }
-  for (int i = threadIdx.x; i <= nsel; i += kCtl) s_vc[i] = r.vc_off[i];
-  if (threadIdx.x == 0) { s_new = 0; s_kth = -1; s_minsc = INT32_MAX; s_stop = 0; }
+  for (int i = threadIdx.x; i <= r.w; i += kBlock) s_vc[i] = r.vc_off[i];
+  const int nsel = *r.nsel;
+  const int64_t gn = r.gamma_num, gd = r.gamma_den;
+  for (int i = threadIdx.x; i < nsel * M; i += kBlock) s_dm[i] = kInf;
+  if (threadIdx.x == 0) { s_nrpg = 0; s_kth = -1; s_minsc = INT32_MAX; s_stop = 0; s_max = 0; }
   __syncthreads();
   // D_j of every CG without an RPG: minimum over its V_C rows
   const uint32_t total = s_vc[nsel];
-  for (uint32_t p = threadIdx.x; p < total; p += kCtl) {
+  for (uint32_t p = threadIdx.x; p < total; p += kBlock) {
+    const int32_t node = r.vc_nodes[p];
     const int rr = upper_index<uint32_t>(s_vc, 0, nsel + 1, p);
     if (s_has[rr]) continue;
     uint8_t b[TP];
-    load_row<TP>(r.H, r.vc_nodes[p], b);
+    load_row<TP>(r.H, node, b);
 #pragma unroll
     for (int j = 0; j < TP; ++j)
-      if (j < M) atomicMin(&s_dm[rr * kMaxKw + j], (uint32_t)b[j]);
+      if (j < M && b[j] != kInf) atomicMin(&s_dm[rr * M + j], (uint32_t)b[j]);
   }
   __syncthreads();
-  for (int rr = threadIdx.x; rr < nsel; rr += kCtl) {
-    if (s_has[rr]) continue;
-    bool all = true;
-    int smax = 0;
-    for (int j = 0; j < M; ++j) {
-      const int d = (int)s_dm[rr * kMaxKw + j];
-      r.dmin[rr * kMaxKw + j] = (uint8_t)d;
-      all &= d != kInf;
-      smax = d > smax ? d : smax;
+  for (int rr = threadIdx.x; rr < nsel; rr += kBlock) {
+    if (!s_has[rr]) {
+      bool all = true;
+      int smax = 0;
+      for (int j = 0; j < M; ++j) {
+        const int d = (int)s_dm[rr * M + j];
+        r.dmin[rr * kMaxKw + j] = (uint8_t)d;
+        all &= d != kInf;
+        smax = d > smax ? d : smax;
+      }
+      if (all) {
+        s_has[rr] = 1;
+        s_sm[rr] = smax;
+        s_key[rr] = r.score_mode ? (int64_t)s_sc[rr] * smax : gn * s_sc[rr] + (gd - gn) * smax;
+        r.has_rpg[rr] = 1;
+        r.sm[rr] = smax;
+        r.key[rr] = s_key[rr];
+      }
     }
-    if (all) {
-      s_has[rr] = 1;
-      s_sm[rr] = smax;
-      s_key[rr] = r.score_mode ? (int64_t)s_sc[rr] * smax : gn * s_sc[rr] + (gd - gn) * smax;
-      atomicAdd(&s_new, 1);
+    if (s_has[rr]) {
+      atomicAdd(&s_nrpg, 1);
+      atomicMax(&s_max, s_sm[rr]);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) { s_nrpg = (int)*nrpg_io + s_new; *nrpg_io = (uint32_t)s_nrpg; }
   __syncthreads();
   const int nrpg = s_nrpg;
   if (nrpg == nsel) {
-    s_stop = 1;
+    if (threadIdx.x == 0) s_stop = 1;
   } else if (nrpg >= r.k) {
-    for (int rr = threadIdx.x; rr < nsel; rr += kCtl) {
+    for (int rr = threadIdx.x; rr < nsel; rr += kBlock) {
       if (s_has[rr]) {
         int rank = 0;
         for (int o = 0; o < nsel; ++o) {
@@ -434,339 +473,534 @@ __device__ int rpg_identify(const RunView& r, uint32_t* nrpg_io, int level) {
       if (r.rerank ? s_key[kth] < bound : s_key[kth] <= bound) s_stop = 1;
     }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nsel; i += kCtl) {
-    r.has_rpg[i] = s_has[i]; r.sm[i] = s_sm[i]; r.key[i] = s_key[i];
+  if (threadIdx.x == 0) {
+    r.st->nrpg = (uint32_t)nrpg;
+    r.st->max_sm = s_max;
+    r.st->rpg_stop = s_stop;
   }
-  return s_stop;
 }
 
 // The final status of the level also goes to `mirror` (pinned host memory),
 // so the host learns it without a copy or an event: the status is written,
 // made visible to the host, and then stamped with `seq`, the launch's number,
-// which the host polls for.  Every thread loads its scan totals
-// (at most two workgroups' worth) before anything else, so the kernel waits
-// for memory about once before the scan.
-static_assert(kScanGroups <= 2 * kCtl, "the control step keeps two scan totals per thread");
+// which the host polls for.
+// Called by one wavefront: the lanes copy a word each, which takes no registers.
+constexpr int kStatusWords = sizeof(RunStatus) / 4;
+static_assert(kStatusWords <= kWave, "one word per lane");
 
-__device__ inline void publish(RunStatus* mirror, const RunStatus& st, uint64_t seq) {
-  *mirror = st;
-  __threadfence_system();
-  *reinterpret_cast<volatile uint64_t*>(&mirror->seq) = seq;
+__device__ inline void copy_status(RunStatus* to, const RunStatus* from) {
+  if (lane_id() < kStatusWords)
+    __builtin_memcpy(reinterpret_cast<char*>(to) + 4 * lane_id(),
+                     reinterpret_cast<const char*>(from) + 4 * lane_id(), 4);
 }
 
-template <int TP>
-__device__ void control_level(const RunView& r, int level, RunStatus* mirror, uint64_t seq) {
-  RunStatus* st = r.st;
-  const int nb = r.nblocks;
-  const int per = (nb + kCtl - 1) / kCtl;   // 1 or 2
-  const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
-  ScanTot t[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (b0 + i < b1) t[i] = r.tot[b0 + i];
-    else t[i] = ScanTot{};
-  }
-  // thread 0 keeps the run's status in LDS (not in private memory, which
-  // every launch of the kernel would then have to set up) and stores it once
+__device__ inline void publish(RunStatus* mirror, const RunStatus* st, uint64_t seq) {
+  copy_status(mirror, st);
+  __threadfence_system();
+  if (lane_id() == 0) *reinterpret_cast<volatile uint64_t*>(&mirror->seq) = seq;
+}
+
+// What every workgroup of the expansion derives from the scan's totals: each
+// thread looks at `per` consecutive scan workgroups.
+struct LevelSums {
+  uint32_t tiles;         // of all scan workgroups
+  uint32_t ncand, exc;    // central nodes; those of the scan workgroups before this thread's
+  bool front;             // some frontier node
+};
+
+// Threads of an expansion workgroup.  Every workgroup reads all totals of the
+// scan (24 KB on large graphs), so on graphs with many scan workgroups there is
+// one of 1024 threads per CU, with the hot nodes' masks in LDS; with few totals
+// small workgroups start sooner (2 us less per level on 10k nodes).
+constexpr int kExpSmall = 256, kExpLarge = 1024;
+constexpr int kExpSmallNb = 256;   // up to this many scan workgroups
+template <int NT> constexpr int kPerCtl = ((NT == kExpSmall ? kExpSmallNb : kScanGroups) + NT - 1) / NT;
+// Reached masks kept in LDS (large workgroups); levels with fewer tiles than
+// kHotTiles gather everything from memory.
+constexpr uint32_t kHotBytes = 64u << 10;
+constexpr uint32_t kHotTiles = 4096;
+
+// Control step of a level (one workgroup): records the level
+// and the run's end in the status and tells the host; keeps the level's
+// central nodes while they do not end the run.
+template <int NT>
+__device__ void control_level(const RunView& r, int level, const LevelSums& ls, int end, int b0,
+                              int b1, RunStatus* mirror, uint64_t seq) {
+  __shared__ uint64_t s_multi[(NT / kWave + 1) * 7];
   __shared__ RunStatus cur;
-  if (threadIdx.x == 0) cur = *st;
-  if (level > st->end_level) {
-    if (threadIdx.x == 0) publish(mirror, cur, seq);
-    return;
+  if (wave_id() == 0) copy_status(&cur, r.st);
+  uint64_t v[7] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+  for (int b = b0; b < b1; ++b) {
+    const uint2 brief = r.brief[b];
+    if (!(brief.y & kHasFront)) continue;
+    const ScanTot x = r.tot[b];
+    v[0] += brief.y & ~kHasFront; v[1] += brief.x; v[2] += x.nfront; v[3] += x.hw;
+    v[4] += x.deg; v[5] += x.degk; v[6] += x.gate;
   }
-  __shared__ int32_t s_end;
-  __shared__ uint32_t s_nrpg;
-  // one pass for all eight values: q, work, cand prefixes; the rest totals
-  __shared__ uint64_t s_multi[(kCtl / kWave + 1) * 8];
-  uint64_t vals[8] = {(uint64_t)t[0].nq + t[1].nq, (uint64_t)t[0].work + t[1].work,
-                      (uint64_t)t[0].ncand + t[1].ncand, (uint64_t)t[0].nfront + t[1].nfront,
-                      (uint64_t)t[0].hw + t[1].hw, t[0].deg + t[1].deg, t[0].degk + t[1].degk,
-                      t[0].gate + t[1].gate};
-  uint64_t tots[8];
-  block_exclusive_scan_multi<8, kCtl>(vals, tots, s_multi);
-  const uint32_t tnq = (uint32_t)tots[0], twk = (uint32_t)tots[1], tnc = (uint32_t)tots[2];
-  const uint32_t tnf = (uint32_t)tots[3], thw = (uint32_t)tots[4];
-  const uint64_t tdg = tots[5], tdk = tots[6], tgt = tots[7];
+  block_totals<7, NT>(v, s_multi);
+  const uint64_t* t = s_multi;
+  const uint32_t base = cur.cand_base[level & 1];
+  // fewer than w so far: the level's central nodes join the list (otherwise
+  // the selection reads them where they are staged)
+  if (r.kind == RUN_CENTRAL && ls.ncand && base + ls.ncand < (uint32_t)r.w) {
+    uint32_t at = base + ls.exc;
+#pragma unroll 1
+    for (int b = b0; b < b1; ++b) {
+      const uint32_t k = r.ncand[b];
+      for (uint32_t i = 0; i < k; ++i) r.cand[at++] = r.s_cand[(int64_t)b * r.cpw * kScanNodes + i];
+    }
+  }
   if (threadIdx.x == 0) {
     cur.levels = level + 1;
-    cur.nfront = tnf;
-    cur.nactive = tnq;
-    cur.W = twk;
-    cur.ncand_level = tnc;
-    cur.frontier_sum += tnf;
-    cur.h_writes += thw;
-    r.q_off[tnq] = twk;
-    s_end = END_NONE;
-    if (tnf == 0) {
-      s_end = END_EXHAUSTED;
-    } else if (r.kind == RUN_CENTRAL) {
-      cur.ncand_total += tnc;
-      if (cur.ncand_total >= (uint32_t)r.w) s_end = END_STOP;
-    }
-    // where the next level's central nodes start (the other slot is read by
-    // this launch's copying workgroups)
-    cur.cand_base[(level + 1) & 1] = cur.cand_base[level & 1] + tnc;
-    s_nrpg = cur.nrpg;
-  }
-  // the next level's superblock sums start from zero (this level's are read
-  // by the copying workgroups of this launch)
-  if (threadIdx.x < kSupers * 3) r.sb[((level + 1) & 1) * kSupers * 3 + threadIdx.x] = 0;
-  __syncthreads();
-  if (s_end == END_NONE && r.kind == RUN_MARGINAL) {
-    if (rpg_identify<TP>(r, &s_nrpg, level) && threadIdx.x == 0) s_end = END_STOP;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    cur.nrpg = s_nrpg;
-    int end = s_end;
-    if (end == END_NONE && level >= r.max_level) end = END_LEVEL_BOUND;
+    cur.nactive = (uint32_t)t[0];
+    cur.W = (uint32_t)t[1];
+    cur.nfront = (uint32_t)t[2];
+    cur.ncand_level = ls.ncand;
+    cur.frontier_sum += t[2];
+    cur.h_writes += t[3];
+    if (r.kind == RUN_CENTRAL) cur.ncand_total = base + ls.ncand;
+    // where the next level's central nodes start (this launch's other
+    // workgroups read the other slot)
+    cur.cand_base[(level + 1) & 1] = base + ls.ncand;
     if (end != END_NONE) {
       cur.end_level = level;
       cur.end_reason = end;
       cur.expand_on = 0;
     } else {
       cur.expand_on = 1;
-      cur.e_arc += tdg;
-      cur.e_alg += tdk;
-      cur.gate_pass += tgt;
+      cur.e_arc += t[4];
+      cur.e_alg += t[5];
+      cur.gate_pass += t[6];
     }
-    *st = cur;
-    publish(mirror, cur, seq);
+  }
+  if (wave_id() == 0) {
+    __builtin_amdgcn_wave_barrier();
+    copy_status(r.st, &cur);
+    publish(mirror, &cur, seq);
   }
 }
 
-// Frontier Enqueue in the same launch: workgroup 0 runs the level's control
-// step; workgroup 1 + b copies scan workgroup b's staged queue entries to
-// its place in the expansion queue (its offsets are the sums of the totals
-// of the scan workgroups before it, read by all its threads at once), its
-// central nodes to the level's place in the candidate list, and, for every
-// expansion tile whose first arc falls in one of its entries, that entry to
-// the tile map.  The copies do not wait for the control step: if the level
-// does not expand, nothing reads the queue.
-template <int TP>
-__global__ __launch_bounds__(kCtl) void k_front_enqueue(RunView r, int level, RunStatus* mirror,
-                                                        uint64_t seq) {
-  if (blockIdx.x == 0) {
-    control_level<TP>(r, level, mirror, seq);
-    return;
-  }
-  const RunStatus* st = r.st;
-  const int b = (int)blockIdx.x - 1;
-  if (level > st->end_level) return;   // (set to this level at most, by workgroup 0)
-  const ScanTot t = r.tot[b];
-  if (t.nq == 0 && t.ncand == 0) return;
-  __shared__ uint32_t s_m32[(kCtl / kWave + 1) * 3];
-  // offsets: the superblocks before b's, then the scan workgroups of b's
-  // superblock before b (one load per thread)
-  uint32_t v[3] = {0, 0, 0}, tot[3];
-  const int sup = b / kSuper, first = sup * kSuper;
-  const uint32_t* sb = r.sb + (level & 1) * kSupers * 3;
-  if ((int)threadIdx.x < sup) {
-    v[0] = sb[threadIdx.x * 3]; v[1] = sb[threadIdx.x * 3 + 1]; v[2] = sb[threadIdx.x * 3 + 2];
-  } else if ((int)threadIdx.x >= kSupers && (int)threadIdx.x - kSupers < b - first) {
-    const ScanTot x = r.tot[first + threadIdx.x - kSupers];
-    v[0] = x.nq; v[1] = x.work; v[2] = x.ncand;
-  }
-  block_exclusive_scan_multi<3, kCtl, uint32_t>(v, tot, s_m32);
-  const uint32_t oq = tot[0], ow = tot[1];
-  const uint32_t oc = st->cand_base[level & 1] + tot[2];
-  const int64_t wg0 = (int64_t)b * r.cpw * kScanNodes;
-  for (uint32_t j = threadIdx.x; j < t.nq; j += kCtl) {
-    const uint4 e = r.s_item[wg0 + j];
-    const uint32_t start = ow + e.x;
-    const uint32_t end = ow + (j + 1 < t.nq ? r.s_item[wg0 + j + 1].x : t.work);
-    r.q_off[oq + j] = start;
-    r.q_rs[oq + j] = e.y;
-    r.q_lo[oq + j] = e.z;
-    r.q_mask[oq + j] = e.w;
-    // expansion tiles whose first arc falls in this entry start at it
-    for (uint32_t tl = (start + kExpandTile - 1) / kExpandTile; tl * kExpandTile < end; ++tl)
-      r.tile_first[tl] = (oq + j) | (tl * kExpandTile == start ? kTileAtEntry : 0u);
-  }
-  for (uint32_t j = threadIdx.x; j < t.ncand; j += kCtl) r.cand[oc + j] = r.s_cand[wg0 + j];
-}
-
-
-// Algorithm 1 at level `level` over the queued row slices (all of them have
+// Algorithm 1 at level `level` over the staged row slices (all of them have
 // level <= l).  For arc f -> n every keyword i that f expands for and that has
 // not reached n gets h_ni = level + 1, which makes n a frontier of the next
-// level.  One gather of the neighbour's reached mask serves
-// every keyword at once.  Tile of 1024 consecutive arcs of the concatenated
-// slices: the tile map gives its first and last queue entry, the entries go
-// to LDS, each entry marks the tile item where it starts and a block max-scan
-// turns the marks into the owner entry of every item; item i of the tile is
-// handled by thread i mod 256, so consecutive lanes read consecutive arcs.
-template <int TP>
-__global__ __launch_bounds__(kBlock) void k_expand(RunView r, DevGraphView g, int level) {
-  RunStatus* st = r.st;
-  if (level > st->end_level || !st->expand_on) return;
-  constexpr int IPT = kExpandTile / kBlock;
-  const uint32_t W = st->W;
-  const int nq = (int)st->nactive;
-  __shared__ uint32_t s_base[kExpandTile];
-  __shared__ uint32_t s_lo[kExpandTile];
-  __shared__ uint32_t s_mask[kExpandTile];
-  __shared__ uint16_t s_own[kExpandTile];
-  __shared__ uint32_t s_scan[kBlock / kWave + 1];
-  const uint32_t ntiles = (W + kExpandTile - 1) / kExpandTile;
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint32_t w0 = tile * kExpandTile;
-    const uint32_t w1 = min(W, w0 + (uint32_t)kExpandTile);
-    // first entry: the one holding arc w0; last: the one holding arc w1 - 1,
-    // which is the next tile's first entry unless that entry starts there
-    const int e0 = (int)(r.tile_first[tile] & ~kTileAtEntry);
-    int e1 = nq - 1;
-    if (tile + 1 < ntiles) {
-      const uint32_t f1 = r.tile_first[tile + 1];
-      e1 = (int)(f1 & ~kTileAtEntry) - ((f1 & kTileAtEntry) ? 1 : 0);
-    }
-    for (int i = threadIdx.x; i < kExpandTile; i += kBlock) s_own[i] = 0;
-    __syncthreads();
-    const int cnt = e1 - e0 + 1;
-    for (int j = threadIdx.x; j < cnt; j += kBlock) {
-      const uint32_t off = r.q_off[e0 + j];
-      s_base[j] = r.q_rs[e0 + j] - off + w0;   // arc of tile item i is s_base[j] + i
-      s_lo[j] = r.q_lo[e0 + j];
-      s_mask[j] = r.q_mask[e0 + j];
-      s_own[off > w0 ? off - w0 : 0] = (uint16_t)j;
-    }
-    __syncthreads();
-    uint32_t loc[IPT];
-    uint32_t m = 0;
+// level.  One gather of the neighbour's reached mask serves every keyword at
+// once.  A tile is kWaveTile consecutive arcs of one scan workgroup's
+// concatenated slices and one wavefront's work, from its entries to its writes:
+// no barrier ties wavefronts together, so while one waits for its gathers the
+// others are at any other step.  A wavefront takes a run of consecutive tiles,
+// searches the first one's first entry in the entries' arc prefixes and walks on
+// from there.  A tile's entries go to LDS, each marks the tile item where it
+// starts and a max-scan turns the marks into the owner entry of every item; the
+// lanes then read consecutive arcs, all of their targets before their masks
+// before their writes, so that a wavefront keeps four independent gathers in
+// flight.  Workgroup 0 is the level's control step; the others take tiles.
+// The lines fetched for the arcs bound it: a slice of a few arcs costs a line
+// (8.4M arcs in 63 us on 2M nodes with 2.5M L2 misses, 4.8 TB/s), then the
+// scattered stores.  Hot masks in LDS take the largest levels from 72 to 67 us
+// there and 2610 to 2450 us for a query's levels on 20M nodes; more wavefronts
+// per CU change nothing.  Scan, enqueue and expansion of a query's 15 levels on
+// 2M nodes took 685 us, scan and expansion take 407 us.
+template <int TP, int NT>
+__global__ __launch_bounds__(NT) void k_expand(RunView r, DevGraphView g, int level,
+                                                   RunStatus* mirror, uint64_t seq) {
+  constexpr int kWaves = NT / kWave, IPT = kWaveTile / kWave;
+  __shared__ uint4 s_first[kWaves];         // scan workgroup, tile, examined arcs, entries
+  __shared__ uint32_t s_pre[NT];        // tiles before each thread's scan workgroups
+  using RB = RBits<TP>;
+  using Mask = typename std::conditional<TP == 16, uint32_t, uint16_t>::type;
+  constexpr int TPb = TP == 16 ? 16 : 8;   // Mask: keywords reached at l | before << TPb
+  __shared__ uint32_t s_base[kWaves][kWaveTile];   // arc of tile item i is s_base[] + i
+  __shared__ uint16_t s_old[kWaves][kWaveTile];    // from this item on the old keywords join
+  __shared__ Mask s_mask[kWaves][kWaveTile];
+  __shared__ __align__(4) uint8_t s_own[kWaves][kWaveTile];    // owner entry of each item
+  __shared__ uint32_t s_hot[NT == kExpLarge ? kHotBytes / 4 : 4];   // reached masks of the first nodes
+  __shared__ uint32_t s_scan[(kWaves + 1) * 2];
+  const int nb = r.nblocks;
+  const int per = (nb + NT - 1) / NT;
+  const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
+  // everything the decision needs in one round of loads
+  uint2 brief[kPerCtl<NT>];
+  uint32_t nc = 0;
 #pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      const uint32_t o = s_own[threadIdx.x * IPT + k];
-      m = o > m ? o : m;
-      loc[k] = m;
-    }
-    const uint32_t pre = block_exclusive_max(m, s_scan);
+  for (int i = 0; i < kPerCtl<NT>; ++i) brief[i] = b0 + i < b1 ? r.brief[b0 + i] : make_uint2(0, 0);
+  if (r.kind == RUN_CENTRAL) {
 #pragma unroll
-    for (int k = 0; k < IPT; ++k) s_own[threadIdx.x * IPT + k] = (uint16_t)(pre > loc[k] ? pre : loc[k]);
-    __syncthreads();
-    // all of the thread's arcs at once: their targets, then the targets'
-    // reached masks, then the writes, so that a wavefront keeps IPT
-    // independent gathers in flight instead of one dependent chain per arc
-    int32_t nbv[IPT];
-    uint32_t wantv[IPT], rv[IPT];
+    for (int i = 0; i < kPerCtl<NT>; ++i) nc += b0 + i < b1 ? r.ncand[b0 + i] : 0u;
+  }
+  const RunStatus* st = r.st;
+  const uint32_t cand_base = st->cand_base[level & 1];
+  const int rpg_stop = r.kind == RUN_MARGINAL ? st->rpg_stop : 0;
+  if (level > st->end_level) {   // (set to this level at most, by workgroup 0)
+    if (blockIdx.x == 0 && wave_id() == 0) publish(mirror, st, seq);   // ended before level 0
+    return;
+  }
+  uint32_t mine = 0, front = 0;
 #pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      const uint32_t i = k * kBlock + threadIdx.x;
-      wantv[k] = 0;
-      nbv[k] = 0;
-      if (w0 + i < w1) {
-        const int j = s_own[i];
-        const uint32_t e = s_base[j] + i;
-        const uint32_t mk = s_mask[j];
-        wantv[k] = (e < s_lo[j]) ? (mk & 0xFFFFu) : ((mk & 0xFFFFu) | (mk >> 16));
-        nbv[k] = g.col_s[e];
+  for (int i = 0; i < kPerCtl<NT>; ++i) {
+    mine += (brief[i].x + kWaveTile - 1) / kWaveTile;
+    front |= brief[i].y & kHasFront;
+  }
+  uint32_t sv[2] = {mine, nc}, sum[2];
+  const bool any = __syncthreads_or((int)(front != 0));
+  block_exclusive_scan_multi<2, NT, uint32_t>(sv, sum, s_scan);
+  const LevelSums ls = {sum[0], sum[1], sv[1], any};
+  int end = END_NONE;
+  if (!ls.front) end = END_EXHAUSTED;
+  else if (r.kind == RUN_CENTRAL ? cand_base + ls.ncand >= (uint32_t)r.w : rpg_stop != 0) end = END_STOP;
+  else if (level >= r.max_level) end = END_LEVEL_BOUND;
+  if (blockIdx.x == 0) {
+    control_level<NT>(r, level, ls, end, b0, b1, mirror, seq);
+    return;
+  }
+  if (end != END_NONE) return;
+  // wavefronts take runs of at most kRun tiles in turn: long enough to spread
+  // the search of a run's first entry, short enough that a stretch of small
+  // rows (many entries per tile) is not one wavefront's
+  constexpr uint32_t kRun = 4;
+  const uint32_t waves = (gridDim.x - 1) * kWaves;
+  const uint32_t run = min(kRun, (ls.tiles + waves - 1) / waves);
+  if ((blockIdx.x - 1) * kWaves * run >= ls.tiles) return;   // none for the workgroup
+  s_pre[threadIdx.x] = sv[0];
+  uint32_t hot = 0;   // nodes whose masks are in LDS
+  if (NT == kExpLarge && ls.tiles >= kHotTiles) {
+    hot = min((uint32_t)r.n_pad, (uint32_t)(kHotBytes * 8 / RB::kBits));
+    for (uint32_t x = threadIdx.x; x < hot * RB::kBits / 128; x += NT)
+      reinterpret_cast<uint4*>(s_hot)[x] = reinterpret_cast<const uint4*>(r.R)[x];
+  }
+  // the wavefronts' first tiles: the thread whose scan workgroups hold one
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    uint32_t k = ((blockIdx.x - 1) * kWaves + w) * run - sv[0];
+    if (k >= mine) continue;
+#pragma unroll
+    for (int i = 0; i < kPerCtl<NT>; ++i) {
+      const uint32_t nt = (brief[i].x + kWaveTile - 1) / kWaveTile;
+      if (k < nt) {
+        s_first[w] = make_uint4((uint32_t)(b0 + i), k, brief[i].x, brief[i].y & ~kHasFront);
+        break;
       }
+      k -= nt;
     }
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) rv[k] = wantv[k] ? RBits<TP>::get(r.R, nbv[k]) : 0xFFFFFFFFu;
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      // keywords that have not reached the target (as of the start of this level)
-      const uint32_t mm = ~rv[k] & wantv[k];
-      if (mm) {
-#pragma unroll
-        for (int t = 0; t < TP; ++t)
-          if ((mm >> t) & 1u) r.H[(int64_t)nbv[k] * TP + t] = (uint8_t)(level + 1);
+  }
+  __syncthreads();
+  const int wv = wave_id(), lane = lane_id();
+  uint32_t* base = s_base[wv];
+  uint16_t* oldv = s_old[wv];
+  Mask* maskv = s_mask[wv];
+  uint8_t* own = s_own[wv];
+  bool first = true;
+  for (uint32_t t0 = ((blockIdx.x - 1) * kWaves + wv) * run; t0 < ls.tiles; t0 += waves * run) {
+    const uint32_t tile_end = min(ls.tiles, t0 + run);
+    bool fresh = true;   // the scan workgroup and entry of the tile's first arc are not known yet
+    uint32_t k = 0, work = 0;
+    int e = 0, nq = 0;
+    const uint4* items = nullptr;
+    for (uint32_t tile = t0; tile < tile_end; ++tile) {
+      if (fresh) {
+        uint32_t sb = s_first[wv].x;
+        if (first) {
+          k = s_first[wv].y;
+          work = s_first[wv].z;
+          nq = (int)s_first[wv].w;
+          first = false;
+        } else {
+          // the thread whose scan workgroups hold the tile (those without tiles
+          // repeat a prefix: the last of them), then the workgroup among them
+          const int th = wave_search(s_pre, NT, tile);
+          const int bl = th * per + lane;
+          uint2 x = make_uint2(0, 0);
+          if (lane < per && bl < nb) x = r.brief[bl];
+          const uint32_t nt = (x.x + kWaveTile - 1) / kWaveTile;
+          const uint32_t inc = wave_inclusive_scan(nt);
+          const uint32_t rem = tile - s_pre[th];
+          const int l = __ffsll((unsigned long long)__ballot(inc > rem)) - 1;
+          k = rem - (uint32_t)__builtin_amdgcn_readlane((int)(inc - nt), l);
+          work = (uint32_t)__builtin_amdgcn_readlane((int)x.x, l);
+          nq = __builtin_amdgcn_readlane((int)(x.y & ~kHasFront), l);
+          sb = (uint32_t)(th * per + l);
+        }
+        items = r.s_item + (int64_t)sb * r.cpw * kScanNodes;
+        e = k ? wave_search_items(items, nq, k * kWaveTile) : 0;
+        fresh = false;
       }
+      const uint32_t w0 = k * kWaveTile, w1 = min(work, w0 + (uint32_t)kWaveTile);
+      const uint32_t none = 0;
+      __builtin_memcpy(&own[4 * lane], &none, 4);
+      // the tile's entries, at most one per arc
+      for (int slot = lane;; slot += kWave) {
+        uint4 it = make_uint4(0, 0, 0, 0);
+        if (e + lane < nq) it = items[e + lane];
+        const bool take = e + lane < nq && it.x < w1;
+        if (take) {
+          const uint32_t ab = it.y - it.x + w0;
+          base[slot] = ab;
+          // item of the first arc of level l (the entry's arcs ascend by level)
+          oldv[slot] = (uint16_t)(it.z > ab ? min(it.z - ab, (uint32_t)kWaveTile) : 0u);
+          maskv[slot] = (Mask)((it.w & 0xFFFFu) | ((it.w >> 16) << TPb));
+          own[it.x > w0 ? it.x - w0 : 0] = (uint8_t)slot;
+        }
+        const int n = __popcll(__ballot(take));
+        e += n;
+        if (n < kWave) {
+          // lane n holds the entry after the tile's: the next tile starts with
+          // it, or with this tile's last one if that goes on
+          const uint32_t nx = (uint32_t)__builtin_amdgcn_readlane((int)it.x, n);
+          if (e >= nq || nx != w1) --e;
+          break;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      uint32_t mk4;   // marks of items 4 * lane .. 4 * lane + 3
+      __builtin_memcpy(&mk4, &own[4 * lane], 4);
+      uint32_t o0 = mk4 & 0xFFu, o1 = (mk4 >> 8) & 0xFFu, o2 = (mk4 >> 16) & 0xFFu, o3 = mk4 >> 24;
+      o1 = max(o0, o1);
+      o2 = max(o1, o2);
+      o3 = max(o2, o3);
+      const uint32_t inc = wave_scan_op(o3, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+      const uint32_t pre = dpp_move<0x138, 0xF>(inc);   // of the lanes before (wave_shr:1)
+      o0 = max(o0, pre); o1 = max(o1, pre); o2 = max(o2, pre); o3 = max(o3, pre);
+      mk4 = o0 | (o1 << 8) | (o2 << 16) | (o3 << 24);
+      __builtin_memcpy(&own[4 * lane], &mk4, 4);
+      __builtin_amdgcn_wave_barrier();
+      int32_t nbv[IPT];
+      uint32_t wantv[IPT], rv[IPT];
+  #pragma unroll
+      for (int q = 0; q < IPT; ++q) {
+        const uint32_t i = q * kWave + lane;
+        wantv[q] = 0;
+        nbv[q] = 0;
+        if (w0 + i < w1) {
+          const int j = own[i];
+          const uint32_t mk = maskv[j];
+          wantv[q] = mk & ((1u << TPb) - 1u);
+          if (i >= oldv[j]) wantv[q] |= mk >> TPb;
+          nbv[q] = g.col_s[base[j] + i];
+        }
+      }
+      // the targets' masks: from LDS for the nodes with the largest rows, which
+      // most arcs point to
+#pragma unroll
+      for (int q = 0; q < IPT; ++q) {
+        rv[q] = 0xFFFFFFFFu;
+        if (wantv[q] && (uint32_t)nbv[q] >= hot) rv[q] = RB::get(r.R, nbv[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < IPT; ++q) {
+        if (wantv[q] && (uint32_t)nbv[q] < hot) rv[q] = RB::get(s_hot, nbv[q]);
+        // keywords that have not reached the target (as of the start of this level)
+        const uint32_t mm = ~rv[q] & wantv[q];
+        if (mm) {
+          // a hot target counts as reached for this workgroup's later arcs
+          if ((uint32_t)nbv[q] < hot)
+            atomicOr(&s_hot[(uint32_t)nbv[q] / (32 / RB::kBits)],
+                     mm << ((uint32_t)nbv[q] % (32 / RB::kBits) * RB::kBits));
+#pragma unroll
+          for (int t = 0; t < TP; ++t)
+            if ((mm >> t) & 1u) r.H[(int64_t)nbv[q] * TP + t] = (uint8_t)(level + 1);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      ++k;
+      fresh = w1 == work;   // on to the next scan workgroup that has tiles
     }
-    __syncthreads();
   }
 }
 
 // -------------------------------------------------------------- top-w ---
 // Top-w central graphs by (S^c, sum of central levels, node id).  All CGs of
 // earlier levels are kept (they are fewer than w); the remaining slots go to
-// the last level's CGs with the smallest sums, ties to smaller node ids.  The
-// keys hold original node ids; the selected nodes are stored by internal id.
-__global__ __launch_bounds__(kCtl) void k_select(SelectView v) {
+// the last level's CGs with the smallest sums, ties to smaller node ids, which
+// is the order of the keys' low 48 bits.  The keys hold original node ids; the
+// selected nodes are stored by internal id.
+//
+// The last level's keys (up to a few percent of all nodes) follow the earlier
+// ones in v.cand or lie where the scan workgroups staged them.  The launch's
+// workgroups split them, each keeps the smallest of its part (at most w), and
+// the last one to finish selects among all kept ones.  One workgroup of 1024
+// threads alone took 223 us on 20M nodes (86 us now) and 450 us on 50M.
+
+// Keys of the last level; f(key) is called by all lanes of a wavefront
+// together, with kNoKey in the lanes that have none.
+constexpr uint64_t kNoKey = ~0ull;
+constexpr uint64_t kLow48 = (1ull << 48) - 1;
+constexpr int kSelPer = 32;      // at least this many scan workgroups per part
+static_assert(kScanGroups / kSelPer <= kSelParts, "parts of the selection");
+
+// Staged keys are numbered over all scan workgroups (pre: those before each):
+// with degree-ordered nodes nearly all of them can lie in the first few.
+struct SelPart {
+  uint32_t pre[kScanGroups];
+  int b0, b1;                    // scan workgroups that hold the part's keys: [b0, b1)
+};
+
+template <typename F>
+__device__ inline void each_key(const SelectView& v, bool staged, const SelPart& p, uint32_t lo,
+                                uint32_t hi, F f) {
+  const int b0 = staged ? p.b0 : 0, b1 = staged ? p.b1 : 0;
+  for (uint32_t i0 = lo; i0 < hi; i0 += kBlock) {
+    const uint32_t i = i0 + threadIdx.x;
+    uint64_t key = kNoKey;
+    if (i < hi) {
+      if (staged) {
+        const int j = upper_index<uint32_t>(p.pre, b0, b1, i);
+        key = v.s_cand[(int64_t)j * v.cpw * kScanNodes + (i - p.pre[j])];
+      } else {
+        key = v.cand[i];
+      }
+    }
+    f(key);
+  }
+}
+
+struct SelLds {
+  uint32_t hist[4096];
+  uint32_t scan[kBlock / kWave + 1];
+  uint32_t dig, below, in;   // chosen bin, keys in the bins before it and in it
+};
+
+// The bin of hist[0..bins) that holds the rem-th smallest key (rem >= 1).
+template <int PER>
+__device__ inline void pick_bin(SelLds& s, uint32_t rem) {
+  uint32_t h[PER], sum = 0, tot;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    h[i] = s.hist[threadIdx.x * PER + i];
+    sum += h[i];
+  }
+  uint32_t cum = block_exclusive_scan<uint32_t, kBlock>(sum, s.scan, &tot);
+  if (cum < rem && cum + sum >= rem) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (cum < rem && cum + h[i] >= rem) {
+        s.dig = threadIdx.x * PER + i;
+        s.below = cum;
+        s.in = h[i];
+      }
+      cum += h[i];
+    }
+  }
+  __syncthreads();
+}
+
+// The largest low-48-bit key among the `need` smallest of the keys that
+// each(f) yields (more than `need` of them): the sum first, then the id byte by
+// byte, stopping where a whole bin is taken.
+template <typename Each>
+__device__ uint64_t select_bound(SelLds& s, uint32_t need, Each each) {
+  for (int i = threadIdx.x; i < 4096; i += kBlock) s.hist[i] = 0;
+  __syncthreads();
+  // the sums crowd into a few bins: one LDS atomic per distinct bin of a
+  // wavefront instead of one per key
+  each([&](uint64_t key) {
+    const int bin = key != kNoKey ? (int)((key >> 32) & 0xFFF) : -1;
+    uint64_t pending = __ballot(bin >= 0);
+    while (pending) {
+      const int leader = __ffsll((unsigned long long)pending) - 1;
+      const int lb = __shfl(bin, leader, kWave);
+      const uint64_t same = __ballot(bin == lb);
+      if (lane_id() == leader) atomicAdd(&s.hist[lb], (uint32_t)__popcll(same));
+      pending &= ~same;
+    }
+  });
+  __syncthreads();
+  pick_bin<4096 / kBlock>(s, need);
+  uint64_t prefix = (uint64_t)s.dig << 32;
+  uint32_t rem = need - s.below;
+  int sh = 32;
+  while (s.in != rem && sh > 0) {
+    sh -= 8;
+    __syncthreads();
+    s.hist[threadIdx.x] = 0;
+    __syncthreads();
+    each([&](uint64_t key) {
+      if (key != kNoKey && ((key & kLow48) >> (sh + 8)) == (prefix >> (sh + 8)))
+        atomicAdd(&s.hist[(key >> sh) & 255u], 1u);
+    });
+    __syncthreads();
+    pick_bin<1>(s, rem);
+    prefix |= (uint64_t)s.dig << sh;
+    rem -= s.below;
+  }
+  __syncthreads();
+  return prefix | ((1ull << sh) - 1);
+}
+
+__global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
   __shared__ uint64_t s_sel[kMaxW];
-  __shared__ uint32_t s_hist[4096];
-  __shared__ uint32_t s_cnt, s_thr, s_take, s_nsel;
+  __shared__ SelLds s_lds;
+  __shared__ SelPart s_part;
+  __shared__ uint32_t s_n, s_last;
   const RunStatus* st = v.st;
   const uint32_t total = st->ncand_total, last = st->ncand_level;
   const uint32_t prev = total - last;
   const uint32_t w = (uint32_t)v.w;
-  if (total <= w) {
-    for (uint32_t i = threadIdx.x; i < total; i += kCtl) s_sel[i] = v.cand[i];
-    if (threadIdx.x == 0) s_nsel = total;
-  } else {
-    const uint32_t need = w - prev;
-    for (uint32_t i = threadIdx.x; i < prev; i += kCtl) s_sel[i] = v.cand[i];
-    for (int i = threadIdx.x; i < 4096; i += kCtl) s_hist[i] = 0;
-    __syncthreads();
-    // the level's sums crowd into a few bins: one LDS atomic per distinct bin
-    // of a wavefront instead of one per candidate
-    for (uint32_t base = prev; base < total; base += kCtl) {
-      const uint32_t i = base + threadIdx.x;
-      const int bin = i < total ? (int)((v.cand[i] >> 32) & 0xFFF) : -1;
-      uint64_t pending = __ballot(bin >= 0);
-      while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int lb = __shfl(bin, leader, kWave);
-        const uint64_t same = __ballot(bin == lb);
-        if (lane_id() == leader) atomicAdd(&s_hist[lb], (uint32_t)__popcll(same));
-        pending &= ~same;
-      }
+  const uint32_t want = w - min(w, prev);   // slots for the last level
+  const bool staged = v.ncand && total >= w;
+  const int parts = gridDim.x, part = blockIdx.x;
+  // the part's keys: [lo, hi) of the last level's
+  const uint32_t lo = (staged ? 0u : prev) + (uint32_t)((uint64_t)last * part / parts);
+  const uint32_t hi = (staged ? 0u : prev) + (uint32_t)((uint64_t)last * (part + 1) / parts);
+  if (staged) {
+    const int per = (v.nblocks + kBlock - 1) / kBlock;
+    const int b0 = min(v.nblocks, (int)threadIdx.x * per), b1 = min(v.nblocks, b0 + per);
+    uint32_t sum = 0, tot;
+    for (int b = b0; b < b1; ++b) sum += v.ncand[b];
+    uint32_t at = block_exclusive_scan<uint32_t, kBlock>(sum, s_lds.scan, &tot);
+    for (int b = b0; b < b1; ++b) {
+      s_part.pre[b] = at;
+      const uint32_t n = v.ncand[b];
+      if (lo < hi && lo >= at && lo < at + n) s_part.b0 = b;
+      if (lo < hi && hi > at && hi <= at + n) s_part.b1 = b + 1;
+      at += n;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t cum = 0, thr = 0;
-      for (uint32_t s = 0; s < 4096; ++s) {
-        if (cum + s_hist[s] >= need) { thr = s; break; }
-        cum += s_hist[s];
-      }
-      s_thr = thr;
-      s_take = need - cum;
-      s_cnt = prev;
-      s_nsel = w;
-    }
-    __syncthreads();
-    const uint32_t thr = s_thr;
-    // ties at the threshold sum go to the smallest node ids: unless every tie
-    // is kept, a byte-wise radix select finds the take-th smallest id T among
-    // them (ids are unique, so exactly `take` ties have an id <= T)
-    uint32_t T = 0xFFFFFFFFu;
-    if (s_hist[thr] != s_take) {
-      uint32_t prefix = 0, mask = 0, rem = s_take;
-      for (int sh = 24; sh >= 0; sh -= 8) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < 256; i += kCtl) s_hist[i] = 0;
-        __syncthreads();
-        for (uint32_t i = prev + threadIdx.x; i < total; i += kCtl) {
-          const uint64_t key = v.cand[i];
-          const uint32_t id = (uint32_t)key;
-          if (((uint32_t)(key >> 32) & 0xFFFF) == thr && (id & mask) == prefix)
-            atomicAdd(&s_hist[(id >> sh) & 255u], 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-          uint32_t cum = 0;
-          for (uint32_t d = 0; d < 256; ++d) {
-            if (cum + s_hist[d] >= rem) { s_thr = prefix | (d << sh); s_take = rem - cum; break; }
-            cum += s_hist[d];
-          }
-        }
-        __syncthreads();
-        prefix = s_thr;
-        rem = s_take;
-        mask |= 255u << sh;
-      }
-      T = prefix;
-    }
-    for (uint32_t i = prev + threadIdx.x; i < total; i += kCtl) {
-      const uint64_t key = v.cand[i];
-      const uint32_t s = (uint32_t)(key >> 32) & 0xFFFF;
-      if (s < thr || (s == thr && (uint32_t)key <= T)) s_sel[atomicAdd(&s_cnt, 1u)] = key;
-    }
   }
+  if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
-  const uint32_t nsel = s_nsel;
-  for (uint32_t i = threadIdx.x; i < nsel; i += kCtl) {
+  auto mine = [&](auto f) { each_key(v, staged, s_part, lo, hi, f); };
+  uint64_t bound = kLow48;
+  if (want && hi - lo > want) bound = select_bound(s_lds, want, mine);
+  mine([&](uint64_t key) {
+    if (key != kNoKey && (key & kLow48) <= bound && want) s_sel[atomicAdd(&s_n, 1u)] = key;
+  });
+  __syncthreads();
+  uint32_t n = s_n;
+  if (parts > 1) {
+    // publish the part's keys; the last workgroup goes on with all of them
+    for (uint32_t i = threadIdx.x; i < n; i += kBlock) v.part_keys[(size_t)part * kMaxW + i] = s_sel[i];
+    if (threadIdx.x == 0) v.part_n[part] = n;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&v.gst->sel_ticket, 1u) == (uint32_t)parts - 1;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    // all kept keys: part p's in slots [p * kMaxW, p * kMaxW + part_n[p])
+    if (threadIdx.x == 0) { s_n = 0; v.gst->sel_ticket = 0; }
+    __syncthreads();
+    uint32_t all = 0, tot;
+    if ((int)threadIdx.x < parts) all = v.part_n[threadIdx.x];
+    (void)block_exclusive_scan<uint32_t, kBlock>(all, s_lds.scan, &tot);
+    auto kept = [&](auto f) {
+      for (int p = wave_id(); p < (parts + 3) / 4 * 4; p += kBlock / kWave) {
+        const uint32_t k = p < parts ? v.part_n[p] : 0u;
+        for (uint32_t i = 0; i < k; i += kWave)
+          f(i + lane_id() < k ? v.part_keys[(size_t)p * kMaxW + i + lane_id()] : kNoKey);
+      }
+    };
+    bound = kLow48;
+    if (want && tot > want) bound = select_bound(s_lds, want, kept);
+    kept([&](uint64_t key) {
+      if (key != kNoKey && (key & kLow48) <= bound) s_sel[atomicAdd(&s_n, 1u)] = key;
+    });
+    __syncthreads();
+    n = s_n;
+  }
+  for (uint32_t i = threadIdx.x; i < min(prev, w); i += kBlock) s_sel[n + i] = v.cand[i];
+  __syncthreads();
+  const uint32_t nsel = n + min(prev, w);
+  for (uint32_t i = threadIdx.x; i < nsel; i += kBlock) {
     const uint64_t key = s_sel[i];
     uint32_t rank = 0;
     for (uint32_t j = 0; j < nsel; ++j) rank += s_sel[j] < key;
@@ -851,10 +1085,6 @@ __global__ __launch_bounds__(kBlock) void k_rerank(ResultHdr* hdr, Status* gst, 
   if (threadIdx.x == 0) gst->nres = min(n, k);
 }
 
-__global__ void k_clear_rpg(int32_t* has, int32_t* sm, int64_t* key, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) { has[i] = 0; sm[i] = 0; key[i] = 0; }
-}
-
 // ------------------------------------------------------------ launchers ---
 
 #define RAKS_TP_DISPATCH(TP, ...)                         \
@@ -864,44 +1094,99 @@ __global__ void k_clear_rpg(int32_t* has, int32_t* sm, int64_t* key, int n) {
     default: { constexpr int kTP = 16; __VA_ARGS__; } break; \
   }
 
-void launch_run_init(const RunView& r, int TP, int32_t n, const int32_t* kw_nodes,
-                     const SeedList& seeds, hipStream_t s) {
-  int empty = 0;
-  for (int i = 0; i < seeds.T; ++i) empty |= seeds.count[i] == 0;
-  k_run_reset<<<1, 1, 0, s>>>(r.st, empty, r.kind == RUN_MARGINAL ? r.nsel : nullptr, r.sb);
-  const unsigned g = (unsigned)std::min<int64_t>(8192, (r.n_pad + kBlock - 1) / kBlock);
-  RAKS_TP_DISPATCH(TP, k_init_rows<kTP><<<g, kBlock, 0, s>>>(
-                           r.H, reinterpret_cast<RMaskT<kTP>*>(r.R), n, r.n_pad, r.T));
-  const uint32_t total = seeds.prefix[seeds.T];
+namespace {
+
+InitRun init_run(const RunView& r, int TP) {
+  InitRun x = {};
+  x.H = reinterpret_cast<uint32_t*>(r.H);
+  x.words = (uint64_t)r.n_pad * TP / 4;
+  x.row_words = (uint32_t)TP / 4;
+  uint8_t pat[16];
+  for (int i = 0; i < 16; ++i) pat[i] = i % TP < r.T ? kInf : 0;
+  __builtin_memcpy(x.pat, pat, 16);
+  x.R = reinterpret_cast<uint32_t*>(r.R);
+  x.r_words = (uint64_t)r.n_pad * r_bits(TP) / 32;
+  return x;
+}
+
+bool empty_keyword(const SeedList& s) {
+  for (int i = 0; i < s.T; ++i)
+    if (s.count[i] == 0) return true;
+  return false;
+}
+
+}  // namespace
+
+void launch_query_init(Status* gst, const RunView& c, int TPc, const SeedList& sc, const RunView& m,
+                       int TPm, const SeedList& sm, bool central, const int32_t* kw_nodes,
+                       hipStream_t s) {
+  InitView v = {};
+  SeedView sv = {};
+  v.gst = gst;
+  v.central = central;
+  v.has_rpg = c.has_rpg;
+  v.sm = c.sm;
+  v.key = c.key;
+  uint64_t words = 0;
+  for (int k = 0; k < 2; ++k) {
+    const RunView& r = k ? m : c;
+    const SeedList& seeds = k ? sm : sc;
+    if (r.T == 0 || (k == 0 && !central)) continue;
+    v.run[k] = init_run(r, k ? TPm : TPc);
+    v.empty[k] = empty_keyword(seeds);
+    words += v.run[k].words / 4;
+    sv.H[k] = r.H;
+    sv.TP[k] = k ? TPm : TPc;
+    sv.s[k] = seeds;
+  }
+  const unsigned g = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(4096, (words + kBlock - 1) / kBlock));
+  k_query_init<<<g, kBlock, 0, s>>>(v);
+  const uint64_t total = (uint64_t)sv.s[0].prefix[sv.s[0].T] + sv.s[1].prefix[sv.s[1].T];
   if (total > 0) {
-    const unsigned gs = (unsigned)std::min<uint32_t>(4096, (total + kBlock - 1) / kBlock);
-    RAKS_TP_DISPATCH(TP, k_seed<kTP><<<gs, kBlock, 0, s>>>(r.H, kw_nodes, seeds));
+    const unsigned gs = (unsigned)std::min<uint64_t>(4096, (total + kBlock - 1) / kBlock);
+    k_seed<<<gs, kBlock, 0, s>>>(sv, kw_nodes);
   }
-  if (r.kind == RUN_MARGINAL) k_clear_rpg<<<1, kBlock, 0, s>>>(r.has_rpg, r.sm, r.key, kMaxW);
 }
 
-void launch_front_count(const RunView& r, int TP, const DevGraphView& g, int level, hipStream_t s) {
-  RAKS_TP_DISPATCH(TP, k_front_count<kTP><<<r.nblocks, kBlock, 0, s>>>(r, g, level));
-}
-
-void launch_front_enqueue(const RunView& r, int TP, int level, RunStatus* mirror, uint64_t seq,
-                          hipStream_t s) {
-  RAKS_TP_DISPATCH(TP, k_front_enqueue<kTP><<<r.nblocks + 1, kCtl, 0, s>>>(r, level, mirror, seq));
-}
-
-
-void launch_expand(const RunView& r, int TP, const DevGraphView& g, int level, int grid,
-                   hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (ev0 && ev1) {
-    // the events take the kernel's own start and end times
-    RAKS_TP_DISPATCH(TP, hipExtLaunchKernelGGL(k_expand<kTP>, dim3(grid), dim3(kBlock), 0, s,
-                                               ev0, ev1, 0, r, g, level));
+void launch_front_scan(const RunView& r, int TP, const DevGraphView& g, int level, hipStream_t s) {
+  const bool in = level < g.nbnd;
+  if (r.kind == RUN_CENTRAL) {
+    RAKS_TP_DISPATCH(TP, if (in) k_front_scan<kTP, true, true><<<r.nblocks, kBlock, 0, s>>>(r, g, level);
+                     else k_front_scan<kTP, true, false><<<r.nblocks, kBlock, 0, s>>>(r, g, level));
   } else {
-    RAKS_TP_DISPATCH(TP, k_expand<kTP><<<grid, kBlock, 0, s>>>(r, g, level));
+    const size_t lds = rpg_lds_bytes(r.w, r.T);
+    RAKS_TP_DISPATCH(TP, if (in) k_front_scan<kTP, false, true><<<r.nblocks + 1, kBlock, lds, s>>>(r, g, level);
+                     else k_front_scan<kTP, false, false><<<r.nblocks + 1, kBlock, lds, s>>>(r, g, level));
   }
 }
 
-void launch_select(const SelectView& v, hipStream_t s) { k_select<<<1, kCtl, 0, s>>>(v); }
+// No more workgroups than the level can have tiles (every scan workgroup's
+// arcs rounded up to whole tiles), and with the control step's no more than run
+// at once: one more would start when the first are done and double the time.
+void launch_expand(const RunView& r, int TP, const DevGraphView& g, int level, int num_cu,
+                   RunStatus* mirror, uint64_t seq, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const int64_t tiles = (int64_t)g.A / kWaveTile + r.nblocks;
+  auto go = [&](auto kernel, int nt, int at_once) {
+    const int waves = nt / kWave;
+    const int grid = 1 + (int)std::min<int64_t>(at_once - 1, (tiles + waves - 1) / waves);
+    // with events: they take the kernel's own start and end times
+    if (ev0 && ev1)
+      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, s, ev0, ev1, 0, r, g, level, mirror, seq);
+    else
+      kernel<<<grid, nt, 0, s>>>(r, g, level, mirror, seq);
+  };
+  if (r.nblocks <= kExpSmallNb) {
+    RAKS_TP_DISPATCH(TP, go(k_expand<kTP, kExpSmall>, kExpSmall, 6 * num_cu));
+  } else {
+    RAKS_TP_DISPATCH(TP, go(k_expand<kTP, kExpLarge>, kExpLarge, num_cu));
+  }
+}
+
+// One part per kSelPer scan workgroups; part_keys / part_n are not used by a
+// single part.
+void launch_select(const SelectView& v, hipStream_t s) {
+  k_select<<<(v.nblocks + kSelPer - 1) / kSelPer, kBlock, 0, s>>>(v);
+}
 
 void launch_rank(const RankView& v, hipStream_t s) { k_rank<<<1, kBlock, 0, s>>>(v); }
 

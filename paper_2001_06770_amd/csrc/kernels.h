@@ -49,6 +49,8 @@ __device__ inline uint32_t count_le(const DevGraphView& g, int32_t v, int x) {
   return a - rs;
 }
 
+constexpr uint32_t kHasFront = 0x80000000u;   // RunView::brief: the workgroup has frontier nodes
+
 // State of one exploration run (Section 4.2), laid out for one query.
 struct RunView {
   int32_t kind;          // RUN_CENTRAL / RUN_MARGINAL
@@ -62,19 +64,17 @@ struct RunView {
   int32_t n_pad;         // n rounded up to kScanNodes
   RunStatus* st;
   ScanTot* tot;          // [nblocks]
-  uint32_t* sb;          // [2][kScanGroups / 64][3] sums of nq, work, ncand per 64 scan
-                         // workgroups, double-buffered by level parity
+  uint2* brief;          // [nblocks] examined arcs; staged entries | kHasFront
+  uint32_t* ncand;       // [nblocks] staged central nodes
   int32_t nblocks;       // frontier-scan workgroups
   int32_t cpw;           // kScanNodes-chunks per scan workgroup
-  uint4* s_item;         // [n_pad] staged queue entries (local arc prefix, rs, lo, mask)
-  uint64_t* s_cand;      // [n_pad] staged central-node keys
-  uint32_t* q_off;       // expansion queue: exclusive prefix of examined arcs [nactive+1]
-  uint32_t* q_rs;        // first examined arc (position in the level-sorted row)
-  uint32_t* q_lo;        // from here on the arcs have level == l: old keywords join
-  uint32_t* q_mask;      // keywords reached at level l | keywords reached before << 16
-  uint32_t* tile_first;  // [A / kExpandTile + 2] queue entry holding each expansion tile's
-                         // first arc (| kTileAtEntry when the tile starts with the entry)
-  uint64_t* cand;        // central run: identified central nodes (S<<48 | sum<<32 | original id)
+  uint4* s_item;         // [n_pad] staged entries, each scan workgroup's in its own node range:
+                         // local prefix of examined arcs, first examined arc (position in the
+                         // level-sorted row), the arc from which on the arcs have level == l
+                         // (old keywords join), keywords reached at level l | before << 16
+  uint64_t* s_cand;      // [n_pad] staged central-node keys of the level, likewise
+  uint64_t* cand;        // central run: central nodes (S<<48 | sum<<32 | original id) of the
+                         // levels so far while they are fewer than w
   int32_t max_level;
   int32_t w, k, gamma_num, gamma_den;
   int32_t score_mode;        // 0: Eq. 6, 1: S^c * S^m
@@ -90,6 +90,9 @@ struct RunView {
   uint8_t* dmin;             // [nsel][kMaxKw]
 };
 
+// Bits per node of a run's reached masks with rows of TP bytes.
+constexpr int r_bits(int TP) { return TP == 4 ? 4 : (TP == 8 ? 8 : 16); }
+
 struct SeedList {
   uint32_t start[kMaxKw];   // offset into kw_nodes
   uint32_t count[kMaxKw];
@@ -97,9 +100,18 @@ struct SeedList {
   int32_t T;
 };
 
+constexpr int kSelParts = 64;   // workgroups of the selection, at most
+
 struct SelectView {
   const int32_t* int_id;    // original id (in the keys) -> internal id
-  const uint64_t* cand;
+  const uint64_t* cand;     // keys: earlier levels first, then the last level's
+  // with `ncand`, and w central nodes or more, the last level's keys are where
+  // the scan workgroups staged them
+  const uint32_t* ncand;
+  const uint64_t* s_cand;
+  int32_t nblocks, cpw;     // scan workgroups; nblocks also sets the launch's size
+  uint64_t* part_keys;      // scratch [kSelParts][kMaxW], part_n [kSelParts]
+  uint32_t* part_n;
   RunStatus* st;
   Status* gst;
   int32_t w;
@@ -236,9 +248,10 @@ __device__ inline uint32_t find_arc_dev(uint32_t lo, uint32_t hi, const int32_t*
 }
 
 // max_sel: an upper bound of the device-side nsel (one workgroup per CG)
+// marginal (optional): the run's status, ended at once when there is no CG
 void launch_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp, const uint64_t* cg_noff,
                     const int32_t* nsel, uint32_t* vc_off, int32_t* vc_nodes, int max_sel,
-                    hipStream_t s);
+                    RunStatus* marginal, hipStream_t s);
 void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc_src, uint32_t* rev,
                             Status* st,
                             hipStream_t s);
@@ -276,17 +289,20 @@ void launch_node_weight_range(const DevGraphView& g, const uint8_t* nw, Status* 
 void launch_act_node(const DevGraphView& g, const uint8_t* nw, const uint8_t* lut, uint32_t wmin,
                      uint8_t* act_node, hipStream_t s);
 
-void launch_run_init(const RunView& r, int TP, int32_t n, const int32_t* kw_nodes,
-                     const SeedList& seeds, hipStream_t s);
-void launch_front_count(const RunView& r, int TP, const DevGraphView& g, int level, hipStream_t s);
-// The level's control step and Frontier Enqueue in one launch.  mirror:
-// device-visible pinned host memory that receives the level's status,
-// stamped with seq once the rest of it is visible to the host.
-void launch_front_enqueue(const RunView& r, int TP, int level, RunStatus* mirror, uint64_t seq,
-                          hipStream_t s);
-// ev0 / ev1 (optional): events that receive the kernel's start and end times
-void launch_expand(const RunView& r, int TP, const DevGraphView& g, int level, int grid,
-                   hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Start of a query: both runs' matrices, reached masks and statuses, the RPG
+// records, then the keyword nodes (M == 0: no marginal run).  `central` false:
+// the marginal run alone, for a repeat.
+void launch_query_init(Status* gst, const RunView& c, int TPc, const SeedList& sc, const RunView& m,
+                       int TPm, const SeedList& sm, bool central, const int32_t* kw_nodes,
+                       hipStream_t s);
+void launch_front_scan(const RunView& r, int TP, const DevGraphView& g, int level, hipStream_t s);
+// The expansion with the level's control step.  mirror: device-visible pinned
+// host memory that receives the level's status, stamped with seq once the rest
+// of it is visible to the host.  ev0 / ev1 (optional): events that receive the
+// kernel's start and end times.
+void launch_expand(const RunView& r, int TP, const DevGraphView& g, int level, int num_cu,
+                   RunStatus* mirror, uint64_t seq, hipStream_t s, hipEvent_t ev0 = nullptr,
+                   hipEvent_t ev1 = nullptr);
 void launch_select(const SelectView& v, hipStream_t s);
 void launch_rank(const RankView& v, hipStream_t s);
 // Re-ranking of equal scores by the arcs' level sum; keeps the first k.

@@ -892,12 +892,19 @@ __global__ __launch_bounds__(kBlock) void k_big_write(FinalizeView v, int t, int
 // the CGs before it and copies CG r's list there.
 __global__ __launch_bounds__(kBlock) void k_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp,
                                                     const uint64_t* cg_noff, const int32_t* nsel_p,
-                                                    uint32_t* vc_off, int32_t* vc_nodes) {
+                                                    uint32_t* vc_off, int32_t* vc_nodes,
+                                                    RunStatus* marginal) {
   __shared__ uint32_t s32[kBlock / kWave + 1];
   const int nsel = *nsel_p;
   const int r = blockIdx.x;
   if (r >= nsel) {
-    if (r == 0 && threadIdx.x == 0) vc_off[0] = 0;   // no CG: empty lists
+    if (r == 0 && threadIdx.x == 0) {   // no CG: empty lists, no marginal run
+      vc_off[0] = 0;
+      if (marginal) {
+        marginal->end_level = -1;
+        marginal->end_reason = END_NONE;
+      }
+    }
     return;
   }
   uint32_t part = 0;
@@ -1008,8 +1015,9 @@ void launch_big_finalize(const FinalizeView& v, int t, uint32_t* bm, uint32_t* c
 
 void launch_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp, const uint64_t* cg_noff,
                     const int32_t* nsel, uint32_t* vc_off, int32_t* vc_nodes, int max_sel,
-                    hipStream_t s) {
-  if (max_sel > 0) k_pack_vc<<<max_sel, kBlock, 0, s>>>(vc_cnt, vc_tmp, cg_noff, nsel, vc_off, vc_nodes);
+                    RunStatus* marginal, hipStream_t s) {
+  if (max_sel > 0)
+    k_pack_vc<<<max_sel, kBlock, 0, s>>>(vc_cnt, vc_tmp, cg_noff, nsel, vc_off, vc_nodes, marginal);
 }
 
 }  // namespace raks

@@ -90,7 +90,7 @@ struct Lane {
   bool no_alloc = false;   // the allocation-free lane: no event timing, buffers from scratch
 
   int32_t n_pad = 0, nblocks = 0, cpw = 1;
-  DevBuf Hc, Hm, R, tot, sb, q_off, q_rs, q_lo, q_mask, tile_first, cand, s_item, s_cand;
+  DevBuf Hc, Hm, R, tot, brief, cand, s_item, s_cand;
   DevBuf sel_node, sel_sc, sel_sumh, has_rpg, sm, key, dmin, ranked;
   DevBuf vc_cnt, vc_tmp, vc_off, vc_nodes;
   // recovery storage, shared by both phases (sized for the larger one)
