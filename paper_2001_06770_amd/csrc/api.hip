@@ -143,7 +143,7 @@ std::vector<DevBuf*> lane_buffers(Lane* L) {
       &L->sel_sumh, &L->has_rpg, &L->sm, &L->key, &L->dmin, &L->ranked, &L->vc_cnt,
       &L->vc_tmp, &L->vc_off, &L->vc_nodes, &L->hpool, &L->nl, &L->al, &L->items, &L->sort_a,
       &L->sort_b, &L->cg_nodes, &L->cg_arcs, &L->cg_cnt, &L->hdr, &L->out_nodes, &L->out_arcs,
-      &L->bigf, &L->big_bm, &L->big_chunk, &L->big_slot};
+      &L->mid, &L->bigf, &L->big_bm, &L->big_chunk, &L->big_slot};
   for (RecPhase& P : L->ph)
     for (DevBuf* b : {&P.layout, &P.cnt, &P.iflag, &P.lcnt, &P.touch, &P.tcnt}) v.push_back(b);
   v.push_back(&L->lab);
@@ -623,6 +623,7 @@ __global__ void k_query_reset(Status* st) {
   st->sel_ticket = 0;
   st->nres = 0;
   st->overflow = 0;
+  st->mid_lists = 0;
   st->out_nodes = 0;
   st->out_arcs = 0;
 }
@@ -869,6 +870,8 @@ int ensure_recovery(Lane* L, const QueryPlan& p) {
   RAKS_TRY(dev_alloc(c, L->hdr, (size_t)std::max(P1.n_res, 1) * sizeof(ResultHdr)));
   RAKS_TRY(dev_alloc(c, L->bigf, (size_t)std::max({P0.n_res, P1.n_res, 1}) * 4));
   RAKS_TRY(dev_alloc(c, L->out_nodes, std::max<uint64_t>(P1.out_n, 1) * 4));
+  RAKS_TRY(dev_alloc(c, L->mid, 2 * (size_t)std::max(P1.n_res, 1) *
+                                    (sizeof(MidList) + finalize_slices(c->n, c->A) * sizeof(uint2))));
   RAKS_TRY(dev_alloc(c, L->out_arcs, std::max<uint64_t>(P1.out_a, 1) * 12));
   // labels of the labelled mode: [T * G][n] words for the larger phase
   uint64_t lw = 0;
@@ -970,6 +973,7 @@ RecoverView recover_view(Lane* L, int ph, const uint8_t* H, int TP, const int32_
   v.dmin = P<uint8_t>(L->dmin);
   v.caps = P<InstCap>(Ph.layout);
   v.hpool = P<uint32_t>(L->hpool);
+  v.vc_cnt = P<uint32_t>(L->vc_cnt);
   v.nl = P<int32_t>(L->nl);
   v.al = P<uint32_t>(L->al);
   v.cnt = P<uint32_t>(Ph.cnt);
@@ -1033,6 +1037,9 @@ FinalizeView finalize_view(Lane* L, int ph, const int32_t* n_valid, int C, const
   v.big = P<uint32_t>(L->bigf);
   v.big_list = L->ctx->big_list;
   v.hdr = P<ResultHdr>(L->hdr);
+  v.mid_z = (uint32_t)finalize_slices(L->ctx->n, L->ctx->A);
+  v.mid = P<MidList>(L->mid);
+  v.mid_slice = reinterpret_cast<uint2*>(v.mid + 2 * (size_t)std::max(L->ph[1].n_res, 1));
   v.out_nodes = P<int32_t>(L->out_nodes);
   v.out_arcs = P<int32_t>(L->out_arcs);
   v.out_ncap = (uint32_t)std::min<size_t>(L->out_nodes.bytes / 4, UINT32_MAX);
@@ -1050,6 +1057,7 @@ FinalizeView finalize_view(Lane* L, int ph, const int32_t* n_valid, int C, const
 __global__ void k_retry_reset(Status* st) {
   st->overflow = 0;
   st->out_nodes = 0;
+  st->mid_lists = 0;
   st->out_arcs = 0;
 }
 

@@ -57,7 +57,7 @@ struct Status {
   uint32_t out_nodes, out_arcs;  // output arena use
   uint64_t pairs;        // arcs that searched for their reverse (load)
   uint32_t sel_ticket;   // workgroups of the selection that are done; 0 between selections
-  uint32_t pad;
+  uint32_t mid_lists;    // result lists beyond one workgroup's LDS (k_fin_slices)
 };
 
 // Per-workgroup totals of the frontier scan that the level's record sums up.

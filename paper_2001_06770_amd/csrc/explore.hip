@@ -128,6 +128,7 @@ __global__ __launch_bounds__(kBlock) void k_query_init(InitView v) {
   if (threadIdx.x == 0 && v.central) {
     v.gst->nsel = 0;
     v.gst->sel_ticket = 0;
+    v.gst->mid_lists = 0;
     v.gst->nres = 0;
     v.gst->overflow = 0;
     v.gst->out_nodes = 0;

@@ -167,6 +167,7 @@ struct RecoverView {
   const uint32_t* vc_off;
   const int32_t* vc_nodes;
   const uint8_t* dmin;       // [nsel][kMaxKw]
+  uint32_t* vc_cnt;          // central graphs: sizes of V_C, zeroed with the phase's counters
   const InstCap* caps;       // [n_inst]
   uint32_t* hpool;           // node sets
   int32_t* nl;               // node lists
@@ -189,6 +190,13 @@ struct RecoverView {
   uint64_t* touch;           // [tcap] (column group << 32) | node, per labelled node
   uint32_t* tcnt;            // entries of `touch` requested (counted past tcap)
   uint32_t tcap;
+};
+
+// A list too long for one workgroup's LDS (n entries; 0: not such a list).
+struct MidList {
+  uint32_t n;
+  uint32_t done;             // slices finished
+  uint32_t total, base;      // distinct ids and their place in the output
 };
 
 // Union, sort and unique per result.
@@ -216,7 +224,8 @@ struct FinalizeView {
   int32_t TPc, Tc;
   uint32_t* vc_cnt;          // [nsel]
   int32_t* vc_tmp;
-  // sort scratch of result t: sort_a / sort_b from soff[t] to soff[t + 1]
+  // scratch of result t's long lists: sort_a (nodes) / sort_b (arcs) from
+  // soff[t] to soff[t + 1]
   uint32_t* sort_a;
   uint32_t* sort_b;
   const uint64_t* soff;
@@ -224,6 +233,10 @@ struct FinalizeView {
   int32_t write_output;
   int32_t skip_bits;         // overflow bits that make this finalize pointless (phase repeats)
   uint32_t* big;             // [n_res] 1: the result's lists go to the bitmap path
+  // long lists of RPGs and final results (list i: result i / 2, pass i % 2)
+  MidList* mid;              // [2 * n_res]
+  uint2* mid_slice;          // [2 * n_res][mid_z] per id slice: start in the scratch, ids before
+  uint32_t mid_z;
   uint64_t big_list;         // lists longer than this take the bitmap path
   ResultHdr* hdr;
   int32_t* out_nodes;
@@ -310,6 +323,7 @@ void launch_rerank(ResultHdr* hdr, Status* gst, int32_t k, hipStream_t s);
 void launch_recover(const RecoverView& v, hipStream_t s);   // all layers of one phase
 void launch_finalize(const FinalizeView& v, hipStream_t s);
 
+size_t finalize_slices(int64_t n, int64_t A);   // id slices of the longest list
 // Results to pinned host memory (device addresses of the host buffers).
 struct CollectView {
   const Status* st;

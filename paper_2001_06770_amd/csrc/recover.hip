@@ -138,6 +138,7 @@ __global__ __launch_bounds__(kBlock) void k_rec_clear(RecoverView v) {
   if ((int)(inst / v.T) >= *v.n_valid) return;
   const InstCap ic = v.caps[inst];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!v.marginal) v.vc_cnt[inst / v.T] = 0;
     v.cnt[inst * 2] = 0;
     v.cnt[inst * 2 + 1] = 0;
     v.iflag[inst] = 0;
@@ -268,6 +269,8 @@ __device__ inline void lr_fresh(const RecoverView& v, bool fresh, uint32_t jg, i
 __global__ __launch_bounds__(kBlock) void k_lr_clear(RecoverView v, size_t wipe_words) {
   const uint32_t tid = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
   for (uint32_t i = tid; i < (uint32_t)v.n_inst * 2u; i += stride) v.cnt[i] = 0;
+  if (!v.marginal)
+    for (uint32_t i = tid; i < (uint32_t)(v.n_inst / v.T); i += stride) v.vc_cnt[i] = 0;
   for (uint32_t i = tid; i < (uint32_t)v.n_inst; i += stride) v.iflag[i] = 0;
   for (uint32_t i = tid; i <= (uint32_t)v.max_layer; i += stride) v.lcnt[i] = 0;
   if (tid == 0) *v.tcnt = 0;
@@ -546,171 +549,402 @@ __global__ __launch_bounds__(kBlock) void k_lr_nodes(RecoverView v) {
   }
 }
 
-// Per result: gather the node lists (and arc lists) of its instances (and,
-// for an RPG, of its CG), radix sort, keep distinct keys.  For CGs also the
-// central-keyword nodes V_C (some central level 0).  Final results go to the
-// output arena with their header; arcs are written as (src, dst, label).
+// ------------------------------------------------- union, sort, unique ---
+//
+// A result's node (pass 0) and arc list (pass 1) are the distinct ids of its
+// instances' lists and, for an RPG, of its CG's.  One workgroup of k_finalize
+// takes a (result, pass) and picks by the number of entries:
+//   <= kRankSort   each thread counts the smaller entries of its one or two
+//                  (all in LDS): one round of LDS reads instead of four radix
+//                  passes of a dozen barriers, 2 us less on lists of 20;
+//   <= kLdsSort    radix sort in LDS;
+//   longer         CGs: the lists are copied as they are, by several workgroups.
+//                  Nothing needs them sorted or distinct: they only join their
+//                  RPGs' lists, and V_C is a set.
+//                  RPGs and final results: bitmaps in LDS.  k_fin_slices gives
+//                  every kSliceBits ids of the id range to a workgroup, which
+//                  reads the list, marks its ids and writes those present in
+//                  order; k_fin_emit writes the output.  Both return at once
+//                  when no list of the query is that long.
+// Beyond big_list entries the host runs the bitmap path over device memory
+// below.  (The longer lists used to be radix sorted by the one workgroup in
+// device memory: 1 ms for 46k arcs, 24 ms for 1.1M; the two kernels take 0.06 and
+// 0.7 ms on 40M arcs.)
+constexpr uint32_t kRankSort = 2 * kBlock;
+constexpr int kRawParts = 8;                       // k_finalize: workgroups per CG
+constexpr uint32_t kSliceBits = 1u << 20;          // 128 KB of LDS
+constexpr int kSliceT = 1024;
+
+// Lists of result t: f(source, entries, maps) for the CG's list (original ids)
+// and every instance's (maps: pass 0 holds internal ids).
+template <typename F>
+__device__ inline void each_list(const FinalizeView& v, int t, int pass, F f) {
+  if (v.marginal) {
+    const int r = v.ranked[t];
+    f(pass == 0 ? v.cg_nodes + v.cg_noff[r] : v.cg_arcs + v.cg_aoff[r], v.cg_cnt[r * 2 + pass], false);
+  }
+  for (int j = 0; j < v.T; ++j) {
+    const int inst = t * v.T + j;
+    const InstCap ic = v.caps[inst];
+    if (pass == 0)
+      f(reinterpret_cast<const uint32_t*>(v.nl) + ic.noff, min(v.cnt[inst * 2], ic.ncap), true);
+    else
+      f(v.al + ic.aoff, min(v.cnt[inst * 2 + 1], ic.acap), false);
+  }
+}
+
+// Sorts the n <= kRankSort entries of `a` into `b` by counting; equal entries
+// keep their order.  All of the workgroup's threads.
+__device__ inline void rank_sort(const uint32_t* a, uint32_t* b, uint32_t n) {
+  uint32_t key[2], rank[2] = {0, 0};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) key[k] = threadIdx.x + k * kBlock < n ? a[threadIdx.x + k * kBlock] : 0u;
+  for (uint32_t j = 0; j < n; ++j) {
+    const uint32_t x = a[j];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) rank[k] += x < key[k] || (x == key[k] && j < threadIdx.x + k * kBlock);
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (threadIdx.x + k * kBlock < n) b[rank[k]] = key[k];
+  __syncthreads();
+}
+
+// V_C test: a node (internal id) with some central level 0.
+__device__ inline bool is_vc(const FinalizeView& v, int64_t x) {
+  bool keep = false;
+  for (int c = 0; c < v.Tc; ++c) keep |= v.Hc[x * v.TPc + c] == 0;
+  return keep;
+}
+
+// Header fields of a pass's list.
+__device__ inline void put_header(const FinalizeView& v, int t, int pass, uint32_t off, uint32_t m,
+                                  int64_t wsum) {
+  ResultHdr& hd = v.hdr[t];
+  if (pass == 0) {
+    const int r = v.marginal ? v.ranked[t] : t;
+    hd.central = v.g.orig_id[v.sel_node[r]];
+    hd.score_c = v.sel_sc[r];
+    hd.score_m = v.sm[r];
+    hd.cg_rank = r;
+    hd.key = v.key[r];
+    hd.node_off = off;
+    hd.n_nodes = m;
+  } else {
+    hd.arc_off = off;
+    hd.n_arcs = m;
+    hd.wsum = wsum;
+  }
+}
+
+// Room for m entries in the pass's output; flags an arena that is too small.
+__device__ inline uint32_t take_output(const FinalizeView& v, int pass, uint32_t m) {
+  const uint32_t off = atomicAdd(pass == 0 ? &v.gst->out_nodes : &v.gst->out_arcs, m);
+  if ((uint64_t)off + m > (pass == 0 ? v.out_ncap : v.out_acap)) atomicOr(&v.gst->overflow, 4);
+  return off;
+}
+
+__device__ inline void put_output(const FinalizeView& v, int pass, uint32_t at, uint32_t id) {
+  if (pass == 0) {
+    v.out_nodes[at] = (int32_t)id;
+  } else {
+    int32_t* o = v.out_arcs + 3 * (size_t)at;
+    o[0] = v.g.arc_src[id];
+    o[1] = v.g.col[id];
+    o[2] = v.g.label[id];
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_finalize(FinalizeView v) {
   const int t = blockIdx.x;
+  const int part = blockIdx.y;   // 0: nodes, 1: arcs, beyond: help with a CG's long lists
   if (t >= *v.n_valid) {
-    if (threadIdx.x == 0) v.big[t] = 0;
+    if (part == 0 && threadIdx.x == 0) v.big[t] = 0;
+    if (part < 2 && v.marginal && threadIdx.x == 0) v.mid[t * 2 + part].n = 0;
     return;
   }
   bool skip = (v.gst->overflow & v.skip_bits) != 0;
-  uint64_t nn = 0, na = 0;   // input sizes of the node and arc lists
+  uint64_t size[2] = {0, 0};
   if (!skip) {
-    // inputs beyond big_list go to the bitmap path (k_big_*), run by the host
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      each_list(v, t, p, [&](const uint32_t*, uint32_t cnt, bool) { size[p] += cnt; });
+    // lists beyond big_list go to the bitmap path (k_big_*), run by the host
     // once this launch has finished
-    const int r0 = v.marginal ? v.ranked[t] : t;
-    nn = v.marginal ? v.cg_cnt[r0 * 2] : 0u;
-    na = v.marginal ? v.cg_cnt[r0 * 2 + 1] : 0u;
-    for (int j = 0; j < v.T; ++j) {
-      const InstCap ic = v.caps[t * v.T + j];
-      nn += min(v.cnt[(t * v.T + j) * 2], ic.ncap);
-      na += min(v.cnt[(t * v.T + j) * 2 + 1], ic.acap);
+    const bool big = size[0] > v.big_list || size[1] > v.big_list;
+    if (part == 0 && threadIdx.x == 0) {
+      v.big[t] = big;
+      if (big) atomicOr(&v.gst->overflow, v.marginal ? kOvfBig1 : kOvfBig0);
     }
-    if (nn > v.big_list || na > v.big_list) {
-      if (threadIdx.x == 0) {
-        v.big[t] = 1;
-        atomicOr(&v.gst->overflow, v.marginal ? kOvfBig1 : kOvfBig0);
-      }
-      skip = true;
-    } else if (threadIdx.x == 0) {
-      v.big[t] = 0;
-    }
-  } else if (threadIdx.x == 0) {
+    skip = big;
+  } else if (part == 0 && threadIdx.x == 0) {
     v.big[t] = 0;
   }
   if (skip) {
-    // the phase is repeated or finished elsewhere: record empty CG lists so
+    // the phase is repeated or finished elsewhere: record empty lists so
     // nothing reads stale sizes
-    if (!v.marginal && threadIdx.x == 0) {
-      v.cg_cnt[t * 2] = 0;
-      v.cg_cnt[t * 2 + 1] = 0;
-      v.vc_cnt[t] = 0;
+    if (part < 2 && threadIdx.x == 0) {
+      if (v.marginal) {
+        v.mid[t * 2 + part].n = 0;
+      } else {
+        v.cg_cnt[t * 2 + part] = 0;
+        if (part == 0) v.vc_cnt[t] = 0;
+      }
+    }
+    return;
+  }
+  const DevGraphView& g = v.g;
+  if (!v.marginal) {
+    // a CG's long lists, as they are; V_C in any order (k_rec_clear zeroed its count)
+    for (int pass = 0; pass < 2; ++pass) {
+      if (size[pass] <= kLdsSort || part == 1 - pass) continue;
+      const uint32_t me = part < 2 ? 0u : (uint32_t)part - 1u;
+      uint32_t at = 0;
+      each_list(v, t, pass, [&](const uint32_t* src, uint32_t cnt, bool maps) {
+        for (uint32_t i0 = me * kBlock; i0 < cnt; i0 += (kRawParts - 1) * kBlock) {
+          const uint32_t i = i0 + threadIdx.x;
+          const uint32_t x = i < cnt ? src[i] : 0u;
+          if (pass == 1) {
+            if (i < cnt) v.cg_arcs[v.cg_aoff[t] + at + i] = x;
+            continue;
+          }
+          if (i < cnt) v.cg_nodes[v.cg_noff[t] + at + i] = (uint32_t)g.orig_id[x];
+          const bool keep = i < cnt && is_vc(v, x);
+          const uint64_t kb = __ballot(keep);
+          if (!kb) continue;
+          uint32_t base = 0;
+          if (lane_id() == 0) base = atomicAdd(&v.vc_cnt[t], (uint32_t)__popcll(kb));
+          base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+          if (keep) v.vc_tmp[v.cg_noff[t] + base + __popcll(kb & ((1ull << lane_id()) - 1))] = (int32_t)x;
+        }
+        at += cnt;
+      });
+      if (part == pass && threadIdx.x == 0) v.cg_cnt[t * 2 + pass] = at;
+    }
+    if (part >= 2) return;
+  }
+  const int pass = part;
+  if (size[pass] > kLdsSort) {
+    if (v.marginal && threadIdx.x == 0) {
+      MidList m = {(uint32_t)size[pass], 0, 0, 0};
+      v.mid[t * 2 + pass] = m;
+      atomicAdd(&v.gst->mid_lists, 1u);
     }
     return;
   }
   __shared__ RadixLds lds;
-  __shared__ uint32_t s_off;
   __shared__ uint64_t s_ws[kBlock / kWave + 1];
+  __shared__ uint32_t s_off;
   __shared__ uint32_t s_sa[kLdsSort], s_sb[kLdsSort];
-  uint32_t* A_g = v.sort_a + v.soff[t];
-  uint32_t* B_g = v.sort_b + v.soff[t];
-  const int r = v.marginal ? v.ranked[t] : t;
-  const DevGraphView& g = v.g;
+  if (v.marginal && threadIdx.x == 0) v.mid[t * 2 + pass].n = 0;
+  uint32_t n = 0;
+  each_list(v, t, pass, [&](const uint32_t* src, uint32_t cnt, bool maps) {
+    for (uint32_t i = threadIdx.x; i < cnt; i += kBlock)
+      s_sa[n + i] = maps ? (uint32_t)g.orig_id[src[i]] : src[i];   // results list original ids
+    n += cnt;
+  });
+  __syncthreads();
+  uint32_t* sorted;
+  if (n <= kRankSort) {
+    rank_sort(s_sa, s_sb, n);
+    sorted = s_sb;
+  } else {
+    sorted = wg_radix_sort_u32(s_sa, s_sb, n, lds);
+  }
+  uint32_t* uniq = sorted == s_sa ? s_sb : s_sa;
+  const uint32_t m = wg_unique_u32(sorted, n, uniq, lds.scan);
+  __syncthreads();
+  if (!v.marginal) {
+    uint32_t* dst = pass == 0 ? v.cg_nodes + v.cg_noff[t] : v.cg_arcs + v.cg_aoff[t];
+    for (uint32_t i = threadIdx.x; i < m; i += kBlock) dst[i] = uniq[i];
+    if (threadIdx.x == 0) v.cg_cnt[t * 2 + pass] = m;
+    if (pass == 0) {
+      // V_C in node order, stored as internal ids
+      int32_t* vc = v.vc_tmp + v.cg_noff[t];
+      uint32_t written = 0;
+      for (uint32_t t0 = 0; t0 < m; t0 += kBlock) {
+        const uint32_t i = t0 + threadIdx.x;
+        uint32_t keep = 0;
+        int64_t x = 0;
+        if (i < m) {
+          x = g.int_id[uniq[i]];
+          keep = is_vc(v, x);
+        }
+        uint32_t tot;
+        const uint32_t ex = block_exclusive_scan<uint32_t, kBlock>(keep, lds.scan, &tot);
+        if (keep) vc[written + ex] = (int32_t)x;
+        written += tot;
+      }
+      if (threadIdx.x == 0) v.vc_cnt[t] = written;
+    }
+    return;
+  }
+  // sum of the arcs' activation levels (the re-ranking weight); integer, so
+  // any summation order gives the same value
+  uint64_t ws = 0;
+  if (pass == 1)
+    for (uint32_t i = threadIdx.x; i < m; i += kBlock) ws += g.act[uniq[i]];
+  ws = block_sum<uint64_t, kBlock>(ws, s_ws);
+  if (threadIdx.x == 0) {
+    s_off = take_output(v, pass, m);
+    put_header(v, t, pass, s_off, m, (int64_t)ws);
+  }
+  __syncthreads();
+  const uint32_t off = s_off;
+  if ((uint64_t)off + m <= (pass == 0 ? v.out_ncap : v.out_acap))
+    for (uint32_t i = threadIdx.x; i < m; i += kBlock) put_output(v, pass, off + i, uniq[i]);
+}
 
-  // When both lists fit LDS, the result's two workgroups (y = 0, 1) take the
-  // node and the arc pass at once; otherwise workgroup 0 takes both, since
-  // they share the result's global sort scratch.
-  const bool split = nn <= kLdsSort && na <= kLdsSort;
-  if (!split && blockIdx.y == 1) return;
-  const int p0 = split ? (int)blockIdx.y : 0, p1 = split ? p0 + 1 : 2;
-  for (int pass = p0; pass < p1; ++pass) {   // 0: nodes, 1: arcs
-    // total input size first: small lists are sorted in LDS
-    uint32_t n = v.marginal ? v.cg_cnt[r * 2 + pass] : 0u;
-    for (int j = 0; j < v.T; ++j)
-      n += min(v.cnt[(t * v.T + j) * 2 + pass],
-               pass == 0 ? v.caps[t * v.T + j].ncap : v.caps[t * v.T + j].acap);
-    const bool small = n <= kLdsSort;
-    uint32_t* A = small ? s_sa : A_g;
-    uint32_t* B = small ? s_sb : B_g;
+// Work items of the long lists: list i (result i / 2, pass i % 2) has items(i)
+// of them; s_pre gets their prefix over lists, the total is returned.
+template <int NT, typename F>
+__device__ inline uint32_t list_items(int lists, uint32_t* s_pre, uint32_t* s_scan, F items) {
+  constexpr int kPer = 2 * kMaxW / NT > 0 ? 2 * kMaxW / NT : 1;
+  uint32_t x[kPer], sum = 0, tot;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = (int)threadIdx.x * kPer + k;
+    x[k] = i < lists ? items(i) : 0u;
+    sum += x[k];
+  }
+  uint32_t at = block_exclusive_scan<uint32_t, NT>(sum, s_scan, &tot);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = (int)threadIdx.x * kPer + k;
+    if (i < 2 * kMaxW) s_pre[i] = at;
+    at += x[k];
+  }
+  __syncthreads();
+  return tot;
+}
+
+// One id slice of one long list per step: the ids present, in order, go to the
+// list's scratch from where the ids below the slice could end (their number
+// with repeats).  The last slice of a list to finish places the list.
+__global__ __launch_bounds__(kSliceT) void k_fin_slices(FinalizeView v) {
+  if (v.gst->mid_lists == 0) return;
+  constexpr int kWords = kSliceBits / 32, kWaves = kSliceT / kWave, kPerWave = kWords / kWaves;
+  __shared__ uint32_t s_bm[kWords];
+  __shared__ uint32_t s_pre[2 * kMaxW], s_scan[kWaves + 1], s_last;
+  const int lists = 2 * min(v.n_res, *v.n_valid);
+  const uint32_t zs[2] = {((uint32_t)v.g.n - 1) / kSliceBits + 1, (v.g.A - 1) / kSliceBits + 1};
+  const uint32_t total = list_items<kSliceT>(lists, s_pre, s_scan,
+                                             [&](int i) { return v.mid[i].n ? zs[i & 1] : 0u; });
+  const int lane = lane_id(), wv = wave_id();
+  for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
+    const int li = upper_index<uint32_t>(s_pre, 0, lists, item);
+    const uint32_t z = item - s_pre[li];
+    const int t = li >> 1, pass = li & 1;
+    const uint32_t lo = z * kSliceBits;
+    for (int i = threadIdx.x * 4; i < kWords; i += kSliceT * 4)
+      *reinterpret_cast<uint4*>(&s_bm[i]) = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    n = 0;
-    if (v.marginal) {
-      const uint32_t cnt = v.cg_cnt[r * 2 + pass];
-      const uint32_t* src = pass == 0 ? v.cg_nodes + v.cg_noff[r] : v.cg_arcs + v.cg_aoff[r];
-      for (uint32_t i = threadIdx.x; i < cnt; i += kBlock) A[i] = src[i];
-      n = cnt;
-    }
-    for (int j = 0; j < v.T; ++j) {
-      const int inst = t * v.T + j;
-      const InstCap ic = v.caps[inst];
-      const uint32_t cnt = min(v.cnt[inst * 2 + pass], pass == 0 ? ic.ncap : ic.acap);
-      if (pass == 0) {
-        // recovered nodes are internal ids; results list original ids
-        const int32_t* src = v.nl + ic.noff;
-        for (uint32_t i = threadIdx.x; i < cnt; i += kBlock) A[n + i] = (uint32_t)g.orig_id[src[i]];
-      } else {
-        const uint32_t* src = v.al + ic.aoff;
-        for (uint32_t i = threadIdx.x; i < cnt; i += kBlock) A[n + i] = src[i];
-      }
-      n += cnt;
-    }
-    __syncthreads();
-    uint32_t* sorted = wg_radix_sort_u32(A, B, n, lds);
-    uint32_t* uniq = (sorted == A) ? B : A;
-    const uint32_t m = wg_unique_u32(sorted, n, uniq, lds.scan);
-    __syncthreads();
-    if (!v.marginal) {
-      uint32_t* dst = pass == 0 ? v.cg_nodes + v.cg_noff[r] : v.cg_arcs + v.cg_aoff[r];
-      for (uint32_t i = threadIdx.x; i < m; i += kBlock) dst[i] = uniq[i];
-      if (threadIdx.x == 0) v.cg_cnt[r * 2 + pass] = m;
-      if (pass == 0) {
-        // V_C in node order, stored as internal ids
-        int32_t* vc = v.vc_tmp + v.cg_noff[r];
-        uint32_t written = 0;
-        for (uint32_t t0 = 0; t0 < m; t0 += kBlock) {
-          const uint32_t i = t0 + threadIdx.x;
-          uint32_t keep = 0;
-          int64_t x = 0;
-          if (i < m) {
-            x = g.int_id[uniq[i]];
-            for (int c = 0; c < v.Tc; ++c) keep |= v.Hc[x * v.TPc + c] == 0;
-          }
-          uint32_t tot;
-          const uint32_t ex = block_exclusive_scan<uint32_t, kBlock>(keep, lds.scan, &tot);
-          if (keep) vc[written + ex] = (int32_t)x;
-          written += tot;
+    uint32_t below = 0;
+    each_list(v, t, pass, [&](const uint32_t* src, uint32_t cnt, bool maps) {
+      for (uint32_t i0 = 0; i0 < cnt; i0 += 4 * kSliceT) {
+        uint32_t x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t i = i0 + k * kSliceT + threadIdx.x;
+          x[k] = i < cnt ? src[i] : 0u;
+          if (maps && i < cnt) x[k] = (uint32_t)v.g.orig_id[x[k]];
         }
-        if (threadIdx.x == 0) v.vc_cnt[r] = written;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (i0 + k * kSliceT + threadIdx.x >= cnt) continue;
+          if (x[k] < lo) ++below;
+          else if (x[k] - lo < kSliceBits) atomicOr(&s_bm[(x[k] - lo) >> 5], 1u << (x[k] & 31u));
+        }
       }
+    });
+    uint32_t pre;
+    (void)block_exclusive_scan<uint32_t, kSliceT>(below, s_scan, &pre);   // also ends the marking
+    // a wavefront takes kPerWave words, 64 at a time
+    uint32_t cnt = 0;
+    for (int i = 0; i < kPerWave; i += kWave) cnt += __popc(s_bm[wv * kPerWave + i + lane]);
+    uint32_t u;
+    (void)block_exclusive_scan<uint32_t, kSliceT>(cnt, s_scan, &u);
+    uint32_t at = wave_last(wave_inclusive_scan(cnt));   // this wavefront's ids
+    if (lane == 0) s_scan[wv] = at;
+    __syncthreads();
+    at = 0;
+    for (int w = 0; w < wv; ++w) at += s_scan[w];
+    uint32_t* out = (pass == 0 ? v.sort_a : v.sort_b) + v.soff[t] + pre;
+    for (int i = 0; i < kPerWave; i += kWave) {
+      const int w = wv * kPerWave + i + lane;
+      const uint32_t bits = s_bm[w];
+      const uint32_t inc = wave_inclusive_scan((uint32_t)__popc(bits));
+      uint32_t o = at + inc - __popc(bits);
+      for (uint32_t b = bits; b; b &= b - 1) out[o++] = lo + (uint32_t)w * 32 + (uint32_t)(__ffs(b) - 1);
+      at += wave_last(inc);
     }
-    if (v.write_output) {
-      // sum of the arcs' activation levels (the re-ranking weight); integer, so
-      // any summation order gives the same value
-      uint64_t ws = 0;
-      if (pass == 1)
-        for (uint32_t i = threadIdx.x; i < m; i += kBlock) ws += g.act[uniq[i]];
-      ws = block_sum<uint64_t, kBlock>(ws, s_ws);
+    uint2* sl = v.mid_slice + (size_t)li * v.mid_z;
+    if (threadIdx.x == 0) sl[z] = make_uint2(pre, u);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&v.mid[li].done, 1u) == zs[pass] - 1;
+    __syncthreads();
+    if (s_last) {
+      __threadfence();
+      uint32_t carry = 0;
+      for (uint32_t z0 = 0; z0 < zs[pass]; z0 += kSliceT) {
+        const uint32_t i = z0 + threadIdx.x;
+        const uint32_t x = i < zs[pass] ? sl[i].y : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_exclusive_scan<uint32_t, kSliceT>(x, s_scan, &tot);
+        if (i < zs[pass]) sl[i].y = carry + ex;   // ids of the slices before
+        carry += tot;
+      }
       if (threadIdx.x == 0) {
-        const uint32_t off = atomicAdd(pass == 0 ? &v.gst->out_nodes : &v.gst->out_arcs, m);
-        const uint32_t cap = pass == 0 ? v.out_ncap : v.out_acap;
-        if (off + m > cap) atomicOr(&v.gst->overflow, 4);
-        s_off = off;
-        ResultHdr& hd = v.hdr[t];
-        if (pass == 0) {
-          hd.central = v.g.orig_id[v.sel_node[r]];
-          hd.score_c = v.sel_sc[r];
-          hd.score_m = v.sm[r];
-          hd.cg_rank = r;
-          hd.key = v.key[r];
-          hd.node_off = off;
-          hd.n_nodes = m;
-        } else {
-          hd.arc_off = off;
-          hd.n_arcs = m;
-          hd.wsum = (int64_t)ws;
-        }
-      }
-      __syncthreads();
-      const uint32_t off = s_off;
-      const uint32_t cap = pass == 0 ? v.out_ncap : v.out_acap;
-      if (off + m <= cap) {
-        if (pass == 0) {
-          for (uint32_t i = threadIdx.x; i < m; i += kBlock) v.out_nodes[off + i] = (int32_t)uniq[i];
-        } else {
-          for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
-            const uint32_t e = uniq[i];
-            int32_t* o = v.out_arcs + 3 * (size_t)(off + i);
-            o[0] = g.arc_src[e];
-            o[1] = g.col[e];
-            o[2] = g.label[e];
-          }
-        }
+        const uint32_t off = take_output(v, pass, carry);
+        v.mid[li].total = carry;
+        v.mid[li].base = off;
+        put_header(v, t, pass, off, carry, 0);   // k_fin_emit adds the arcs' levels
       }
     }
     __syncthreads();
+  }
+}
+
+// Output of the long lists, 1024 entries per step.
+__global__ __launch_bounds__(kBlock) void k_fin_emit(FinalizeView v) {
+  if (v.gst->mid_lists == 0) return;
+  constexpr uint32_t kChunk = 4 * kBlock;
+  __shared__ uint32_t s_pre[2 * kMaxW], s_scan[kBlock / kWave + 1];
+  __shared__ uint64_t s_ws[kBlock / kWave + 1];
+  const int lists = 2 * min(v.n_res, *v.n_valid);
+  const uint32_t zs[2] = {((uint32_t)v.g.n - 1) / kSliceBits + 1, (v.g.A - 1) / kSliceBits + 1};
+  const uint32_t total = list_items<kBlock>(lists, s_pre, s_scan, [&](int i) {
+    return v.mid[i].n ? (v.mid[i].total + kChunk - 1) / kChunk : 0u;
+  });
+  for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
+    const int li = upper_index<uint32_t>(s_pre, 0, lists, item);
+    const int t = li >> 1, pass = li & 1;
+    const MidList m = v.mid[li];
+    const uint2* sl = v.mid_slice + (size_t)li * v.mid_z;
+    const uint32_t* ids = (pass == 0 ? v.sort_a : v.sort_b) + v.soff[t];
+    const bool fits = (uint64_t)m.base + m.total <= (pass == 0 ? v.out_ncap : v.out_acap);
+    uint64_t ws = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t i = (item - s_pre[li]) * kChunk + k * kBlock + threadIdx.x;
+      if (i >= m.total) continue;
+      // the slice that holds the i-th id (empty slices repeat a prefix)
+      uint32_t a = 0, b = zs[pass];
+      while (b - a > 1) {
+        const uint32_t mid = (a + b) >> 1;
+        if (sl[mid].y <= i) a = mid; else b = mid;
+      }
+      const uint2 x = sl[a];
+      const uint32_t id = ids[x.x + (i - x.y)];
+      if (pass == 1) ws += v.g.act[id];
+      if (fits) put_output(v, pass, m.base + i, id);
+    }
+    if (pass == 1) {
+      ws = block_sum<uint64_t, kBlock>(ws, s_ws);
+      if (threadIdx.x == 0 && ws)
+        atomicAdd((unsigned long long*)&v.hdr[t].wsum, (unsigned long long)ws);
+    }
   }
 }
 
@@ -964,8 +1198,17 @@ void launch_recover(const RecoverView& v, hipStream_t s) {
   }
 }
 
+size_t finalize_slices(int64_t n, int64_t A) {
+  return (size_t)std::max(n, std::max<int64_t>(A, 1)) / kSliceBits + 1;
+}
+
 void launch_finalize(const FinalizeView& v, hipStream_t s) {
-  if (v.n_res > 0) k_finalize<<<dim3(v.n_res, 2), kBlock, 0, s>>>(v);
+  if (v.n_res <= 0) return;
+  k_finalize<<<dim3(v.n_res, v.marginal ? 2 : kRawParts), kBlock, 0, s>>>(v);
+  if (v.marginal) {
+    k_fin_slices<<<256, kSliceT, 0, s>>>(v);
+    k_fin_emit<<<1024, kBlock, 0, s>>>(v);
+  }
 }
 
 // The query's status, its result headers and as much of its output lists as

@@ -98,6 +98,7 @@ struct Lane {
   DevBuf cg_nodes, cg_arcs, cg_cnt;   // CG lists, kept for the marginal phase
   DevBuf hdr, out_nodes, out_arcs, status;
   DevBuf Hq;                          // cohort path: the query's hitting levels, [n_pad][TPq]
+  DevBuf mid;                         // long result lists: MidList records, id slices
   DevBuf bigf, big_bm, big_chunk, big_slot;   // bitmap path of large results
   RecPhase ph[2];                     // [0] CG recovery, [1] RPG recovery + output
   DevBuf lab;                         // labels of the labelled mode, [T * G][n] words
