@@ -343,9 +343,9 @@ int check_graph(Ctx* c, Lane* L) {
   if (c->mode == RAKS_ACT_NODE) {
     launch_node_weight_range(g, P<uint8_t>(c->nw), st, s);
     HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipStreamSynchronize(s));
   }
-  HIP_OK(hipGetLastError());
-  HIP_OK(hipStreamSynchronize(s));
   c->wmin = L->h_status->cmin;
   c->wmax = L->h_status->cmax;
   if (c->A == 0 && c->mode == RAKS_ACT_EDGE) c->wmin = c->wmax = 1;
@@ -398,7 +398,9 @@ int build_view(Ctx* c, Lane* L, AlphaView& v, double alpha) {
   in.row_amax = P<uint8_t>(v.row_amax);
   in.bnd = P<uint32_t>(v.bnd);
   in.n_big = c->n_big;
+  in.n_top = c->n_top;
   in.n_mid = c->n_mid;
+  in.n_wave = c->n_wave;
   in.big_arcs = c->big_arcs;
   // levels never exceed Round(2 * a_bar) (x <= 1 in Eqs. 1-3); one more for
   // the last digit of the quotient at x = 1
@@ -621,9 +623,9 @@ RunView run_view(Lane* L, int kind, int T, DevBuf& H, const QueryPlan& p) {
 __global__ void k_query_reset(Status* st) {
   st->nsel = 0;
   st->sel_ticket = 0;
+  st->mid_lists = 0;
   st->nres = 0;
   st->overflow = 0;
-  st->mid_lists = 0;
   st->out_nodes = 0;
   st->out_arcs = 0;
 }
@@ -868,10 +870,10 @@ int ensure_recovery(Lane* L, const QueryPlan& p) {
   RAKS_TRY(dev_alloc(c, L->sort_a, std::max<uint64_t>(sc, 1) * 4));
   RAKS_TRY(dev_alloc(c, L->sort_b, std::max<uint64_t>(sc, 1) * 4));
   RAKS_TRY(dev_alloc(c, L->hdr, (size_t)std::max(P1.n_res, 1) * sizeof(ResultHdr)));
-  RAKS_TRY(dev_alloc(c, L->bigf, (size_t)std::max({P0.n_res, P1.n_res, 1}) * 4));
-  RAKS_TRY(dev_alloc(c, L->out_nodes, std::max<uint64_t>(P1.out_n, 1) * 4));
   RAKS_TRY(dev_alloc(c, L->mid, 2 * (size_t)std::max(P1.n_res, 1) *
                                     (sizeof(MidList) + finalize_slices(c->n, c->A) * sizeof(uint2))));
+  RAKS_TRY(dev_alloc(c, L->bigf, (size_t)std::max({P0.n_res, P1.n_res, 1}) * 4));
+  RAKS_TRY(dev_alloc(c, L->out_nodes, std::max<uint64_t>(P1.out_n, 1) * 4));
   RAKS_TRY(dev_alloc(c, L->out_arcs, std::max<uint64_t>(P1.out_a, 1) * 12));
   // labels of the labelled mode: [T * G][n] words for the larger phase
   uint64_t lw = 0;
@@ -971,9 +973,9 @@ RecoverView recover_view(Lane* L, int ph, const uint8_t* H, int TP, const int32_
   v.vc_off = P<uint32_t>(L->vc_off);
   v.vc_nodes = P<int32_t>(L->vc_nodes);
   v.dmin = P<uint8_t>(L->dmin);
+  v.vc_cnt = P<uint32_t>(L->vc_cnt);
   v.caps = P<InstCap>(Ph.layout);
   v.hpool = P<uint32_t>(L->hpool);
-  v.vc_cnt = P<uint32_t>(L->vc_cnt);
   v.nl = P<int32_t>(L->nl);
   v.al = P<uint32_t>(L->al);
   v.cnt = P<uint32_t>(Ph.cnt);
@@ -1035,11 +1037,11 @@ FinalizeView finalize_view(Lane* L, int ph, const int32_t* n_valid, int C, const
   v.write_output = ph;
   v.skip_bits = ph == 0 ? 1 : 3;
   v.big = P<uint32_t>(L->bigf);
-  v.big_list = L->ctx->big_list;
-  v.hdr = P<ResultHdr>(L->hdr);
   v.mid_z = (uint32_t)finalize_slices(L->ctx->n, L->ctx->A);
   v.mid = P<MidList>(L->mid);
   v.mid_slice = reinterpret_cast<uint2*>(v.mid + 2 * (size_t)std::max(L->ph[1].n_res, 1));
+  v.big_list = L->ctx->big_list;
+  v.hdr = P<ResultHdr>(L->hdr);
   v.out_nodes = P<int32_t>(L->out_nodes);
   v.out_arcs = P<int32_t>(L->out_arcs);
   v.out_ncap = (uint32_t)std::min<size_t>(L->out_nodes.bytes / 4, UINT32_MAX);
@@ -1055,9 +1057,9 @@ FinalizeView finalize_view(Lane* L, int ph, const int32_t* n_valid, int C, const
 
 // Clears the flags and output counters before a phase is repeated.
 __global__ void k_retry_reset(Status* st) {
+  st->mid_lists = 0;
   st->overflow = 0;
   st->out_nodes = 0;
-  st->mid_lists = 0;
   st->out_arcs = 0;
 }
 
@@ -1742,12 +1744,14 @@ int raks_load_graph(raks_ctx* c, const raks_graph_desc* g) {
     }
     rpi[0] = 0;
     // rows of the traversal copy's size classes (largest first)
-    c->n_big = c->n_mid = 0;
+    c->n_big = c->n_top = c->n_mid = c->n_wave = 0;
     for (int64_t u = 0; u < n; ++u) {
       const uint32_t d = (uint32_t)(g->row_ptr[orig_id[u] + 1] - g->row_ptr[orig_id[u]]);
       rpi[u + 1] = rpi[u] + d;
       c->n_big += d > kBigRow;
+      c->n_top += d > kTopRow;
       c->n_mid += d > kMidRow;
+      c->n_wave += d > kWaveRow;
     }
     c->big_arcs = rpi[c->n_big];
   }

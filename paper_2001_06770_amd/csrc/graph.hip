@@ -17,9 +17,12 @@ namespace raks {
 
 // Number of arcs of row [lo, hi) that share arc e's label: the ends of e's run
 // of that label (labels ascend along a row), found by doubling steps from e.
-// Most runs hold one or two arcs, which the neighbours tell.
+// Most runs hold one arc, which its neighbours tell: both are read at once.
 __device__ inline uint32_t label_run(const uint16_t* label, uint32_t lo, uint32_t hi, uint32_t e,
                                      uint16_t lab) {
+  const uint32_t before = e > lo ? label[e - 1] : 0x10000u;
+  const uint32_t after = e + 1 < hi ? label[e + 1] : 0x10000u;
+  if (before != lab && after != lab) return 1;
   uint32_t first = e, last = e;   // known members of the run
   uint32_t step = 1;
   while (first >= lo + step && label[first - step] == lab) { first -= step; step <<= 1; }
@@ -38,13 +41,12 @@ __device__ inline uint32_t label_run(const uint16_t* label, uint32_t lo, uint32_
 // one search of the smaller of its two rows; both get the sum of the runs of
 // their label around the two positions.  Every arc has a reverse exactly when
 // each searching arc finds one and half of the arcs search.  A workgroup takes
-// tiles of kCheckTile consecutive arcs; the rows that start in a tile mark
+// tiles of consecutive arcs; the rows that start in a tile mark
 // their first arc and a block max-scan gives every arc its row.  The random
 // reads of the searches bound it.  24.7M arcs on 1.5M nodes: 6.9 ms with a
 // search per arc in its target's row (a hub's, mostly) and one of all row
-// starts, 2.4 ms now.
-constexpr int kCheckTile = 1024;
-
+// starts, 2.3 ms now.
+template <int kCheckTile>
 __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_ptr,
                                                             const int32_t* col,
                                                             const uint16_t* label, int32_t n,
@@ -115,20 +117,38 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
     }
     __syncthreads();
   }
-  // wave reductions, then one atomic per wave
+  // One atomic per workgroup and value (they all go to the same three words of
+  // device memory, where they are performed one at a time: a few per wavefront
+  // took 50 us on 126k arcs), and the range only where it widens what is there.
+  __shared__ unsigned long long s_min, s_max;
+  __shared__ uint32_t s_err, s_found;
+  if (threadIdx.x == 0) {
+    s_min = ~0ull;
+    s_max = 0;
+    s_err = 0;
+    s_found = 0;
+  }
+  __syncthreads();
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) {
-    uint64_t a = __shfl_xor(cmin, d, kWave), b = __shfl_xor(cmax, d, kWave);
-    cmin = a < cmin ? a : cmin;
-    cmax = b > cmax ? b : cmax;
+    const uint64_t x = __shfl_xor(cmin, d, kWave), y = __shfl_xor(cmax, d, kWave);
+    cmin = x < cmin ? x : cmin;
+    cmax = y > cmax ? y : cmax;
     err |= __shfl_xor(err, d, kWave);
     found += __shfl_xor(found, d, kWave);
   }
   if (lane_id() == 0) {
-    if (found) atomicAdd((unsigned long long*)&st->pairs, (unsigned long long)found);
-    if (err) atomicOr(&st->err, (int32_t)err);
-    atomicMin((unsigned long long*)&st->cmin, (unsigned long long)cmin);
-    atomicMax((unsigned long long*)&st->cmax, (unsigned long long)cmax);
+    atomicMin(&s_min, (unsigned long long)cmin);
+    atomicMax(&s_max, (unsigned long long)cmax);
+    atomicOr(&s_err, err);
+    atomicAdd(&s_found, found);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s_err) atomicOr(&st->err, (int32_t)s_err);
+    if (s_found) atomicAdd((unsigned long long*)&st->pairs, (unsigned long long)s_found);
+    if (s_min < *(volatile uint64_t*)&st->cmin) atomicMin((unsigned long long*)&st->cmin, s_min);
+    if (s_max > *(volatile uint64_t*)&st->cmax) atomicMax((unsigned long long*)&st->cmax, s_max);
   }
 }
 
@@ -169,19 +189,22 @@ __global__ __launch_bounds__(kBlock) void k_act_node(const uint8_t* nw, int32_t 
 // neighbours and each class gets the split that fills the machine (the order
 // of the arcs of one level within a row is free: no result depends on it):
 //   <= 64 arcs       k_sort_small: a group of 1 to 64 lanes per row, one arc
-//                    per lane, positions from ballots; a workgroup takes 128
+//                    per lane, positions from ballots; a workgroup takes 32
 //                    neighbouring rows, whose arcs are contiguous in the copy,
 //                    and writes their level-table entries as whole lines;
-//   <= kBigRow arcs  k_sort_mid: one wavefront per row, two passes;
+//   <= kMidRow arcs  k_sort_row<64>: a wavefront per row, its arcs in registers;
+//   <= kTopRow arcs  k_sort_row<256>: a workgroup per row, likewise;
+//   <= kBigRow arcs  k_sort_row<1024>: a workgroup of 1024 threads per row;
 //   larger           k_big_hist, k_big_prefix, k_big_scatter: tiles of
 //                    kBigTile arcs over all workgroups, so that a hub's row is
-//                    not one wavefront's work.
-// Memory traffic bounds it: per arc 8 bytes read and 10 written plus the
-// gathers of the target's id and the count's level.  On 2M nodes and 40M arcs
-// (largest row 1.3M arcs) the three classes take 0.25, 0.18 and 0.22 ms; with
-// one wavefront per row for every row it was 17.0 ms, all but about 1 ms of it
-// in the largest row, plus 0.08 ms for the separate pass over the levels.
-constexpr int kSmallRows = 128;     // rows per workgroup of k_sort_small
+//                    not one workgroup's work.
+// Every row but the hubs' is one round of loads, which is what a small graph's
+// load waits for; memory traffic bounds a large one's: per arc 8 bytes read and
+// 10 written plus the gathers of the target's id and the count's level.  On 2M
+// nodes and 40M arcs (largest row 1.3M arcs) the levels and the copy take 0.72
+// ms; with one wavefront per row for every row it was 17.0 ms, all but about
+// 1 ms of it in the largest row, plus 0.08 ms for a pass over the levels.
+constexpr int kSmallRows = 32;      // rows per workgroup of k_sort_small
 
 struct SortView {
   DevGraphView g;
@@ -195,7 +218,8 @@ struct SortView {
   uint32_t* eid_s;
   uint8_t* row_amax;
   uint32_t* bnd;
-  int32_t n_big, n_mid;   // rows [0, n_big) exceed kBigRow arcs, [n_big, n_mid) exceed 64
+  int32_t n_big, n_top, n_mid, n_wave;   // rows below these exceed kBigRow, kTopRow, kMidRow,
+                                         // kWaveRow arcs
   uint32_t big_arcs;      // arcs of the big rows
   uint32_t* cursor;       // [n_big][nlev]
   int32_t nlev;           // levels are below this
@@ -257,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_small(SortView v) {
   __shared__ uint32_t s_rs[kSmallRows + 1], s_ro[kSmallRows], s_am[kSmallRows];
   __shared__ uint32_t s_cnt[16][kSmallRows];   // arcs of each level below nbnd
   const DevGraphView& g = v.g;
-  const int32_t u0 = v.n_mid + (int32_t)blockIdx.x * kSmallRows;
+  const int32_t u0 = v.n_wave + (int32_t)blockIdx.x * kSmallRows;
   const int rows = min(kSmallRows, g.n - u0);
   for (int i = threadIdx.x; i <= rows; i += kBlock) {
     s_rs[i] = g.row_ptr[u0 + i];
@@ -305,58 +329,64 @@ __device__ inline uint32_t wave_level_rank(uint32_t* hist, bool live, uint32_t a
   return rank;
 }
 
-__global__ __launch_bounds__(kBlock) void k_sort_mid(SortView v) {
-  __shared__ uint32_t s_hist[kBlock / kWave][256];
-  uint32_t* hist = s_hist[wave_id()];
-  const int lane = lane_id();
+// One row per NT threads (a wavefront or a workgroup), its arcs in registers.
+template <int NT, int ROW>
+__global__ __launch_bounds__(NT < kBlock ? kBlock : NT) void k_sort_row(SortView v, int32_t first,
+                                                                       int32_t end) {
+  constexpr int IPT = ROW / NT, kRows = NT < kBlock ? kBlock / NT : 1;
+  __shared__ uint32_t s_hist[kRows][256], s_max[kRows];
   const DevGraphView& g = v.g;
-  const int32_t u = v.n_big + (int32_t)blockIdx.x * (kBlock / kWave) + wave_id();
-  if (u >= v.n_mid) return;
-  const uint32_t rs_o = g.row_ptr_o[g.orig_id[u]];
-  const uint32_t rs = g.row_ptr[u], d = g.row_ptr[u + 1] - rs;
-  for (int b = lane; b < 256; b += kWave) hist[b] = 0;
-  __builtin_amdgcn_wave_barrier();
-  uint32_t amax = 0;
-  for (uint32_t k0 = 0; k0 < d; k0 += kWave) {
-    const uint32_t k = k0 + lane;
-    uint32_t a = 0;
-    if (k < d) {
-      a = arc_level(v, rs_o + k);
-      v.act[rs_o + k] = (uint8_t)a;
-      amax = a > amax ? a : amax;
-    }
-    (void)wave_level_rank(hist, k < d, a);
+  const int32_t u = first + (int32_t)blockIdx.x * kRows + (int)threadIdx.x / NT;
+  const int q = threadIdx.x % NT;
+  uint32_t* hist = s_hist[threadIdx.x / NT];
+  const bool row = u < end;
+  const uint32_t rs_o = row ? g.row_ptr_o[g.orig_id[u]] : 0u;
+  const uint32_t rs = row ? g.row_ptr[u] : 0u, d = row ? g.row_ptr[u + 1] - rs : 0u;
+  for (int i = q; i < 256; i += NT) hist[i] = 0;
+  if (q == 0) s_max[threadIdx.x / NT] = 0;
+  __syncthreads();
+  uint32_t a[IPT], rank[IPT], amax = 0;
+  int32_t to[IPT];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const uint32_t k = i * NT + q;
+    a[i] = k < d ? arc_level(v, rs_o + k) : 0u;
+    to[i] = k < d ? g.int_id[g.col[rs_o + k]] : 0;
+    amax = a[i] > amax ? a[i] : amax;
   }
 #pragma unroll
-  for (int s = kWave / 2; s > 0; s >>= 1) {
-    const uint32_t o = __shfl_xor(amax, s, kWave);
-    amax = o > amax ? o : amax;
+  for (int i = 0; i < IPT; ++i) {
+    const uint32_t k = i * NT + q;
+    if (k < d) v.act[rs_o + k] = (uint8_t)a[i];
+    rank[i] = wave_level_rank(hist, k < d, a[i]);
   }
-  __builtin_amdgcn_wave_barrier();
-  // exclusive prefix over the 256 bins: lane owns bins 4*lane .. 4*lane+3
-  const uint32_t c0 = hist[4 * lane], c1 = hist[4 * lane + 1], c2 = hist[4 * lane + 2],
-                 c3 = hist[4 * lane + 3];
-  const uint32_t tot = c0 + c1 + c2 + c3;
-  const uint32_t ex = wave_inclusive_scan(tot) - tot;
-  hist[4 * lane] = ex;
-  hist[4 * lane + 1] = ex + c0;
-  hist[4 * lane + 2] = ex + c0 + c1;
-  hist[4 * lane + 3] = ex + c0 + c1 + c2;
-  __builtin_amdgcn_wave_barrier();
+  amax = wave_last(wave_scan_op(amax, [](uint32_t x, uint32_t y) { return x > y ? x : y; }));
+  if (lane_id() == 0) atomicMax(&s_max[threadIdx.x / NT], amax);
+  __syncthreads();
+  // level counts to level starts, by the row's first wavefront: lane owns bins
+  // 4 * lane .. 4 * lane + 3
+  if (q < kWave) {
+    const uint32_t c0 = hist[4 * q], c1 = hist[4 * q + 1], c2 = hist[4 * q + 2], c3 = hist[4 * q + 3];
+    const uint32_t tot = c0 + c1 + c2 + c3;
+    const uint32_t ex = wave_inclusive_scan(tot) - tot;
+    hist[4 * q] = ex;
+    hist[4 * q + 1] = ex + c0;
+    hist[4 * q + 2] = ex + c0 + c1;
+    hist[4 * q + 3] = ex + c0 + c1 + c2;
+  }
+  __syncthreads();
   // arcs with level <= l = start of level l + 1
-  if (lane < g.nbnd) v.bnd[(size_t)lane * g.n + u] = hist[lane + 1];
-  __builtin_amdgcn_wave_barrier();
-  for (uint32_t k0 = 0; k0 < d; k0 += kWave) {
-    const uint32_t k = k0 + lane;
-    const uint32_t a = k < d ? v.act[rs_o + k] : 0u;   // written by this thread
-    const uint32_t p = rs + wave_level_rank(hist, k < d, a);
-    if (k < d) {
-      v.col_s[p] = g.int_id[g.col[rs_o + k]];
-      v.act_s[p] = (uint8_t)a;
-      v.eid_s[p] = rs_o + k;
-    }
+  if (row && q < g.nbnd) v.bnd[(size_t)q * g.n + u] = hist[q + 1];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const uint32_t k = i * NT + q;
+    if (k >= d) continue;
+    const uint32_t p = rs + hist[a[i]] + rank[i];
+    v.col_s[p] = to[i];
+    v.act_s[p] = (uint8_t)a[i];
+    v.eid_s[p] = rs_o + k;
   }
-  if (lane == 0) v.row_amax[u] = (uint8_t)amax;
+  if (row && q == 0) v.row_amax[u] = (uint8_t)s_max[threadIdx.x / NT];
 }
 
 // Big rows: workgroup t takes arcs [t * kBigTile, (t + 1) * kBigTile) of the
@@ -480,7 +510,9 @@ void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s)
   v.row_amax = in.row_amax;
   v.bnd = in.bnd;
   v.n_big = in.n_big;
+  v.n_top = in.n_top;
   v.n_mid = in.n_mid;
+  v.n_wave = in.n_wave;
   v.big_arcs = in.big_arcs;
   v.cursor = in.cursor;
   v.nlev = in.nlev;
@@ -488,14 +520,18 @@ void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s)
   // other rows fill afterwards
   if (v.n_big > 0) {
     const unsigned tiles = (v.big_arcs + kBigTile - 1) / kBigTile;
-    k_big_zero<<<64, kBlock, 0, s>>>(v);
+    k_big_zero<<<std::min(64, v.n_big), kBlock, 0, s>>>(v);
     k_big_hist<<<tiles, kBlock, 0, s>>>(v);
     k_big_prefix<<<(v.n_big + kBlock - 1) / kBlock, kBlock, 0, s>>>(v);
     k_big_scatter<<<tiles, kBlock, 0, s>>>(v);
   }
-  const int mid = v.n_mid - v.n_big, small = g.n - v.n_mid;
+  const int top = v.n_top - v.n_big, mid = v.n_mid - v.n_top, wave = v.n_wave - v.n_mid,
+            small = g.n - v.n_wave;
   constexpr int kRows = kBlock / kWave;
-  if (mid > 0) k_sort_mid<<<(mid + kRows - 1) / kRows, kBlock, 0, s>>>(v);
+  if (top > 0) k_sort_row<1024, kBigRow><<<top, 1024, 0, s>>>(v, v.n_big, v.n_top);
+  if (mid > 0) k_sort_row<kBlock, kTopRow><<<mid, kBlock, 0, s>>>(v, v.n_top, v.n_mid);
+  if (wave > 0)
+    k_sort_row<kWave, kMidRow><<<(wave + kRows - 1) / kRows, kBlock, 0, s>>>(v, v.n_mid, v.n_wave);
   if (small > 0) k_sort_small<<<(small + kSmallRows - 1) / kSmallRows, kBlock, 0, s>>>(v);
 }
 
@@ -517,8 +553,13 @@ static unsigned grid_for(uint64_t items, unsigned cap = 8192) {
 void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc_src, uint32_t* rev,
                             Status* st, hipStream_t s) {
   k_status_reset_minmax<<<1, 1, 0, s>>>(st);
-  if (g.A > 0)
-    k_check_and_count<<<grid_for((g.A - 1) / 4 + 1), kBlock, 0, s>>>(
+  // small graphs wait for one arc's chain of reads per thread, larger ones
+  // spread a tile's row search over four
+  if (g.A > 0 && g.A <= (1u << 21))
+    k_check_and_count<kBlock><<<grid_for(g.A), kBlock, 0, s>>>(
+        g.row_ptr_o, g.col, g.label, g.n, g.A, c_tmp, arc_src, rev, st);
+  else if (g.A > 0)
+    k_check_and_count<4 * kBlock><<<grid_for((g.A - 1) / 4 + 1), kBlock, 0, s>>>(
         g.row_ptr_o, g.col, g.label, g.n, g.A, c_tmp, arc_src, rev, st);
 }
 

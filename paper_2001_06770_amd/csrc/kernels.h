@@ -269,9 +269,10 @@ void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc
                             Status* st,
                             hipStream_t s);
 // Size classes of the traversal copy's rows (internal rows are in order of
-// degree): rows above kMidRow arcs take a wavefront each, rows above kBigRow
-// are split into tiles of kBigTile arcs over many workgroups.
-constexpr uint32_t kMidRow = 64, kBigRow = 2048, kBigTile = 4096;
+// degree): rows above 64 arcs take a wavefront each, above kMidRow a workgroup,
+// above kTopRow a large one, above kBigRow they are split into tiles of kBigTile
+// arcs.
+constexpr uint32_t kWaveRow = 64, kMidRow = 256, kTopRow = 4096, kBigRow = 16384, kBigTile = 4096;
 // Levels and traversal copy: inputs (label counts and the host's table, or the
 // nodes' levels by original id) and outputs (see DevGraphView).
 struct SortInput {
@@ -285,7 +286,8 @@ struct SortInput {
   uint32_t* eid_s;
   uint8_t* row_amax;
   uint32_t* bnd;
-  int32_t n_big, n_mid;     // rows with more than kBigRow / kMidRow arcs
+  int32_t n_big, n_top, n_mid, n_wave;   // rows with more than kBigRow / kTopRow / kMidRow /
+                                         // kWaveRow arcs
   uint32_t big_arcs;        // arcs of the first n_big rows
   uint32_t* cursor;         // scratch [n_big][nlev], may be eid_s + big_arcs
   int32_t nlev;             // levels are below this
@@ -321,9 +323,9 @@ void launch_rank(const RankView& v, hipStream_t s);
 // Re-ranking of equal scores by the arcs' level sum; keeps the first k.
 void launch_rerank(ResultHdr* hdr, Status* gst, int32_t k, hipStream_t s);
 void launch_recover(const RecoverView& v, hipStream_t s);   // all layers of one phase
+size_t finalize_slices(int64_t n, int64_t A);   // id slices of the longest list
 void launch_finalize(const FinalizeView& v, hipStream_t s);
 
-size_t finalize_slices(int64_t n, int64_t A);   // id slices of the longest list
 // Results to pinned host memory (device addresses of the host buffers).
 struct CollectView {
   const Status* st;

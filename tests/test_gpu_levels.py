@@ -15,14 +15,14 @@ import synth
 pytestmark = pytest.mark.gpu
 
 DEGREES = (1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 4095,
-           4096, 4097, 9001)
+           255, 256, 257, 4096, 4097, 8193, 9001, 16384, 16385, 17000)
 
 
 def hub_graph(seed):
     """One hub per degree, its edges going to a shared pool of leaves and to
     the other hubs' leaves; labels of very different counts."""
     rng = np.random.default_rng(seed)
-    hubs, leaves = len(DEGREES), 10_000
+    hubs, leaves = len(DEGREES), 18_000
     n = hubs + leaves + 7   # some isolated nodes
     edges = set()
     for h, d in enumerate(DEGREES):
