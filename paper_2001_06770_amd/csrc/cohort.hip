@@ -899,95 +899,154 @@ __global__ void k_co_post_init(const CoSlot* slot, Status* gst) {
   gst->run[1] = b;
 }
 
-// Counters of one run at one node from its final hitting levels h[0..T)
-// (entries above the run's end level L are not part of the run).  The node is
-// a frontier at the levels where a keyword reached it, and at every level l in
+// The work counters of both runs at every node, from its final hitting levels
+// (entries above a run's end level L are not part of the run).  The node is a
+// frontier at the levels where a keyword reached it, and at every level l in
 // (hmin, U] with U = min(L, largest arc level, the level its row became
 // complete when the run blocks); at each such level below L where it is not
 // blocked it expands: its whole row is scanned (e_arc), once per keyword with
 // h <= l (e_alg), and its arcs of level <= l pass the gate.
-struct RunCnt {
-  uint64_t fr, ea, eg, gp, hw;
-};
+//
+// In the same pass over the rows the query's columns are copied out and reset.
+// It runs on the query's lane stream while the next levels run: the level
+// kernels may write other columns of the same rows, so the reset stores cover
+// the query's own bytes alone, in the widest stores that lie within them.
+//
+// Memory traffic bounds it: per node the row, its copy and the reset, 8 bytes
+// of row start and largest level, and one table entry per level at which the
+// node expands.  The columns stay in NW registers as bytes and a level is
+// compared with all of them at once, so no array is indexed by a variable (with
+// arrays and a sorted list of the levels in scratch memory a query on 2M nodes
+// took @FIN0@ us, on 50M nodes 7.9 ms; now @FIN1@ us and @FIN2@ ms).  512
+// workgroups at most, two per CU: each ends with ten additions to the same words,
+// which device memory performs one at a time.
+constexpr int kFinT = 512;
 
-__device__ inline void run_counts(const uint8_t* h, int T, int L, bool blk, const DevGraphView& g,
-                                  int32_t v, uint32_t rs, uint32_t d, uint32_t amax, RunCnt& o) {
-  int vals[kMaxKw];
-  int nv = 0;
-  bool complete = true;
-  for (int j = 0; j < T; ++j) {
-    const int x = h[j];
-    if (x == kInf || x > L) { complete = false; continue; }
-    // insertion into the sorted list
-    int p = nv++;
-    while (p > 0 && vals[p - 1] > x) { vals[p] = vals[p - 1]; --p; }
-    vals[p] = x;
-    if (x >= 1) ++o.hw;
-  }
-  if (nv == 0) return;
-  const int hmin = vals[0];
-  const int done = complete ? vals[nv - 1] : INT_MAX;
-  const int U = min(min(L, (int)amax), blk ? done : INT_MAX);
-  int p = 0;   // values <= l: vals[0..p)
-  for (int l = hmin; l <= L; ++l) {
-    bool point = false;
-    while (p < nv && vals[p] <= l) { point |= vals[p] == l; ++p; }
-    const bool inF = point || (l > hmin && l <= U);
-    if (!inF) {
-      if (l > U && p == nv) break;   // no value left above l and no retention
-      continue;
+template <int NW>
+__global__ __launch_bounds__(kFinT) void k_co_finish(CoFinishView fv, DevGraphView g) {
+  __shared__ uint64_t s_sum[(kFinT / kWave + 1) * 10];
+  const int Lc = fv.slot->c_end, Lm = fv.slot->m_end;
+  const int lend = max(Lc, Lm), C = fv.C, M = fv.M, T = C + M, sh = fv.c0 * 8;
+  const bool blk = fv.m_block != 0;
+  // bytes of the copy beyond the query's columns, the flag bits of either run's
+  // columns, the query's own bytes of the row in place
+  uint32_t pad[NW], fc[NW], fm[NW], own[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t o = 0, p = 0, a = 0, b = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = 4 * k + i;
+      if (j >= fv.c0 && j < fv.c0 + T) o |= 0xFFu << (8 * i);
+      if (j >= T) p |= 0xFFu << (8 * i);
+      else if (j >= C) b |= 0x80u << (8 * i);
+      else a |= 0x80u << (8 * i);
     }
-    ++o.fr;
-    if (l < L && !(blk && done <= l)) {
-      o.ea += d;
-      o.eg += (uint64_t)d * p;
-      o.gp += cnt_le(g, v, l, rs, d, amax);
-    }
+    own[k] = o;
+    if (k < NW) { pad[k] = p; fc[k] = a; fm[k] = b; }
   }
-}
-
-// One pass over the query's rows: counters, copy-out and reset.  Runs on the
-// query's lane stream while the next levels run: the level kernels may write
-// other columns of the same rows, so the reset stores only the query's own
-// bytes (and only those that are not INF already).
-__global__ __launch_bounds__(kBlock) void k_co_finish(CoFinishView fv, DevGraphView g) {
-  __shared__ uint64_t s_multi[(kBlock / kWave + 1) * 10];
-  const CoSlot s = *fv.slot;
-  const int Lc = s.c_end, Lm = s.m_end;
-  const int T = fv.C + fv.M;
   uint64_t acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < fv.n_pad;
-       v += (int64_t)gridDim.x * kBlock) {
+  for (int64_t v = (int64_t)blockIdx.x * kFinT + threadIdx.x; v < fv.n_pad;
+       v += (int64_t)gridDim.x * kFinT) {
     uint4* rowp = reinterpret_cast<uint4*>(fv.seg) + v;
     const uint4 row = *rowp;
-    uint8_t b[16], out[16];
-    __builtin_memcpy(b, &row, 16);
+    uint64_t lo = row.x | (uint64_t)row.y << 32, hi = row.z | (uint64_t)row.w << 32;
+    if (sh >= 64) {
+      lo = hi >> (sh - 64);
+    } else if (sh > 0) {
+      lo = lo >> sh | hi << (64 - sh);
+      hi >>= sh;
+    }
+    const uint32_t all[4] = {(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi,
+                             (uint32_t)(hi >> 32)};
+    uint32_t h[NW], some = 0xFFFFFFFFu;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) out[j] = kInf;
-    for (int j = 0; j < T; ++j) out[j] = b[fv.c0 + j];
-    if (v < g.n && ((row.x & row.y & row.z & row.w) != 0xFFFFFFFFu)) {
-      const uint32_t rs = g.row_ptr[v], d = g.row_ptr[v + 1] - rs, amax = g.row_amax[v];
-      RunCnt a = {0, 0, 0, 0, 0};
-      run_counts(out, fv.C, Lc, true, g, (int32_t)v, rs, d, amax, a);
-      acc[0] += a.fr; acc[1] += a.ea; acc[2] += a.eg; acc[3] += a.gp; acc[4] += a.hw;
-      if (Lm >= 0) {
-        RunCnt c = {0, 0, 0, 0, 0};
-        run_counts(out + fv.C, fv.M, Lm, fv.m_block != 0, g, (int32_t)v, rs, d, amax, c);
-        acc[5] += c.fr; acc[6] += c.ea; acc[7] += c.eg; acc[8] += c.gp; acc[9] += c.hw;
+    for (int k = 0; k < NW; ++k) {
+      h[k] = all[k] | pad[k];
+      some &= h[k];
+    }
+    if (NW == 1) reinterpret_cast<uint32_t*>(fv.Hq)[v] = h[0];
+    else if (NW == 2) reinterpret_cast<uint2*>(fv.Hq)[v] = make_uint2(h[0], h[NW > 1 ? 1 : 0]);
+    else
+      reinterpret_cast<uint4*>(fv.Hq)[v] =
+          make_uint4(h[0], h[NW > 1 ? 1 : 0], h[NW > 2 ? 2 : 0], h[NW > 2 ? 3 : 0]);
+    if (some == 0xFFFFFFFFu) continue;   // the query never reached the node
+    // reset
+    uint8_t* rb = reinterpret_cast<uint8_t*>(rowp);
+    const uint32_t was[4] = {row.x, row.y, row.z, row.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (own[k] == 0xFFFFFFFFu) {
+        if (was[k] != 0xFFFFFFFFu) reinterpret_cast<uint32_t*>(rb)[k] = 0xFFFFFFFFu;
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t o = own[k] >> (16 * i) & 0xFFFFu, w = was[k] >> (16 * i) & 0xFFFFu;
+        if (o == 0xFFFFu) {
+          if (w != 0xFFFFu) reinterpret_cast<uint16_t*>(rb)[2 * k + i] = 0xFFFFu;
+        } else if (o == 0xFFu) {
+          if ((w & 0xFFu) != 0xFFu) rb[4 * k + 2 * i] = 0xFFu;
+        } else if (o == 0xFF00u) {
+          if (w >> 8 != 0xFFu) rb[4 * k + 2 * i + 1] = 0xFFu;
+        }
       }
     }
-    uint4 o;
-    __builtin_memcpy(&o, out, 16);
-    if (fv.TPq == 4) reinterpret_cast<uint32_t*>(fv.Hq)[v] = o.x;
-    else if (fv.TPq == 8) reinterpret_cast<uint2*>(fv.Hq)[v] = make_uint2(o.x, o.y);
-    else reinterpret_cast<uint4*>(fv.Hq)[v] = o;
-    uint8_t* rb = reinterpret_cast<uint8_t*>(rowp);
-    for (int j = 0; j < T; ++j)
-      if (out[j] != kInf) rb[fv.c0 + j] = kInf;
+    if (v >= g.n) continue;
+    // counters: 7-bit compares (levels stay below 127, INF reads as 127)
+    const uint32_t rs = g.row_ptr[v], d = g.row_ptr[v + 1] - rs;
+    const int amax = g.row_amax[v];
+    int nf = 0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      h[k] &= 0x7F7F7F7Fu;
+      nf += __popc((0xFEFEFEFEu - h[k]) & (fc[k] | fm[k]));
+    }
+    int pc = 0, pm = 0;                  // levels below l of either run
+    uint32_t xc = 0, xm = 0, kc = 0, km = 0;   // expansions, and keywords expanded
+    for (int l = 0; l <= lend; ++l) {
+      int nc = 0, nm = 0;                // levels of at most l
+      const uint32_t lv = 0x80808080u + 0x01010101u * (uint32_t)l;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        const uint32_t le = lv - h[k];
+        nc += __popc(le & fc[k]);
+        nm += __popc(le & fm[k]);
+      }
+      bool ec = false, em = false;
+      if (l <= Lc) {
+        if (nc > pc || (pc > 0 && l <= amax && pc != C)) {
+          ++acc[0];
+          ec = l < Lc && nc != C;
+        }
+        if (l > 0) acc[4] += nc - pc;
+      }
+      if (l <= Lm) {
+        if (nm > pm || (pm > 0 && l <= amax && !(blk && pm == M))) {
+          ++acc[5];
+          em = l < Lm && !(blk && nm == M);
+        }
+        if (l > 0) acc[9] += nm - pm;
+      }
+      if (ec || em) {
+        const uint32_t gate = cnt_le(g, (int32_t)v, l, rs, d, (uint32_t)amax);
+        if (ec) { ++xc; kc += nc; acc[3] += gate; }
+        if (em) { ++xm; km += nm; acc[8] += gate; }
+      }
+      pc = nc;
+      pm = nm;
+      // no level above l is left and the node is no longer held
+      if (nc + nm == nf &&
+          (l >= amax || ((nc == 0 || nc == C) && (nm == 0 || (blk && nm == M)))))
+        break;
+    }
+    acc[1] += (uint64_t)d * xc;
+    acc[2] += (uint64_t)d * kc;
+    acc[6] += (uint64_t)d * xm;
+    acc[7] += (uint64_t)d * km;
   }
-  uint64_t tot[10];
-  block_exclusive_scan_multi<10, kBlock>(acc, tot, s_multi);
-  if (threadIdx.x < 10 && tot[threadIdx.x]) {
+  block_totals<10, kFinT>(acc, s_sum);
+  if (threadIdx.x < 10 && s_sum[threadIdx.x]) {
     const int k = threadIdx.x;
     RunStatus& rs = fv.gst->run[k / 5];
     unsigned long long* dst = nullptr;
@@ -998,7 +1057,7 @@ __global__ __launch_bounds__(kBlock) void k_co_finish(CoFinishView fv, DevGraphV
       case 3: dst = reinterpret_cast<unsigned long long*>(&rs.gate_pass); break;
       default: dst = reinterpret_cast<unsigned long long*>(&rs.h_writes); break;
     }
-    atomicAdd(dst, (unsigned long long)tot[k]);
+    atomicAdd(dst, (unsigned long long)s_sum[k]);
   }
 }
 
@@ -1077,8 +1136,11 @@ void launch_co_rpg_final(const CohortView& v, int q, hipStream_t s) {
 
 void launch_co_finish(const CoFinishView& fv, const DevGraphView& g, hipStream_t s) {
   k_co_post_init<<<1, 1, 0, s>>>(fv.slot, fv.gst);
-  const unsigned grid = (unsigned)std::min<int64_t>(8192, ((int64_t)fv.n_pad + kBlock - 1) / kBlock);
-  k_co_finish<<<std::max(1u, grid), kBlock, 0, s>>>(fv, g);
+  const unsigned grid = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>(768, ((int64_t)fv.n_pad + kFinT - 1) / kFinT));
+  if (fv.TPq == 4) k_co_finish<1><<<grid, kFinT, 0, s>>>(fv, g);
+  else if (fv.TPq == 8) k_co_finish<2><<<grid, kFinT, 0, s>>>(fv, g);
+  else k_co_finish<4><<<grid, kFinT, 0, s>>>(fv, g);
 }
 
 }  // namespace raks
