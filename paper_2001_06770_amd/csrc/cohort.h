@@ -160,9 +160,11 @@ void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int
                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // CG selection input of slot q (three launches), then the selection kernel
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s);
-// After slot q's CG recovery: V_C ready unless a recovery capacity ran out
+// After slot q's CG recovery: its outcome to the host
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,
                        hipStream_t s);
+// In the level loop's stream: slot q's V_C is ready
+void launch_co_cg_ready(const CohortView& v, int q, const Status* gst, hipStream_t s);
 // Final marginal decision (Theorem 4 replayed up to the exploration's end)
 void launch_co_rpg_final(const CohortView& v, int q, hipStream_t s);
 // D_j minima over V_C for every slot whose marginal run is checked (q < 0), or

@@ -799,23 +799,22 @@ __global__ __launch_bounds__(kBlock) void k_co_cand_write(CoCandView cv, int32_t
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_co_cg_done(CohortView v, int q, const Status* gst,
-                                                       uint64_t seq) {
-  const int32_t ovf = gst->overflow & (1 | kOvfBig0);
-  const int32_t nsel = gst->nsel;
-  // the D_j minima of the new V_C lists start at INF
+// The outcome of slot q's CG stage, for the host.
+__global__ void k_co_cg_done(CohortView v, int q, const Status* gst, uint64_t seq) {
+  v.mirror->cg_ovf[q] = gst->overflow & (1 | kOvfBig0);
+  v.mirror->cg_nsel[q] = gst->nsel;
+  __threadfence_system();
+  *reinterpret_cast<volatile uint64_t*>(&v.mirror->cg_seq[q]) = seq;
+}
+
+// In the level loop's stream, after a CG stage that ran out of nothing: the
+// slot's V_C lists count from the next level on, with D_j minima of INF.
+__global__ __launch_bounds__(kBlock) void k_co_cg_ready(CohortView v, int q, const Status* gst) {
   uint32_t* dm = v.dmin + (size_t)q * kMaxW * kMaxKw;
   for (int i = threadIdx.x; i < kMaxW * kMaxKw; i += kBlock) dm[i] = kInf;
-  __syncthreads();
   if (threadIdx.x == 0) {
-    if (!ovf) {
-      v.slots[q].nsel = nsel;
-      v.slots[q].vc_ready = 1;
-    }
-    v.mirror->cg_ovf[q] = ovf;
-    v.mirror->cg_nsel[q] = nsel;
-    __threadfence_system();
-    *reinterpret_cast<volatile uint64_t*>(&v.mirror->cg_seq[q]) = seq;
+    v.slots[q].nsel = gst->nsel;
+    v.slots[q].vc_ready = 1;
   }
 }
 
@@ -917,7 +916,7 @@ __global__ void k_co_post_init(const CoSlot* slot, Status* gst) {
 // node expands.  The columns stay in NW registers as bytes and a level is
 // compared with all of them at once, so no array is indexed by a variable (with
 // arrays and a sorted list of the levels in scratch memory a query on 2M nodes
-// took @FIN0@ us, on 50M nodes 7.9 ms; now @FIN1@ us and @FIN2@ ms).  512
+// took 248 us, on 50M nodes 7.9 ms; now 75 us and 3.0 ms, beside the level loop).  512
 // workgroups at most, two per CU: each ends with ten additions to the same words,
 // which device memory performs one at a time.
 constexpr int kFinT = 512;
@@ -1123,7 +1122,11 @@ void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s) {
 
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,
                        hipStream_t s) {
-  k_co_cg_done<<<1, kBlock, 0, s>>>(v, q, gst, seq);
+  k_co_cg_done<<<1, 1, 0, s>>>(v, q, gst, seq);
+}
+
+void launch_co_cg_ready(const CohortView& v, int q, const Status* gst, hipStream_t s) {
+  k_co_cg_ready<<<1, kBlock, 0, s>>>(v, q, gst);
 }
 
 void launch_co_dmin(const CohortView& v, int q, int grid, hipStream_t s) {
