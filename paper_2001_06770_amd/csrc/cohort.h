@@ -124,12 +124,13 @@ struct CohortView {
 
 // Candidate keys of one slot's central run (CG selection after the run).
 struct CoCandView {
-  const uint8_t* Hc;             // segment base + c0 (stride 16)
+  const uint8_t* seg;            // the query's segment [n_pad][16]
+  int32_t c0;                    // its first central column
   int32_t C, end;                // central keywords, end level of the central run
-  uint32_t* cnt;                 // [nblocks] last-level candidates per workgroup
-  uint32_t* off;                 // [nblocks] their offsets
-  uint32_t* cursor;              // [2]: earlier-level candidates placed / counted
-  uint64_t* cand;                // keys: earlier levels first, then the last level in node order
+  uint32_t* cnt;                 // [nblocks] last-level candidates per scan workgroup
+  uint64_t* cand;                // their keys, at each scan workgroup's nodes
+  uint32_t* cursor;              // [1] earlier-level candidates placed; 0 between stages
+  uint64_t* early;               // [kMaxW] keys of earlier levels (fewer than w), in any order
   RunStatus* st;                 // receives ncand_total / ncand_level for the selection
   const int32_t* orig_id;        // internal id -> original id (the keys' node ids)
 };
@@ -158,7 +159,7 @@ void launch_co_control(const CohortView& v, int level, uint64_t seq, hipStream_t
 // tile: examined arcs per expansion tile (512, 1024 or 2048)
 void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int grid, int tile,
                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// CG selection input of slot q (three launches), then the selection kernel
+// CG selection input of slot q (two launches)
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s);
 // After slot q's CG recovery: its outcome to the host
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,

@@ -103,75 +103,52 @@ struct SlotCfg {
 };
 
 struct CoCfg {
-  int32_t nslot;
-  uint32_t seg_mask;               // segments with a running run
   int32_t first[kCoSegs + 1];      // slots of segment s: sl[first[s] .. first[s+1])
-  SlotCfg sl[kCoSlots];
+  SlotCfg sl[kCoSlots];            // slots with a running run
   uint32_t lvw[kCoSegs][4];        // per-column local level (127 where no run expands)
   unsigned long long run;          // columns of running runs
 };
 
-// The fields of a slot that the level kernels use.
-struct SlotLite {
-  int32_t on, seg, c0, C, M, start, c_run, m_run, m_block;
-};
-
-// Loads the slot table, one slot per thread (threads 0..kCoSlots-1).
-__device__ inline void load_lite(const CohortView& v, SlotLite* lite) {
+// Built by the first wavefront, a slot per lane (every workgroup builds its
+// own: what the last control step and the admissions since have left; one
+// thread walking over the slots took longer than the scan of 2M nodes itself).
+__device__ inline void build_cfg(const CohortView& v, int level, CoCfg& cfg) {
   const int q = threadIdx.x;
-  if (q < kCoSlots) {
-    const CoSlot& s = v.slots[q];
-    SlotLite x;
-    x.on = s.active && (s.c_run || s.m_run);
-    x.seg = s.seg; x.c0 = s.c0; x.C = s.C; x.M = s.M; x.start = s.start;
-    x.c_run = s.c_run; x.m_run = s.m_run; x.m_block = s.m_block;
-    lite[q] = x;
+  if (q < kWave) {
+    if (q < kCoSegs * 4) (&cfg.lvw[0][0])[q] = 0x7F7F7F7Fu;
+    if (q == 0) cfg.run = 0;
+    SlotCfg c = {};
+    bool on = false;
+    int c0 = 0, T = 0;
+    if (q < kCoSlots) {
+      const CoSlot& s = v.slots[q];
+      on = s.active && (s.c_run || s.m_run);
+      c0 = s.c0;
+      T = s.C + s.M;
+      c.q = (uint8_t)q;
+      c.seg = (uint8_t)s.seg;
+      c.lq = (uint8_t)(level - s.start);
+      c.blk_m = (uint8_t)s.m_block;
+      c.gc = s.c_run ? (uint16_t)(((1u << s.C) - 1u) << c0) : 0;
+      c.gm = (s.m_run && s.M > 0) ? (uint16_t)(((1u << s.M) - 1u) << (c0 + s.C)) : 0;
+    }
+    __builtin_amdgcn_wave_barrier();
+    int acc = 0;
+#pragma unroll
+    for (int s = 0; s < kCoSegs; ++s) {
+      const uint64_t b = __ballot(on && c.seg == s);
+      if (q == 0) cfg.first[s] = acc;
+      if (on && c.seg == s) cfg.sl[acc + __popcll(b & ((1ull << q) - 1))] = c;
+      acc += __popcll(b);
+    }
+    if (q == 0) cfg.first[kCoSegs] = acc;
+    if (on) {
+      uint8_t* lv = reinterpret_cast<uint8_t*>(cfg.lvw) + c.seg * 16 + c0;
+      for (int j = 0; j < T; ++j) lv[j] = c.lq;
+      atomicOr(&cfg.run, (unsigned long long)(uint16_t)(c.gc | c.gm) << (16 * c.seg));
+    }
   }
-}
-
-// Built by thread 0 from the loaded slot table.
-__device__ void build_cfg(const SlotLite* lite, int level, CoCfg& cfg) {
-  uint8_t lv[kCoCols];
-  for (int c = 0; c < kCoCols; ++c) lv[c] = 0x7F;
-  int cnt[kCoSegs] = {0, 0, 0, 0};
-  SlotCfg tmp[kCoSlots];
-  int nt = 0;
-  uint32_t segm = 0;
-  for (int q = 0; q < kCoSlots; ++q) {
-    const SlotLite& s = lite[q];
-    if (!s.on) continue;
-    SlotCfg c;
-    c.q = (uint8_t)q;
-    c.seg = (uint8_t)s.seg;
-    c.lq = (uint8_t)(level - s.start);
-    c.blk_m = (uint8_t)s.m_block;
-    c.gc = s.c_run ? (uint16_t)(((1u << s.C) - 1u) << s.c0) : 0;
-    c.gm = (s.m_run && s.M > 0) ? (uint16_t)(((1u << s.M) - 1u) << (s.c0 + s.C)) : 0;
-    for (int j = 0; j < s.C + s.M; ++j) lv[s.seg * 16 + s.c0 + j] = c.lq;
-    tmp[nt++] = c;
-    ++cnt[s.seg];
-    segm |= 1u << s.seg;
-  }
-  int acc = 0;
-  for (int s = 0; s < kCoSegs; ++s) {
-    cfg.first[s] = acc;
-    acc += cnt[s];
-  }
-  cfg.first[kCoSegs] = acc;
-  int pos[kCoSegs];
-  for (int s = 0; s < kCoSegs; ++s) pos[s] = cfg.first[s];
-  for (int i = 0; i < nt; ++i) cfg.sl[pos[tmp[i].seg]++] = tmp[i];
-  cfg.nslot = nt;
-  cfg.seg_mask = segm;
-  unsigned long long run = 0;
-  for (int i = 0; i < nt; ++i)
-    run |= (unsigned long long)(tmp[i].gc | tmp[i].gm) << (16 * tmp[i].seg);
-  cfg.run = run;
-  for (int s = 0; s < kCoSegs; ++s)
-    for (int k = 0; k < 4; ++k)
-      cfg.lvw[s][k] = (uint32_t)lv[s * 16 + 4 * k] | ((uint32_t)lv[s * 16 + 4 * k + 1] << 8) |
-                      ((uint32_t)lv[s * 16 + 4 * k + 2] << 16) |
-                      ((uint32_t)lv[s * 16 + 4 * k + 3] << 24);
+  __syncthreads();
 }
 
 // Last index j in [lo, hi) with a[j * stride] <= x (non-decreasing, a[lo] <= x),
@@ -247,26 +224,28 @@ __global__ __launch_bounds__(kBlock) void k_co_seed(uint8_t* Hs, const int32_t* 
 // that is not blocked expands for the run's keywords with h <= l.  The entry
 // covers the union of the row slices its runs need; the expansion filters
 // every arc by its level and each column's level.
-__global__ __launch_bounds__(kBlock) void k_co_scan(CohortView v, DevGraphView g, int level) {
+//
+// A node's rows of all segments are read at once, before any is looked at.
+// The rows' bytes bound it (2M nodes and 64
+// columns: 128 MB, 82 us before this order and the parallel table, 57 us now; 50M
+// nodes: 3.2 GB, 1.1 ms before, 0.9 ms now, segments without queries left out).
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
+void k_co_scan(CohortView v, DevGraphView g, int level) {
   __shared__ CoCfg cfg;
-  __shared__ SlotLite s_lite[kCoSlots];
   __shared__ uint32_t s_ncand[kCoSlots];
   __shared__ unsigned long long s_gf;
   __shared__ uint32_t s_m32[(kBlock / kWave + 1) * 2];
-  load_lite(v, s_lite);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    build_cfg(s_lite, level, cfg);
-    s_gf = 0;
-  }
   if (threadIdx.x < kCoSlots) s_ncand[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t segm = cfg.seg_mask;
+  if (threadIdx.x == 0) s_gf = 0;
+  build_cfg(v, level, cfg);
+  int first[kCoSegs + 1];
+#pragma unroll
+  for (int s = 0; s <= kCoSegs; ++s) first[s] = __builtin_amdgcn_readfirstlane(cfg.first[s]);
   const int64_t wg0 = (int64_t)blockIdx.x * v.cpw * kScanNodes;
   const int64_t wg1 = min(wg0 + (int64_t)v.cpw * kScanNodes, (int64_t)v.n_pad);
   uint32_t cq = 0, cw = 0;
   unsigned long long gf = 0;
-  if (segm) {
+  if (first[kCoSegs]) {
 #pragma unroll 1
     for (int64_t b0 = wg0; b0 < wg1; b0 += kBlock) {
       const int64_t vv = b0 + threadIdx.x;
@@ -275,15 +254,22 @@ __global__ __launch_bounds__(kBlock) void k_co_scan(CohortView v, DevGraphView g
       int hi_lv = -1, lo_lv = INT_MAX;
       uint32_t amax = 0;
       if (vv < v.n) {
-        amax = g.row_amax[vv];
-#pragma unroll 1
+        uint4 row[kCoSegs];
+#pragma unroll
         for (int s = 0; s < kCoSegs; ++s) {
-          if (!((segm >> s) & 1u)) continue;
-          const uint4 row = reinterpret_cast<const uint4*>(seg_base(v, s))[vv];
-          if ((row.x & row.y & row.z & row.w) == 0xFFFFFFFFu) continue;
-          const RowMasks m = row_masks(row, cfg.lvw[s]);
+          row[s] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+          if (first[s] < first[s + 1])
+            row[s] = reinterpret_cast<const uint4*>(seg_base(v, s))[vv];
+        }
+        amax = g.row_amax[vv];
+        const unsigned long long rold = r_get(v, vv);
+#pragma unroll
+        for (int s = 0; s < kCoSegs; ++s) {
+          if ((row[s].x & row[s].y & row[s].z & row[s].w) == 0xFFFFFFFFu) continue;
+          const RowMasks m = row_masks(row[s], cfg.lvw[s]);
           rfin |= (unsigned long long)m.fin << (16 * s);
-          for (int i = cfg.first[s]; i < cfg.first[s + 1]; ++i) {
+#pragma unroll 1
+          for (int i = first[s]; i < first[s + 1]; ++i) {
             const SlotCfg sc = cfg.sl[i];
 #pragma unroll
             for (int grp = 0; grp < 2; ++grp) {
@@ -304,11 +290,9 @@ __global__ __launch_bounds__(kBlock) void k_co_scan(CohortView v, DevGraphView g
             }
           }
         }
-      }
-      if (vv < v.n) {
         // the reached mask of the running columns, as the expansion reads it
         const unsigned long long rnew = rfin & cfg.run;
-        if (r_get(v, vv) != rnew) r_put(v, vv, rnew);
+        if (rold != rnew) r_put(v, vv, rnew);
       }
       CoEntry e = {};
       uint32_t work = 0;
@@ -340,7 +324,11 @@ __global__ __launch_bounds__(kBlock) void k_co_scan(CohortView v, DevGraphView g
   __syncthreads();
   if (threadIdx.x == 0) {
     v.tot[blockIdx.x] = make_uint2(cq, cw);
-    if (s_gf) atomicOr(&v.acc->gfront[level & 1], s_gf);
+    // only bits that are not there yet: device memory performs the updates of
+    // one word one at a time
+    unsigned long long* all = &v.acc->gfront[level & 1];
+    if (s_gf & ~__hip_atomic_load(all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicOr(all, s_gf);
   }
   if (threadIdx.x < kCoSlots && s_ncand[threadIdx.x])
     atomicAdd(&v.acc->ncand[level & 1][threadIdx.x], s_ncand[threadIdx.x]);
@@ -582,51 +570,30 @@ __global__ __launch_bounds__(kCtlT) void k_co_control(CohortView v, int level, u
 template <int TILE>
 __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView g, int level) {
   __shared__ unsigned long long s_ge[256], s_eq[256];
-  __shared__ uint8_t s_lv1[kCoCols];
-  __shared__ uint8_t s_lvc[kCoCols];
-  __shared__ unsigned long long s_run;
+  __shared__ CoCfg cfg;
   __shared__ uint32_t s_base[TILE];
   __shared__ unsigned long long s_nm[TILE], s_om[TILE];
   __shared__ uint16_t s_own[TILE];
   __shared__ uint32_t s_scan[kBlock / kWave + 1];
   __shared__ int32_t s_e[4];
-  __shared__ SlotLite s_lite[kCoSlots];
   const uint32_t W = v.wtot[0];
   if (W == 0) return;
-  load_lite(v, s_lite);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long run = 0;
-    for (int c = 0; c < kCoCols; ++c) { s_lvc[c] = 0xFF; s_lv1[c] = 0; }
-    for (int q = 0; q < kCoSlots; ++q) {
-      const SlotLite& s = s_lite[q];
-      if (!s.on) continue;
-      const int lq = level - s.start;
-      for (int j = 0; j < s.C + s.M; ++j) {
-        const bool on = j < s.C ? s.c_run != 0 : s.m_run != 0;
-        const int c = s.seg * 16 + s.c0 + j;
-        s_lvc[c] = (uint8_t)lq;
-        s_lv1[c] = (uint8_t)(lq + 1);
-        if (on) run |= 1ull << c;
-      }
-    }
-    s_run = run;
-  }
-  __syncthreads();
+  build_cfg(v, level, cfg);
   {
     const int a = threadIdx.x;   // kBlock == 256 levels
     unsigned long long ge = 0, eq = 0;
-    const unsigned long long run = s_run;
-    for (int c = 0; c < kCoCols; ++c) {
-      if (!((run >> c) & 1ull)) continue;
-      if ((int)s_lvc[c] >= a) ge |= 1ull << c;
-      if ((int)s_lvc[c] == a) eq |= 1ull << c;
+    for (int i = 0; i < cfg.first[kCoSegs]; ++i) {
+      const SlotCfg sc = cfg.sl[i];
+      const unsigned long long m = (unsigned long long)(uint16_t)(sc.gc | sc.gm) << (16 * sc.seg);
+      if ((int)sc.lq >= a) ge |= m;
+      if ((int)sc.lq == a) eq |= m;
     }
     s_ge[a] = ge;
     s_eq[a] = eq;
   }
   __syncthreads();
-  if (s_run == 0) return;
+  if (cfg.run == 0) return;
+  const uint8_t* lv = reinterpret_cast<const uint8_t*>(cfg.lvw);
   constexpr int IPT = TILE / kBlock;
   const int nb = v.nblocks;
   const int64_t per_wg = (int64_t)v.cpw * kScanNodes;
@@ -703,7 +670,7 @@ __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView
       while (mm) {
         const int c = __ffsll(mm) - 1;
         mm &= mm - 1;
-        seg_base(v, c >> 4)[(size_t)nbv[k] * 16 + (c & 15)] = s_lv1[c];
+        seg_base(v, c >> 4)[(size_t)nbv[k] * 16 + (c & 15)] = lv[c] + 1;
       }
     }
     __syncthreads();
@@ -718,84 +685,60 @@ __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView
 // than w) go first in any order, those of the last level follow in node
 // order, which is what the top-w selection expects.
 
-__global__ __launch_bounds__(kBlock) void k_co_cand_count(CoCandView cv, int32_t n, int32_t n_pad,
-                                                          int32_t cpw) {
+// One pass: the last level's keys are staged at each scan workgroup's nodes, as
+// on the single path, with their number; the few of earlier levels go to a
+// list.  The rows' bytes bound it (a count, a prefix and a second pass that
+// wrote took 84 us beside the levels of 2M nodes and 3.9 ms beside those of
+// 50M; this one takes 35 us and 1.5 ms).
+__global__ __launch_bounds__(kBlock) void k_co_cand(CoCandView cv, int32_t n, int32_t cpw) {
   __shared__ uint32_t s_red[kBlock / kWave + 1];
   const int64_t wg0 = (int64_t)blockIdx.x * cpw * kScanNodes;
   const int64_t wg1 = min(wg0 + (int64_t)cpw * kScanNodes, (int64_t)n);
-  uint32_t last = 0, prev = 0;
-  for (int64_t v = wg0 + threadIdx.x; v < wg1; v += kBlock) {
-    const uint8_t* r = cv.Hc + v * 16;
-    bool complete = true;
-    int mx = 0;
-    for (int j = 0; j < cv.C; ++j) {
-      const int h = r[j];
-      complete &= h != kInf;
-      mx = h > mx ? h : mx;
-    }
-    if (complete && mx <= cv.end) {
-      if (mx == cv.end) ++last; else ++prev;
-    }
-  }
-  const uint32_t tl = block_sum<uint32_t, kBlock>(last, s_red);
-  const uint32_t tp = block_sum<uint32_t, kBlock>(prev, s_red);
-  if (threadIdx.x == 0) {
-    cv.cnt[blockIdx.x] = tl;
-    if (tp) atomicAdd(&cv.cursor[1], tp);
-  }
-}
-
-__global__ __launch_bounds__(kCtlT) void k_co_cand_scan(CoCandView cv, int32_t nb) {
-  __shared__ uint32_t s_m32[kCtlT / kWave + 1];
-  const uint32_t prev = cv.cursor[1];
-  const int per = (nb + kCtlT - 1) / kCtlT;
-  const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
-  uint32_t sum = 0;
-  for (int b = b0; b < b1; ++b) sum += cv.cnt[b];
-  uint32_t tot;
-  uint32_t ex = block_exclusive_scan<uint32_t, kCtlT>(sum, s_m32, &tot);
-  for (int b = b0; b < b1; ++b) {
-    cv.off[b] = prev + ex;
-    ex += cv.cnt[b];
-  }
-  if (threadIdx.x == 0) {
-    RunStatus st = {};
-    st.ncand_total = prev + tot;
-    st.ncand_level = tot;
-    *cv.st = st;
-    cv.cursor[0] = 0;
-    cv.cursor[1] = 0;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_co_cand_write(CoCandView cv, int32_t n, int32_t cpw) {
-  __shared__ uint32_t s_red[kBlock / kWave + 1];
-  const int64_t wg0 = (int64_t)blockIdx.x * cpw * kScanNodes;
-  const int64_t wg1 = min(wg0 + (int64_t)cpw * kScanNodes, (int64_t)n);
-  uint32_t base = cv.off[blockIdx.x];
+  const int sh = cv.c0 * 8;
+  uint32_t base = 0;
   for (int64_t b0 = wg0; b0 < wg1; b0 += kBlock) {
     const int64_t v = b0 + threadIdx.x;
     bool keep = false, last = false;
-    uint64_t key = 0;
+    int mx = 0, sum = 0;
     if (v < wg1) {
-      const uint8_t* r = cv.Hc + v * 16;
-      bool complete = true;
-      int mx = 0, sum = 0;
-      for (int j = 0; j < cv.C; ++j) {
-        const int h = r[j];
-        complete &= h != kInf;
-        mx = h > mx ? h : mx;
-        sum += h == kInf ? 0 : h;
+      const uint4 row = reinterpret_cast<const uint4*>(cv.seg)[v];
+      uint64_t lo = row.x | (uint64_t)row.y << 32, hi = row.z | (uint64_t)row.w << 32;
+      if (sh >= 64) {
+        lo = hi >> (sh - 64);
+      } else if (sh > 0) {
+        lo = lo >> sh | hi << (64 - sh);
+        hi >>= sh;
       }
-      keep = complete && mx <= cv.end;
-      last = keep && mx == cv.end;
-      key = ((uint64_t)mx << 48) | ((uint64_t)sum << 32) | (uint32_t)cv.orig_id[v];
+      for (int j = 0; j < cv.C; ++j) {
+        const int h = (int)((j < 8 ? lo >> (8 * j) : hi >> (8 * j - 64)) & 0xFF);
+        mx = h > mx ? h : mx;   // INF: above every level
+        sum += h;
+      }
+      keep = mx <= cv.end;
+      last = mx == cv.end;
     }
+    uint64_t key = 0;
+    if (keep) key = ((uint64_t)mx << 48) | ((uint64_t)sum << 32) | (uint32_t)cv.orig_id[v];
     uint32_t tot;
     const uint32_t ex = block_exclusive_scan<uint32_t, kBlock>(last ? 1u : 0u, s_red, &tot);
-    if (last) cv.cand[base + ex] = key;
-    else if (keep) cv.cand[atomicAdd(&cv.cursor[0], 1u)] = key;
+    if (last) cv.cand[wg0 + base + ex] = key;
+    else if (keep) cv.early[atomicAdd(&cv.cursor[0], 1u)] = key;
     base += tot;
+  }
+  if (threadIdx.x == 0) cv.cnt[blockIdx.x] = base;
+}
+
+__global__ __launch_bounds__(kCtlT) void k_co_cand_sum(CoCandView cv, int32_t nb) {
+  __shared__ uint32_t s_m32[kCtlT / kWave + 1];
+  uint32_t sum = 0;
+  for (int b = threadIdx.x; b < nb; b += kCtlT) sum += cv.cnt[b];
+  const uint32_t tot = block_sum<uint32_t, kCtlT>(sum, s_m32);
+  if (threadIdx.x == 0) {
+    RunStatus st = {};
+    st.ncand_total = cv.cursor[0] + tot;
+    st.ncand_level = tot;
+    *cv.st = st;
+    cv.cursor[0] = 0;
   }
 }
 
@@ -1115,9 +1058,8 @@ void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int
 }
 
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s) {
-  k_co_cand_count<<<v.nblocks, kBlock, 0, s>>>(cv, v.n, v.n_pad, v.cpw);
-  k_co_cand_scan<<<1, kCtlT, 0, s>>>(cv, v.nblocks);
-  k_co_cand_write<<<v.nblocks, kBlock, 0, s>>>(cv, v.n, v.cpw);
+  k_co_cand<<<v.nblocks, kBlock, 0, s>>>(cv, v.n, v.cpw);
+  k_co_cand_sum<<<1, kCtlT, 0, s>>>(cv, v.nblocks);
 }
 
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,

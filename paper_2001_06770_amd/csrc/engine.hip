@@ -87,7 +87,7 @@ struct Engine {
   hipStream_t cg_stream = nullptr;
   hipEvent_t lvl_ev[kCoMirrors] = {};   // level l's control step is done (slot l % kCoMirrors)
   CohortView v = {};
-  DevBuf H, R, slots, acc, tot, wpre, qpre, wtot, stage, cand, ccnt, coff, ccur, cst, csel, dmin;
+  DevBuf H, R, slots, acc, tot, wpre, qpre, wtot, stage, cand, ccnt, cearly, ccur, cst, csel, dmin;
   bool any_vc = false;   // some slot's marginal run is checked (V_C ready): minima each level
   CoMirror* h_mir = nullptr;
   CoMirror* d_mir = nullptr;
@@ -138,7 +138,7 @@ int engine_alloc(Engine& E) {
   RAKS_TRY(dev_alloc(c, E.stage, (size_t)n_pad * sizeof(CoEntry)));
   RAKS_TRY(dev_alloc(c, E.cand, (size_t)n_pad * 8));
   RAKS_TRY(dev_alloc(c, E.ccnt, (size_t)nb * 4));
-  RAKS_TRY(dev_alloc(c, E.coff, (size_t)nb * 4));
+  RAKS_TRY(dev_alloc(c, E.cearly, (size_t)kMaxW * 8));
   RAKS_TRY(dev_alloc(c, E.ccur, 16));
   RAKS_TRY(dev_alloc(c, E.cst, sizeof(RunStatus)));
   RAKS_TRY(dev_alloc(c, E.csel, (size_t)kSelParts * (kMaxW * 8 + 4)));
@@ -212,7 +212,7 @@ int engine_create(Ctx* c, Engine** out) {
   if (!rc) rc = engine_alloc(*E);
   if (rc) {
     for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->wpre, &E->qpre, &E->wtot, &E->stage,
-                      &E->cand, &E->ccnt, &E->coff, &E->ccur, &E->cst, &E->csel, &E->dmin})
+                      &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
       dev_free(c, *b);
     if (E->h_mir) (void)hipHostFree(E->h_mir);
     drop_streams(*E);
@@ -534,19 +534,23 @@ int enqueue_cg(Engine& E, CoQuery* q) {
   Status* st = P<Status>(L->status);
   const uint8_t* Hc = seg_ptr(E, q->seg, q->c0);
   CoCandView cv;
-  cv.Hc = Hc;
+  cv.seg = seg_ptr(E, q->seg, 0);
+  cv.c0 = q->c0;
   cv.C = q->p.C;
   cv.end = q->c_end;
   cv.cnt = P<uint32_t>(E.ccnt);
-  cv.off = P<uint32_t>(E.coff);
-  cv.cursor = P<uint32_t>(E.ccur);
   cv.cand = P<uint64_t>(E.cand);
+  cv.cursor = P<uint32_t>(E.ccur);
+  cv.early = P<uint64_t>(E.cearly);
   cv.st = P<RunStatus>(E.cst);
   cv.orig_id = P<int32_t>(c->orig_id);
   launch_co_cand(cv, E.v, s);
   SelectView sv = {};
   sv.int_id = P<int32_t>(c->int_id);
-  sv.cand = P<uint64_t>(E.cand);
+  sv.cand = P<uint64_t>(E.cearly);
+  sv.ncand = P<uint32_t>(E.ccnt);
+  sv.s_cand = P<uint64_t>(E.cand);
+  sv.always_staged = 1;
   sv.nblocks = E.v.nblocks;
   sv.cpw = E.v.cpw;
   sv.part_keys = P<uint64_t>(E.csel);
@@ -929,7 +933,7 @@ void cohort_destroy(Ctx* c) {
   (void)hipStreamSynchronize(E->stream);
   (void)hipStreamSynchronize(E->cg_stream);
   for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->wpre, &E->qpre, &E->wtot, &E->stage,
-                    &E->cand, &E->ccnt, &E->coff, &E->ccur, &E->cst, &E->csel, &E->dmin})
+                    &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
     dev_free(c, *b);
   for (hipEvent_t e : E->ev_pool) (void)hipEventDestroy(e);
   for (hipEvent_t e : E->tev_pool) (void)hipEventDestroy(e);

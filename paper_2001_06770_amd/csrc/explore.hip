@@ -937,7 +937,7 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
   const uint32_t prev = total - last;
   const uint32_t w = (uint32_t)v.w;
   const uint32_t want = w - min(w, prev);   // slots for the last level
-  const bool staged = v.ncand && total >= w;
+  const bool staged = v.ncand && (v.always_staged || total >= w);
   const int parts = gridDim.x, part = blockIdx.x;
   // the part's keys: [lo, hi) of the last level's
   const uint32_t lo = (staged ? 0u : prev) + (uint32_t)((uint64_t)last * part / parts);
