@@ -286,9 +286,9 @@ int raks_set_batch_mode(raks_ctx* ctx, int32_t mode);
 
 /* Tuning of the cohort path (chosen per workload by the package's autotuner).
  *   expand_wg_per_cu: workgroups per compute unit of the expansion launch
- *     (0 = 8);
- *   expand_tile: arcs per tile of the expansion (each tile's entries and
- *     owner map live in LDS);
+ *     (0 = 8; no more are launched than fit);
+ *   expand_tile: examined arcs that a wavefront of the expansion takes at a
+ *     time;
  *   admit_below: a batch admits waiting queries only while at most this many
  *     queries of the cohort are still exploring (32 admits whenever a query
  *     fits; 0 admits in waves, so a group starts level-aligned and shares more
@@ -297,7 +297,7 @@ int raks_set_batch_mode(raks_ctx* ctx, int32_t mode);
 typedef struct {
     int32_t expand_wg_per_cu;
     int32_t admit_below;
-    int32_t expand_tile;    /* examined arcs per expansion tile: 512, 1024 or 2048 (0 = 1024) */
+    int32_t expand_tile;    /* examined arcs that a wavefront takes: 512, 1024 or 2048 (0 = 1024) */
     int32_t cohort_cols;    /* columns of the cohort: 16, 32 or 64 (0 = 64); a narrower cohort
                              * holds fewer queries at once and keeps its per-node reached masks
                              * in 2 or 4 bytes instead of 8 */

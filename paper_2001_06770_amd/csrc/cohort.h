@@ -113,9 +113,8 @@ struct CohortView {
   CoSlot* slots;                 // [kCoSlots]
   CoAcc* acc;
   uint2* tot;                    // [nblocks] per scan workgroup: entries, examined arcs
-  uint32_t* wpre;                // [nblocks + 1] exclusive prefix of examined arcs
-  uint32_t* qpre;                // [nblocks + 1] exclusive prefix of entries
-  uint32_t* wtot;                // [2] arcs and entries of the level
+  uint32_t* tpre;                // [nblocks] exclusive prefix of expansion tiles
+  uint32_t* wtot;                // [3] arcs, entries and expansion tiles of the level
   CoEntry* stage;                // [n_pad] entries, in each scan workgroup's node range
   CoMirror* mirror;              // device address of the pinned mirror
   uint32_t* dmin;                // [kCoSlots][kMaxW][kMaxKw] running minima of the marginal
@@ -156,9 +155,11 @@ void launch_co_seed(const CohortView& v, int seg, int c0, const int32_t* kw_node
                     const SeedList& seeds, hipStream_t s);
 void launch_co_scan(const CohortView& v, const DevGraphView& g, int level, hipStream_t s);
 void launch_co_control(const CohortView& v, int level, uint64_t seq, hipStream_t s);
-// tile: examined arcs per expansion tile (512, 1024 or 2048)
-void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int grid, int tile,
-                      hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// wpc: workgroups per CU (at most what fits); tile: examined arcs that a
+// wavefront takes at a time (512, 1024 or 2048)
+void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int num_cu, int wpc,
+                      int tile, hipStream_t s, hipEvent_t ev0 = nullptr,
+                      hipEvent_t ev1 = nullptr);
 // CG selection input of slot q (two launches)
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s);
 // After slot q's CG recovery: its outcome to the host

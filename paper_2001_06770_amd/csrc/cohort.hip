@@ -8,12 +8,12 @@
 //                 level), the central-node test (Theorem identifyCG), the
 //                 joining-flag block, and one staged expansion entry per node
 //                 with the columns it expands for;
-//   k_co_control  workgroup 0 turns the scan totals into the level's queue
+//   k_co_control  workgroup 0 turns the scan totals into the level's tile
 //                 prefixes; workgroup 1 + q applies slot q's identification
 //                 and termination rules (>= w CGs; the RPG check over V_C
 //                 with Theorem 4, replayed over the levels it has missed);
-//   k_co_expand   Algorithm 1 over tiles of 1024 consecutive examined arcs,
-//                 reading the staged entries in place; an arc is read once
+//   k_co_expand   Algorithm 1 over tiles of consecutive examined arcs, a
+//                 wavefront each, reading the staged entries in place; an arc is read once
 //                 for every query that expands its source node.
 // After a query's runs: its CG selection input (k_co_cand_*), the final
 // marginal decision (k_co_rpg_final) and its work counters (k_co_counters)
@@ -458,32 +458,29 @@ __device__ inline void co_publish_slot(CoLevelMirror* mir, int q, const CoSlot& 
 
 __global__ __launch_bounds__(kCtlT) void k_co_control(CohortView v, int level, uint64_t seq) {
   if (blockIdx.x == 0) {
-    // queue prefixes of the level: each thread takes a run of `per` scan
+    // tile prefixes of the level: each thread takes a run of `per` scan
     // workgroups
-    __shared__ uint32_t s_m32[(kCtlT / kWave + 1) * 2];
+    __shared__ uint32_t s_m32[(kCtlT / kWave + 1) * 3];
     const int nb = v.nblocks;
     const int per = (nb + kCtlT - 1) / kCtlT;
     const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
-    uint32_t x[2] = {0, 0}, tt[2];
+    uint32_t x[3] = {0, 0, 0}, tt[3];
     for (int b = b0; b < b1; ++b) {
       const uint2 t = v.tot[b];
       x[0] += t.x;
       x[1] += t.y;
+      x[2] += (t.y + kWaveTile - 1) / kWaveTile;
     }
-    block_exclusive_scan_multi<2, kCtlT, uint32_t>(x, tt, s_m32);
-    uint32_t q = x[0], w = x[1];
+    block_exclusive_scan_multi<3, kCtlT, uint32_t>(x, tt, s_m32);
+    uint32_t before = x[2];
     for (int b = b0; b < b1; ++b) {
-      const uint2 t = v.tot[b];
-      v.qpre[b] = q;
-      v.wpre[b] = w;
-      q += t.x;
-      w += t.y;
+      v.tpre[b] = before;
+      before += (v.tot[b].y + kWaveTile - 1) / kWaveTile;
     }
     if (threadIdx.x == 0) {
-      v.qpre[nb] = tt[0];
-      v.wpre[nb] = tt[1];
       v.wtot[0] = tt[1];
       v.wtot[1] = tt[0];
+      v.wtot[2] = tt[2];
       v.acc->gfront[(level + 1) & 1] = 0;
     }
     if (threadIdx.x < kCoSlots) v.acc->ncand[(level + 1) & 1][threadIdx.x] = 0;
@@ -558,29 +555,44 @@ __global__ __launch_bounds__(kCtlT) void k_co_control(CohortView v, int level, u
 
 // ------------------------------------------------------------ expansion ---
 //
-// Algorithm 1 at cohort level `level`.  Tile of 1024 consecutive examined
-// arcs; the scan workgroups holding its first and last arc are found in the
-// level's arc prefix, its entries in their staging slots, and an owner map
-// gives every arc its entry.  For arc f -> n with level a the columns to
-// relax are the entry's new columns whose query level is >= a and its old
-// columns whose query level equals a (precomputed per a); every one of them
-// still INF at n gets its query's level + 1.  Writes need no atomics: every
-// write of a level stores the same value into a byte that was INF (Theorem
-// "lockfree").
-template <int TILE>
-__global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView g, int level) {
-  __shared__ unsigned long long s_ge[256], s_eq[256];
+// Algorithm 1 at cohort level `level`, in tiles of kWaveTile consecutive
+// examined arcs of one scan workgroup's entries.  For arc f -> n with level a
+// the columns to relax are the entry's new columns whose query level is >= a
+// and its old columns whose query level equals a (precomputed per a); every one
+// of them still INF at n gets its query's level + 1.  Writes need no atomics:
+// every write of a level stores the same value into a byte that was INF
+// (Theorem "lockfree").
+//
+// A tile is one wavefront's work from its entries to its writes, as on the
+// single path: no barrier ties wavefronts together, so while one searches or
+// waits for its gathers the others are at any other step.  A wavefront takes
+// runs of a few consecutive tiles, searches the first one's first entry and
+// walks on from there.  At most kCoExpWgs workgroups per CU, what its LDS holds
+// (more would start when the first ones end, with a full share of the tiles).
+//
+// The lines of the gathered masks and of the scattered stores bound it (many
+// arcs of a level reach the same target and store the same bytes; the masks stay
+// as the scan left them, since plain stores to them from several XCDs at once
+// leave their caches with different values).  Per level, 32 queries on 2M
+// nodes: 167 us with a workgroup per tile of 1024 arcs, 159 us now; 12 queries
+// on 50M nodes and 1B arcs: 3.9 ms and 3.6 ms.
+constexpr int kCoExpWgs = 6;
+
+__global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView g, int level,
+                                                      uint32_t max_run) {
+  constexpr int kWaves = kBlock / kWave, IPT = kWaveTile / kWave, kLevels = 128;
   __shared__ CoCfg cfg;
-  __shared__ uint32_t s_base[TILE];
-  __shared__ unsigned long long s_nm[TILE], s_om[TILE];
-  __shared__ uint16_t s_own[TILE];
-  __shared__ uint32_t s_scan[kBlock / kWave + 1];
-  __shared__ int32_t s_e[4];
-  const uint32_t W = v.wtot[0];
-  if (W == 0) return;
+  __shared__ unsigned long long s_ge[kLevels], s_eq[kLevels];
+  __shared__ uint32_t s_base[kWaves][kWaveTile];   // arc of tile item i is s_base[] + i
+  __shared__ unsigned long long s_nm[kWaves][kWaveTile], s_om[kWaves][kWaveTile];
+  __shared__ __align__(4) uint8_t s_own[kWaves][kWaveTile];   // owner entry of each item
+  const uint32_t tiles = v.wtot[2];
+  const uint32_t waves = gridDim.x * kWaves;
+  const uint32_t run = min(max_run, (tiles + waves - 1) / waves);
+  if (blockIdx.x * kWaves * run >= tiles) return;   // none for the workgroup
   build_cfg(v, level, cfg);
-  {
-    const int a = threadIdx.x;   // kBlock == 256 levels
+  if (threadIdx.x < kLevels) {
+    const int a = threadIdx.x;   // queries' levels are below the last one
     unsigned long long ge = 0, eq = 0;
     for (int i = 0; i < cfg.first[kCoSegs]; ++i) {
       const SlotCfg sc = cfg.sl[i];
@@ -594,86 +606,100 @@ __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView
   __syncthreads();
   if (cfg.run == 0) return;
   const uint8_t* lv = reinterpret_cast<const uint8_t*>(cfg.lvw);
-  constexpr int IPT = TILE / kBlock;
-  const int nb = v.nblocks;
+  const int wv = wave_id(), lane = lane_id();
+  uint32_t* base = s_base[wv];
+  unsigned long long* nm = s_nm[wv];
+  unsigned long long* om = s_om[wv];
+  uint8_t* own = s_own[wv];
   const int64_t per_wg = (int64_t)v.cpw * kScanNodes;
-  const uint32_t ntiles = (W + TILE - 1) / TILE;
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint32_t w0 = tile * TILE;
-    const uint32_t w1 = min(W, w0 + (uint32_t)TILE);
-    if (wave_id() == 0) {
-      // entries holding the tile's first and last arcs (global entry numbers)
-#pragma unroll 1
-      for (int k = 0; k < 2; ++k) {
-        const uint32_t x = k == 0 ? w0 : w1 - 1;
-        const int b = wave_search_s(v.wpre, 0, nb + 1, 1, x);
-        const uint32_t nqb = v.qpre[b + 1] - v.qpre[b];
-        const int j = wave_search_s(&v.stage[b * per_wg].pre, 0, (int)nqb,
-                                    (int)(sizeof(CoEntry) / 4), x - v.wpre[b]);
-        if (lane_id() == 0) { s_e[2 * k] = (int)(v.qpre[b] + j); s_e[2 * k + 1] = b; }
+  for (uint32_t t0 = (blockIdx.x * kWaves + wv) * run; t0 < tiles; t0 += waves * run) {
+    const uint32_t tile_end = min(tiles, t0 + run);
+    bool fresh = true;   // the scan workgroup and entry of the tile's first arc are not known yet
+    uint32_t k = 0, work = 0;
+    int e = 0, nq = 0;
+    const CoEntry* items = nullptr;
+    for (uint32_t tile = t0; tile < tile_end; ++tile) {
+      if (fresh) {
+        // the last scan workgroup with at most `tile` tiles before it has some
+        const int sb = wave_search_s(v.tpre, 0, v.nblocks, 1, tile);
+        const uint2 t = v.tot[sb];
+        k = tile - v.tpre[sb];
+        nq = (int)t.x;
+        work = t.y;
+        items = v.stage + sb * per_wg;
+        e = k ? wave_search_s(&items->pre, 0, nq, (int)(sizeof(CoEntry) / 4), k * kWaveTile) : 0;
+        fresh = false;
       }
-    }
-    for (int i = threadIdx.x; i < TILE; i += kBlock) s_own[i] = 0;
-    __syncthreads();
-    const int E0 = s_e[0], bA = s_e[1], E1 = s_e[2], bB = s_e[3];
-    const int cnt = E1 - E0 + 1;
-    for (int t = threadIdx.x; t < cnt; t += kBlock) {
-      const uint32_t E = (uint32_t)(E0 + t);
-      // scan workgroup of entry E: last b in [bA, bB] with qpre[b] <= E
-      int b = bA;
-      if (bB > bA) b = upper_index<uint32_t>(v.qpre, bA, bB + 1, E);
-      const CoEntry e = v.stage[b * per_wg + (E - v.qpre[b])];
-      const uint32_t off = v.wpre[b] + e.pre;
-      s_base[t] = e.arc - off + w0;   // arc of tile item i is s_base[t] + i
-      s_nm[t] = ((unsigned long long)e.nhi << 32) | e.nlo;
-      s_om[t] = ((unsigned long long)e.ohi << 32) | e.olo;
-      s_own[off > w0 ? off - w0 : 0] = (uint16_t)t;
-    }
-    __syncthreads();
-    uint32_t loc[IPT];
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      const uint32_t o = s_own[threadIdx.x * IPT + k];
-      m = o > m ? o : m;
-      loc[k] = m;
-    }
-    const uint32_t pre = block_exclusive_max(m, s_scan);
-#pragma unroll
-    for (int k = 0; k < IPT; ++k)
-      s_own[threadIdx.x * IPT + k] = (uint16_t)(pre > loc[k] ? pre : loc[k]);
-    __syncthreads();
-    // all of the thread's arcs at once: their levels and targets, then the
-    // targets' reached masks, then the writes, so that a wavefront has IPT
-    // independent gathers in flight instead of one dependent chain per arc
-    int32_t nbv[IPT];
-    unsigned long long wantv[IPT], rv[IPT];
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      const uint32_t i = k * kBlock + threadIdx.x;
-      wantv[k] = 0;
-      nbv[k] = 0;
-      if (w0 + i < w1) {
-        const int j = s_own[i];
-        const uint32_t e = s_base[j] + i;
-        const uint32_t a = g.act_s[e];
-        nbv[k] = g.col_s[e];
-        wantv[k] = (s_nm[j] & s_ge[a]) | (s_om[j] & s_eq[a]);
+      const uint32_t w0 = k * kWaveTile, w1 = min(work, w0 + (uint32_t)kWaveTile);
+      const uint32_t none = 0;
+      __builtin_memcpy(&own[4 * lane], &none, 4);
+      // the tile's entries, at most one per arc
+      for (int slot = lane;; slot += kWave) {
+        CoEntry it = {};
+        if (e + lane < nq) it = items[e + lane];
+        const bool take = e + lane < nq && it.pre < w1;
+        if (take) {
+          base[slot] = it.arc - it.pre + w0;
+          nm[slot] = ((unsigned long long)it.nhi << 32) | it.nlo;
+          om[slot] = ((unsigned long long)it.ohi << 32) | it.olo;
+          own[it.pre > w0 ? it.pre - w0 : 0] = (uint8_t)slot;
+        }
+        const int n = __popcll(__ballot(take));
+        e += n;
+        if (n < kWave) {
+          // lane n holds the entry after the tile's: the next tile starts with
+          // it, or with this tile's last one if that goes on
+          const uint32_t nx = (uint32_t)__builtin_amdgcn_readlane((int)it.pre, n);
+          if (e >= nq || nx != w1) --e;
+          break;
+        }
       }
-    }
+      __builtin_amdgcn_wave_barrier();
+      uint32_t mk4;   // marks of items 4 * lane .. 4 * lane + 3
+      __builtin_memcpy(&mk4, &own[4 * lane], 4);
+      uint32_t o0 = mk4 & 0xFFu, o1 = (mk4 >> 8) & 0xFFu, o2 = (mk4 >> 16) & 0xFFu, o3 = mk4 >> 24;
+      o1 = max(o0, o1);
+      o2 = max(o1, o2);
+      o3 = max(o2, o3);
+      const uint32_t inc = wave_scan_op(o3, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+      const uint32_t pre = dpp_move<0x138, 0xF>(inc);   // of the lanes before (wave_shr:1)
+      o0 = max(o0, pre); o1 = max(o1, pre); o2 = max(o2, pre); o3 = max(o3, pre);
+      mk4 = o0 | (o1 << 8) | (o2 << 16) | (o3 << 24);
+      __builtin_memcpy(&own[4 * lane], &mk4, 4);
+      __builtin_amdgcn_wave_barrier();
+      // all of the lane's arcs at once: their levels and targets, then the
+      // targets' reached masks, then the writes
+      int32_t nbv[IPT];
+      unsigned long long wantv[IPT], rv[IPT];
 #pragma unroll
-    for (int k = 0; k < IPT; ++k) rv[k] = wantv[k] ? r_get(v, nbv[k]) : ~0ull;
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-      // columns that have not reached the target (as of the start of the level)
-      unsigned long long mm = ~rv[k] & wantv[k];
-      while (mm) {
-        const int c = __ffsll(mm) - 1;
-        mm &= mm - 1;
-        seg_base(v, c >> 4)[(size_t)nbv[k] * 16 + (c & 15)] = lv[c] + 1;
+      for (int q = 0; q < IPT; ++q) {
+        const uint32_t i = q * kWave + lane;
+        wantv[q] = 0;
+        nbv[q] = 0;
+        if (w0 + i < w1) {
+          const int j = own[i];
+          const uint32_t at = base[j] + i;
+          const uint32_t a = min((uint32_t)g.act_s[at], (uint32_t)kLevels - 1);
+          nbv[q] = g.col_s[at];
+          wantv[q] = (nm[j] & s_ge[a]) | (om[j] & s_eq[a]);
+        }
       }
+#pragma unroll
+      for (int q = 0; q < IPT; ++q) rv[q] = wantv[q] ? r_get(v, nbv[q]) : ~0ull;
+#pragma unroll
+      for (int q = 0; q < IPT; ++q) {
+        // columns that have not reached the target (as of the start of the level)
+        unsigned long long mm = ~rv[q] & wantv[q];
+        while (mm) {
+          const int c = __ffsll(mm) - 1;
+          mm &= mm - 1;
+          seg_base(v, c >> 4)[(size_t)nbv[q] * 16 + (c & 15)] = lv[c] + 1;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      ++k;
+      fresh = w1 == work;   // on to the next scan workgroup that has tiles
     }
-    __syncthreads();
   }
 }
 
@@ -1040,21 +1066,14 @@ void launch_co_control(const CohortView& v, int level, uint64_t seq, hipStream_t
   k_co_control<<<1 + kCoSlots, kCtlT, 0, s>>>(v, level, seq);
 }
 
-template <int TILE>
-void co_expand_at(const CohortView& v, const DevGraphView& g, int level, int grid, hipStream_t s,
-                  hipEvent_t ev0, hipEvent_t ev1) {
+void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int num_cu, int wpc,
+                      int tile, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const dim3 grid((unsigned)(num_cu * std::min(wpc, kCoExpWgs)));
+  const uint32_t run = (uint32_t)std::max(1, tile / kWaveTile);
   if (ev0 && ev1)
-    hipExtLaunchKernelGGL(k_co_expand<TILE>, dim3(grid), dim3(kBlock), 0, s, ev0, ev1, 0, v, g,
-                          level);
+    hipExtLaunchKernelGGL(k_co_expand, grid, dim3(kBlock), 0, s, ev0, ev1, 0, v, g, level, run);
   else
-    k_co_expand<TILE><<<grid, kBlock, 0, s>>>(v, g, level);
-}
-
-void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int grid, int tile,
-                      hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (tile == 512) co_expand_at<512>(v, g, level, grid, s, ev0, ev1);
-  else if (tile == 2048) co_expand_at<2048>(v, g, level, grid, s, ev0, ev1);
-  else co_expand_at<1024>(v, g, level, grid, s, ev0, ev1);
+    k_co_expand<<<grid, kBlock, 0, s>>>(v, g, level, run);
 }
 
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s) {

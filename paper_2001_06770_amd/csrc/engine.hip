@@ -87,7 +87,7 @@ struct Engine {
   hipStream_t cg_stream = nullptr;
   hipEvent_t lvl_ev[kCoMirrors] = {};   // level l's control step is done (slot l % kCoMirrors)
   CohortView v = {};
-  DevBuf H, R, slots, acc, tot, wpre, qpre, wtot, stage, cand, ccnt, cearly, ccur, cst, csel, dmin;
+  DevBuf H, R, slots, acc, tot, tpre, wtot, stage, cand, ccnt, cearly, ccur, cst, csel, dmin;
   bool any_vc = false;   // some slot's marginal run is checked (V_C ready): minima each level
   CoMirror* h_mir = nullptr;
   CoMirror* d_mir = nullptr;
@@ -132,8 +132,7 @@ int engine_alloc(Engine& E) {
   RAKS_TRY(dev_alloc(c, E.slots, sizeof(CoSlot) * kCoSlots));
   RAKS_TRY(dev_alloc(c, E.acc, sizeof(CoAcc)));
   RAKS_TRY(dev_alloc(c, E.tot, (size_t)nb * sizeof(uint2)));
-  RAKS_TRY(dev_alloc(c, E.wpre, (size_t)(nb + 1) * 4));
-  RAKS_TRY(dev_alloc(c, E.qpre, (size_t)(nb + 1) * 4));
+  RAKS_TRY(dev_alloc(c, E.tpre, (size_t)nb * 4));
   RAKS_TRY(dev_alloc(c, E.wtot, 16));
   RAKS_TRY(dev_alloc(c, E.stage, (size_t)n_pad * sizeof(CoEntry)));
   RAKS_TRY(dev_alloc(c, E.cand, (size_t)n_pad * 8));
@@ -164,8 +163,7 @@ int engine_alloc(Engine& E) {
   v.slots = P<CoSlot>(E.slots);
   v.acc = P<CoAcc>(E.acc);
   v.tot = P<uint2>(E.tot);
-  v.wpre = P<uint32_t>(E.wpre);
-  v.qpre = P<uint32_t>(E.qpre);
+  v.tpre = P<uint32_t>(E.tpre);
   v.wtot = P<uint32_t>(E.wtot);
   v.stage = P<CoEntry>(E.stage);
   v.mirror = E.d_mir;
@@ -211,7 +209,7 @@ int engine_create(Ctx* c, Engine** out) {
       rc = fail(RAKS_EDEVICE, "event creation failed");
   if (!rc) rc = engine_alloc(*E);
   if (rc) {
-    for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->wpre, &E->qpre, &E->wtot, &E->stage,
+    for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->tpre, &E->wtot, &E->stage,
                       &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
       dev_free(c, *b);
     if (E->h_mir) (void)hipHostFree(E->h_mir);
@@ -488,10 +486,10 @@ int enqueue_level(Engine& E, int level, uint64_t seq) {
   HIP_OK(hipEventRecord(E.lvl_ev[level & (kCoMirrors - 1)], s));
   if (tm & 1u) {
     hipEvent_t a = timing_event(E), b = timing_event(E);
-    launch_co_expand(E.v, g, level, c->num_cu * c->co_wpc, c->co_tile, s, a, b);
+    launch_co_expand(E.v, g, level, c->num_cu, c->co_wpc, c->co_tile, s, a, b);
     if (a && b) E.timed.push_back({a, b, 0, 0.0, level});
   } else {
-    launch_co_expand(E.v, g, level, c->num_cu * c->co_wpc, c->co_tile, s);
+    launch_co_expand(E.v, g, level, c->num_cu, c->co_wpc, c->co_tile, s);
   }
   HIP_OK(hipGetLastError());
   return RAKS_OK;
@@ -932,7 +930,7 @@ void cohort_destroy(Ctx* c) {
   stop_workers(*E);
   (void)hipStreamSynchronize(E->stream);
   (void)hipStreamSynchronize(E->cg_stream);
-  for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->wpre, &E->qpre, &E->wtot, &E->stage,
+  for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->tpre, &E->wtot, &E->stage,
                     &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
     dev_free(c, *b);
   for (hipEvent_t e : E->ev_pool) (void)hipEventDestroy(e);
