@@ -205,6 +205,10 @@ __global__ __launch_bounds__(kBlock) void k_act_node(const uint8_t* nw, int32_t 
 // ms; with one wavefront per row for every row it was 17.0 ms, all but about
 // 1 ms of it in the largest row, plus 0.08 ms for a pass over the levels.
 constexpr int kSmallRows = 32;      // rows per workgroup of k_sort_small
+// Up to this many rows of the middle classes take one launch of the largest
+// workgroups, two to a CU at once: 13 us where three launches in a row take 36
+// (126k arcs), each as long as its one round of loads.
+constexpr int kFewRows = 512;
 
 struct SortView {
   DevGraphView g;
@@ -528,10 +532,14 @@ void launch_sort_rows(const DevGraphView& g, const SortInput& in, hipStream_t s)
   const int top = v.n_top - v.n_big, mid = v.n_mid - v.n_top, wave = v.n_wave - v.n_mid,
             small = g.n - v.n_wave;
   constexpr int kRows = kBlock / kWave;
-  if (top > 0) k_sort_row<1024, kBigRow><<<top, 1024, 0, s>>>(v, v.n_big, v.n_top);
-  if (mid > 0) k_sort_row<kBlock, kTopRow><<<mid, kBlock, 0, s>>>(v, v.n_top, v.n_mid);
-  if (wave > 0)
-    k_sort_row<kWave, kMidRow><<<(wave + kRows - 1) / kRows, kBlock, 0, s>>>(v, v.n_mid, v.n_wave);
+  if (top + mid + wave > 0 && top + mid + wave <= kFewRows) {
+    k_sort_row<1024, kBigRow><<<top + mid + wave, 1024, 0, s>>>(v, v.n_big, v.n_wave);
+  } else {
+    if (top > 0) k_sort_row<1024, kBigRow><<<top, 1024, 0, s>>>(v, v.n_big, v.n_top);
+    if (mid > 0) k_sort_row<kBlock, kTopRow><<<mid, kBlock, 0, s>>>(v, v.n_top, v.n_mid);
+    if (wave > 0)
+      k_sort_row<kWave, kMidRow><<<(wave + kRows - 1) / kRows, kBlock, 0, s>>>(v, v.n_mid, v.n_wave);
+  }
   if (small > 0) k_sort_small<<<(small + kSmallRows - 1) / kSmallRows, kBlock, 0, s>>>(v);
 }
 
