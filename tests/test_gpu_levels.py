@@ -18,14 +18,16 @@ DEGREES = (1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64, 65, 127, 128, 129, 2047,
            255, 256, 257, 4096, 4097, 8193, 9001, 16384, 16385, 17000)
 
 
-def hub_graph(seed):
-    """One hub per degree, its edges going to a shared pool of leaves and to
-    the other hubs' leaves; labels of very different counts."""
+def hub_graph(seed, more):
+    """One hub per degree (and `more` of 65 to 300 arcs), its edges going to a
+    shared pool of leaves and to the other hubs' leaves; labels of very different
+    counts."""
     rng = np.random.default_rng(seed)
-    hubs, leaves = len(DEGREES), 18_000
+    degrees = DEGREES + tuple(int(x) for x in rng.integers(65, 301, size=more))
+    hubs, leaves = len(degrees), 18_000
     n = hubs + leaves + 7   # some isolated nodes
     edges = set()
-    for h, d in enumerate(DEGREES):
+    for h, d in enumerate(degrees):
         for v in rng.choice(leaves, size=d, replace=False):
             edges.add((h, hubs + int(v), int(min(rng.geometric(0.3), 12))))
     keywords = [sorted(set(int(x) for x in rng.integers(0, n, size=k))) for k in (3, 5, 9, 40, 200, 2)]
@@ -35,9 +37,10 @@ def hub_graph(seed):
 
 @pytest.mark.parametrize("abar_x100", [305, 4000])
 @pytest.mark.parametrize("mode", [0, 1], ids=["edge", "node"])
-def test_row_size_classes(mode, abar_x100):
+@pytest.mark.parametrize("more", [0, 700])   # all middle classes in one launch, one launch each
+def test_row_size_classes(more, mode, abar_x100):
     import paper_2001_06770_amd as raks
-    g = hub_graph(abar_x100 + mode)
+    g = hub_graph(abar_x100 + mode, more)
     g.abar_x100 = abar_x100
     o = oracle.Oracle(g)
     with raks.Context(0, poison=0xA5) as ctx:
