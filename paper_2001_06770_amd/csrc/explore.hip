@@ -819,7 +819,8 @@ __global__ __launch_bounds__(NT) void k_expand(RunView r, DevGraphView g, int le
 // ones in v.cand or lie where the scan workgroups staged them.  The launch's
 // workgroups split them, each keeps the smallest of its part (at most w), and
 // the last one to finish selects among all kept ones.  One workgroup of 1024
-// threads alone took 223 us on 20M nodes (86 us now) and 450 us on 50M.
+// threads alone took 223 us on 20M nodes and 450 us on 50M; 86 us with the keys read
+// again in each pass on 20M, 41 us with them in registers.
 
 // Keys of the last level; f(key) is called by all lanes of a wavefront
 // together, with kNoKey in the lanes that have none.
@@ -834,25 +835,6 @@ struct SelPart {
   uint32_t pre[kScanGroups];
   int b0, b1;                    // scan workgroups that hold the part's keys: [b0, b1)
 };
-
-template <typename F>
-__device__ inline void each_key(const SelectView& v, bool staged, const SelPart& p, uint32_t lo,
-                                uint32_t hi, F f) {
-  const int b0 = staged ? p.b0 : 0, b1 = staged ? p.b1 : 0;
-  for (uint32_t i0 = lo; i0 < hi; i0 += kBlock) {
-    const uint32_t i = i0 + threadIdx.x;
-    uint64_t key = kNoKey;
-    if (i < hi) {
-      if (staged) {
-        const int j = upper_index<uint32_t>(p.pre, b0, b1, i);
-        key = v.s_cand[(int64_t)j * v.cpw * kScanNodes + (i - p.pre[j])];
-      } else {
-        key = v.cand[i];
-      }
-    }
-    f(key);
-  }
-}
 
 struct SelLds {
   uint32_t hist[4096];
@@ -927,6 +909,46 @@ __device__ uint64_t select_bound(SelLds& s, uint32_t need, Each each) {
   return prefix | ((1ull << sh) - 1);
 }
 
+// The `need` smallest of keys fetch(0 .. cnt) (all of them if there are no more)
+// to s_sel, their number to s_n.  Up to kSelReg keys per thread are read once,
+// all at the same time, and kept in registers over the passes.
+constexpr int kSelReg = 16;
+
+template <typename Fetch>
+__device__ inline void select_keys(uint32_t cnt, uint32_t need, SelLds& s, uint64_t* s_sel,
+                                   uint32_t* s_n, Fetch fetch) {
+  if (threadIdx.x == 0) *s_n = 0;
+  __syncthreads();
+  if (!need) return;
+  auto select = [&](auto each) {
+    const uint64_t bound = cnt > need ? select_bound(s, need, each) : kLow48;
+    each([&](uint64_t key) {
+      if (key != kNoKey && (key & kLow48) <= bound) s_sel[atomicAdd(s_n, 1u)] = key;
+    });
+  };
+  if (cnt <= (uint32_t)(kSelReg * kBlock)) {
+    uint64_t k[kSelReg];
+#pragma unroll
+    for (int r = 0; r < kSelReg; ++r) {
+      const uint32_t i = r * kBlock + threadIdx.x;
+      k[r] = i < cnt ? fetch(i) : kNoKey;
+    }
+    select([&](auto f) {
+#pragma unroll
+      for (int r = 0; r < kSelReg; ++r)
+        if (r * kBlock < cnt) f(k[r]);
+    });
+  } else {
+    select([&](auto f) {
+      for (uint32_t i0 = 0; i0 < cnt; i0 += kBlock) {
+        const uint32_t i = i0 + threadIdx.x;
+        f(i < cnt ? fetch(i) : kNoKey);
+      }
+    });
+  }
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
   __shared__ uint64_t s_sel[kMaxW];
   __shared__ SelLds s_lds;
@@ -957,15 +979,12 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
-  auto mine = [&](auto f) { each_key(v, staged, s_part, lo, hi, f); };
-  uint64_t bound = kLow48;
-  if (want && hi - lo > want) bound = select_bound(s_lds, want, mine);
-  mine([&](uint64_t key) {
-    if (key != kNoKey && (key & kLow48) <= bound && want) s_sel[atomicAdd(&s_n, 1u)] = key;
+  const int b0 = staged ? s_part.b0 : 0, b1 = staged ? s_part.b1 : 0;
+  select_keys(hi - lo, want, s_lds, s_sel, &s_n, [&](uint32_t i) {
+    if (!staged) return v.cand[lo + i];
+    const int j = upper_index<uint32_t>(s_part.pre, b0, b1, lo + i);
+    return v.s_cand[(int64_t)j * v.cpw * kScanNodes + (lo + i - s_part.pre[j])];
   });
-  __syncthreads();
   uint32_t n = s_n;
   if (parts > 1) {
     // publish the part's keys; the last workgroup goes on with all of them
@@ -978,24 +997,16 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
     if (!s_last) return;
     __threadfence();
     // all kept keys: part p's in slots [p * kMaxW, p * kMaxW + part_n[p])
-    if (threadIdx.x == 0) { s_n = 0; v.gst->sel_ticket = 0; }
-    __syncthreads();
+    if (threadIdx.x == 0) v.gst->sel_ticket = 0;
     uint32_t all = 0, tot;
     if ((int)threadIdx.x < parts) all = v.part_n[threadIdx.x];
-    (void)block_exclusive_scan<uint32_t, kBlock>(all, s_lds.scan, &tot);
-    auto kept = [&](auto f) {
-      for (int p = wave_id(); p < (parts + 3) / 4 * 4; p += kBlock / kWave) {
-        const uint32_t k = p < parts ? v.part_n[p] : 0u;
-        for (uint32_t i = 0; i < k; i += kWave)
-          f(i + lane_id() < k ? v.part_keys[(size_t)p * kMaxW + i + lane_id()] : kNoKey);
-      }
-    };
-    bound = kLow48;
-    if (want && tot > want) bound = select_bound(s_lds, want, kept);
-    kept([&](uint64_t key) {
-      if (key != kNoKey && (key & kLow48) <= bound) s_sel[atomicAdd(&s_n, 1u)] = key;
-    });
+    const uint32_t ex = block_exclusive_scan<uint32_t, kBlock>(all, s_lds.scan, &tot);
+    if ((int)threadIdx.x < parts) s_part.pre[threadIdx.x] = ex;
     __syncthreads();
+    select_keys(tot, want, s_lds, s_sel, &s_n, [&](uint32_t i) {
+      const int p = upper_index<uint32_t>(s_part.pre, 0, parts, i);
+      return v.part_keys[(size_t)p * kMaxW + (i - s_part.pre[p])];
+    });
     n = s_n;
   }
   for (uint32_t i = threadIdx.x; i < min(prev, w); i += kBlock) s_sel[n + i] = v.cand[i];

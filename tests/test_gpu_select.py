@@ -28,7 +28,7 @@ def check(g, queries, alpha=0.5):
                 assert got == exp, q
 
 
-@pytest.mark.parametrize("leaves", [255, 1024, 33 * 1024 + 5, 70_001])
+@pytest.mark.parametrize("leaves", [255, 1024, 4096, 4097, 33 * 1024 + 5, 70_001])
 def test_many_tied_central_nodes(leaves):
     """Every leaf of two hubs is a central node of the two hub keywords: one
     level's candidates, all with the same sum, spread over all scan workgroups
