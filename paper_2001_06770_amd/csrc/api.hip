@@ -1672,7 +1672,7 @@ int raks_destroy(raks_ctx* c) {
   free_view(c, c->base);
   DevBuf* bufs[] = {&c->row_ptr, &c->col, &c->label, &c->nw, &c->kw_nodes, &c->arc_src,
                     &c->rev, &c->cweight, &c->wstat, &c->lut, &c->row_ptr_o, &c->orig_id,
-                    &c->int_id, &c->node_tmp};
+                    &c->int_id, &c->num_tmp, &c->node_tmp};
   for (DevBuf* b : bufs) dev_free(c, *b);
   delete c;
   return RAKS_OK;
@@ -1722,51 +1722,37 @@ int raks_load_graph(raks_ctx* c, const raks_graph_desc* g) {
   c->alpha = g->alpha;
   std::vector<uint32_t> rp32(n + 1);
   for (int64_t v = 0; v <= n; ++v) rp32[v] = (uint32_t)g->row_ptr[v];
-  // internal numbering: nodes by degree, largest first, ties by original id
-  // (a counting sort), and the internal row starts
-  std::vector<int32_t> orig_id(n), int_id(n);
-  std::vector<uint32_t> rpi(n + 1);
-  {
-    int64_t maxd = 0;
-    for (int64_t v = 0; v < n; ++v) maxd = std::max(maxd, g->row_ptr[v + 1] - g->row_ptr[v]);
-    std::vector<int64_t> start((size_t)maxd + 1, 0);
-    for (int64_t v = 0; v < n; ++v) ++start[g->row_ptr[v + 1] - g->row_ptr[v]];
-    int64_t acc = 0;
-    for (int64_t d = maxd; d >= 0; --d) {
-      const int64_t k = start[d];
-      start[d] = acc;
-      acc += k;
-    }
-    for (int64_t v = 0; v < n; ++v) {
-      const int64_t u = start[g->row_ptr[v + 1] - g->row_ptr[v]]++;
-      orig_id[u] = (int32_t)v;
-      int_id[v] = (int32_t)u;
-    }
-    rpi[0] = 0;
-    // rows of the traversal copy's size classes (largest first)
-    c->n_big = c->n_top = c->n_mid = c->n_wave = 0;
-    for (int64_t u = 0; u < n; ++u) {
-      const uint32_t d = (uint32_t)(g->row_ptr[orig_id[u] + 1] - g->row_ptr[orig_id[u]]);
-      rpi[u + 1] = rpi[u] + d;
-      c->n_big += d > kBigRow;
-      c->n_top += d > kTopRow;
-      c->n_mid += d > kMidRow;
-      c->n_wave += d > kWaveRow;
-    }
-    c->big_arcs = rpi[c->n_big];
+  // rows of the traversal copy's size classes (the internal numbering puts the
+  // largest first), and the arcs of the largest
+  int64_t maxd = 0, big_arcs = 0;
+  int32_t n_big = 0, n_top = 0, n_mid = 0, n_wave = 0;
+  for (int64_t v = 0; v < n; ++v) {
+    const int64_t d = g->row_ptr[v + 1] - g->row_ptr[v];
+    maxd = std::max(maxd, d);
+    n_big += d > kBigRow;
+    n_top += d > kTopRow;
+    n_mid += d > kMidRow;
+    n_wave += d > kWaveRow;
+    big_arcs += d > kBigRow ? d : 0;
   }
+  c->n_big = n_big;
+  c->n_top = n_top;
+  c->n_mid = n_mid;
+  c->n_wave = n_wave;
+  c->big_arcs = (uint32_t)big_arcs;
   RAKS_TRY(dev_alloc(c, c->row_ptr, (n + 1) * 4));
   RAKS_TRY(dev_alloc(c, c->row_ptr_o, (n + 1) * 4));
   RAKS_TRY(dev_alloc(c, c->orig_id, n * 4));
   RAKS_TRY(dev_alloc(c, c->int_id, n * 4));
+  RAKS_TRY(dev_alloc(c, c->num_tmp, numbering_scratch(n)));
   RAKS_TRY(dev_alloc(c, c->col, std::max<int64_t>(A, 1) * 4));
   RAKS_TRY(dev_alloc(c, c->label, std::max<int64_t>(A, 1) * 2));
   drop_views(c);
   RAKS_TRY(dev_alloc(c, c->kw_nodes, std::max<int64_t>(nkw, 1) * 4));
   HIP_OK(hipMemcpyAsync(c->row_ptr_o.p, rp32.data(), (n + 1) * 4, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(c->row_ptr.p, rpi.data(), (n + 1) * 4, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(c->orig_id.p, orig_id.data(), n * 4, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(c->int_id.p, int_id.data(), n * 4, hipMemcpyHostToDevice, s));
+  launch_numbering(P<uint32_t>(c->row_ptr_o), (int32_t)n, (uint32_t)maxd, P<int32_t>(c->orig_id),
+                   P<int32_t>(c->int_id), P<uint32_t>(c->row_ptr), P<uint32_t>(c->num_tmp), s);
+  HIP_OK(hipGetLastError());
   if (A > 0) {
     HIP_OK(hipMemcpyAsync(c->col.p, g->col, A * 4, hipMemcpyHostToDevice, s));
     HIP_OK(hipMemcpyAsync(c->label.p, g->label, A * 2, hipMemcpyHostToDevice, s));

@@ -269,6 +269,11 @@ void launch_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp, const uint64_
 void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc_src, uint32_t* rev,
                             Status* st,
                             hipStream_t s);
+// Degree order of the nodes (n > 0): both id maps and the row starts in the new
+// order, from the original row starts; maxd: the largest degree.
+size_t numbering_scratch(int64_t n);
+void launch_numbering(const uint32_t* row_ptr_o, int32_t n, uint32_t maxd, int32_t* orig_id,
+                      int32_t* int_id, uint32_t* row_ptr, uint32_t* scratch, hipStream_t s);
 // Size classes of the traversal copy's rows (internal rows are in order of
 // degree): rows above 64 arcs take a wavefront each, above kMidRow a workgroup,
 // above kTopRow a large one, above kBigRow they are split into tiles of kBigTile

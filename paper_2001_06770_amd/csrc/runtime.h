@@ -175,6 +175,7 @@ struct Ctx {
   DevBuf row_ptr, col, label, nw, kw_nodes, arc_src;
   // internal (degree-ordered) node numbering: original row starts, both id maps
   DevBuf row_ptr_o, orig_id, int_id, node_tmp;
+  DevBuf num_tmp;        // counters of the numbering (load)
   // internal rows above kBigRow / kTopRow / kMidRow / kWaveRow arcs
   int32_t n_big = 0, n_top = 0, n_mid = 0, n_wave = 0;
   uint32_t big_arcs = 0;          // arcs of the first n_big rows
