@@ -128,9 +128,8 @@ struct CoCandView {
   int32_t C, end;                // central keywords, end level of the central run
   uint32_t* cnt;                 // [nblocks] last-level candidates per scan workgroup
   uint64_t* cand;                // their keys, at each scan workgroup's nodes
-  uint32_t* cursor;              // [1] earlier-level candidates placed; 0 between stages
+  uint32_t* cursor;              // [1] earlier-level candidates placed; the selection clears it
   uint64_t* early;               // [kMaxW] keys of earlier levels (fewer than w), in any order
-  RunStatus* st;                 // receives ncand_total / ncand_level for the selection
   const int32_t* orig_id;        // internal id -> original id (the keys' node ids)
 };
 
@@ -160,7 +159,7 @@ void launch_co_control(const CohortView& v, int level, uint64_t seq, hipStream_t
 void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int num_cu, int wpc,
                       int tile, hipStream_t s, hipEvent_t ev0 = nullptr,
                       hipEvent_t ev1 = nullptr);
-// CG selection input of slot q (two launches)
+// CG selection input of slot q
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s);
 // After slot q's CG recovery: its outcome to the host
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,
@@ -168,7 +167,7 @@ void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t s
 // In the level loop's stream: slot q's V_C is ready
 void launch_co_cg_ready(const CohortView& v, int q, const Status* gst, hipStream_t s);
 // Final marginal decision (Theorem 4 replayed up to the exploration's end)
-void launch_co_rpg_final(const CohortView& v, int q, hipStream_t s);
+void launch_co_rpg_final(const CohortView& v, int q, Status* gst, hipStream_t s);
 // D_j minima over V_C for every slot whose marginal run is checked (q < 0), or
 // for slot q alone; many workgroups, before the control step reads them
 void launch_co_dmin(const CohortView& v, int q, int grid, hipStream_t s);

@@ -15,8 +15,8 @@
 //   k_co_expand   Algorithm 1 over tiles of consecutive examined arcs, a
 //                 wavefront each, reading the staged entries in place; an arc is read once
 //                 for every query that expands its source node.
-// After a query's runs: its CG selection input (k_co_cand_*), the final
-// marginal decision (k_co_rpg_final) and its work counters (k_co_counters)
+// After a query's runs: its CG selection input (k_co_cand), the final
+// marginal decision (k_co_rpg_final) and its work counters (k_co_finish)
 // come from its final hitting levels; recovery, ranking and output are the
 // single-query kernels on views of its columns.
 #include <hip/hip_ext.h>
@@ -715,7 +715,8 @@ __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView
 // on the single path, with their number; the few of earlier levels go to a
 // list.  The rows' bytes bound it (a count, a prefix and a second pass that
 // wrote took 84 us beside the levels of 2M nodes and 3.9 ms beside those of
-// 50M; this one takes 35 us and 1.5 ms).
+// 50M; this one takes 35 us and 1.5 ms).  The selection sums the numbers up: a
+// launch of one workgroup for that took 13 us and 0.33 ms there.
 __global__ __launch_bounds__(kBlock) void k_co_cand(CoCandView cv, int32_t n, int32_t cpw) {
   __shared__ uint32_t s_red[kBlock / kWave + 1];
   const int64_t wg0 = (int64_t)blockIdx.x * cpw * kScanNodes;
@@ -752,20 +753,6 @@ __global__ __launch_bounds__(kBlock) void k_co_cand(CoCandView cv, int32_t n, in
     base += tot;
   }
   if (threadIdx.x == 0) cv.cnt[blockIdx.x] = base;
-}
-
-__global__ __launch_bounds__(kCtlT) void k_co_cand_sum(CoCandView cv, int32_t nb) {
-  __shared__ uint32_t s_m32[kCtlT / kWave + 1];
-  uint32_t sum = 0;
-  for (int b = threadIdx.x; b < nb; b += kCtlT) sum += cv.cnt[b];
-  const uint32_t tot = block_sum<uint32_t, kCtlT>(sum, s_m32);
-  if (threadIdx.x == 0) {
-    RunStatus st = {};
-    st.ncand_total = cv.cursor[0] + tot;
-    st.ncand_level = tot;
-    *cv.st = st;
-    cv.cursor[0] = 0;
-  }
 }
 
 // The outcome of slot q's CG stage, for the host.
@@ -818,8 +805,9 @@ __global__ __launch_bounds__(kBlock) void k_co_dmin(CohortView v, int only) {
 
 // The marginal run's end: decided already by a control step (Theorem 4 or
 // every CG with an RPG), or replayed here up to where the exploration ended
-// (the level before an empty frontier, or the level bound).
-__global__ __launch_bounds__(kCtlT) void k_co_rpg_final(CohortView v, int q) {
+// (the level before an empty frontier, or the level bound).  The lane's run
+// status follows: levels, end reasons, CG count; k_co_finish adds the counters.
+__global__ __launch_bounds__(kCtlT) void k_co_rpg_final(CohortView v, int q, Status* gst) {
   __shared__ CoSlot s;
   __shared__ int32_t s_go;
   if (threadIdx.x == 0) {
@@ -843,28 +831,24 @@ __global__ __launch_bounds__(kCtlT) void k_co_rpg_final(CohortView v, int q) {
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) v.slots[q] = s;
-}
-
-// The lane's run status from the slot: levels, end reasons, CG count; the
-// counters are added by k_co_counters.
-__global__ void k_co_post_init(const CoSlot* slot, Status* gst) {
-  const CoSlot s = *slot;
-  RunStatus a = {}, b = {};
-  a.end_level = s.c_end;
-  a.end_reason = s.c_reason;
-  a.levels = s.c_end + 1;
-  a.ncand_total = s.ncand;
-  if (s.m_end >= 0) {
-    b.end_level = s.m_end;
-    b.end_reason = s.m_reason;
-    b.levels = s.m_end + 1;
-  } else {
-    b.end_level = -1;
-    b.end_reason = END_NONE;
+  if (threadIdx.x == 0) {
+    v.slots[q] = s;
+    RunStatus a = {}, b = {};
+    a.end_level = s.c_end;
+    a.end_reason = s.c_reason;
+    a.levels = s.c_end + 1;
+    a.ncand_total = s.ncand;
+    if (s.m_end >= 0) {
+      b.end_level = s.m_end;
+      b.end_reason = s.m_reason;
+      b.levels = s.m_end + 1;
+    } else {
+      b.end_level = -1;
+      b.end_reason = END_NONE;
+    }
+    gst->run[0] = a;
+    gst->run[1] = b;
   }
-  gst->run[0] = a;
-  gst->run[1] = b;
 }
 
 // The work counters of both runs at every node, from its final hitting levels
@@ -1078,7 +1062,6 @@ void launch_co_expand(const CohortView& v, const DevGraphView& g, int level, int
 
 void launch_co_cand(const CoCandView& cv, const CohortView& v, hipStream_t s) {
   k_co_cand<<<v.nblocks, kBlock, 0, s>>>(cv, v.n, v.cpw);
-  k_co_cand_sum<<<1, kCtlT, 0, s>>>(cv, v.nblocks);
 }
 
 void launch_co_cg_done(const CohortView& v, int q, const Status* gst, uint64_t seq,
@@ -1094,12 +1077,11 @@ void launch_co_dmin(const CohortView& v, int q, int grid, hipStream_t s) {
   k_co_dmin<<<grid, kBlock, 0, s>>>(v, q);
 }
 
-void launch_co_rpg_final(const CohortView& v, int q, hipStream_t s) {
-  k_co_rpg_final<<<1, kCtlT, 0, s>>>(v, q);
+void launch_co_rpg_final(const CohortView& v, int q, Status* gst, hipStream_t s) {
+  k_co_rpg_final<<<1, kCtlT, 0, s>>>(v, q, gst);
 }
 
 void launch_co_finish(const CoFinishView& fv, const DevGraphView& g, hipStream_t s) {
-  k_co_post_init<<<1, 1, 0, s>>>(fv.slot, fv.gst);
   const unsigned grid = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>(768, ((int64_t)fv.n_pad + kFinT - 1) / kFinT));
   if (fv.TPq == 4) k_co_finish<1><<<grid, kFinT, 0, s>>>(fv, g);

@@ -87,7 +87,7 @@ struct Engine {
   hipStream_t cg_stream = nullptr;
   hipEvent_t lvl_ev[kCoMirrors] = {};   // level l's control step is done (slot l % kCoMirrors)
   CohortView v = {};
-  DevBuf H, R, slots, acc, tot, tpre, wtot, stage, cand, ccnt, cearly, ccur, cst, csel, dmin;
+  DevBuf H, R, slots, acc, tot, tpre, wtot, stage, cand, ccnt, cearly, ccur, csel, dmin;
   bool any_vc = false;   // some slot's marginal run is checked (V_C ready): minima each level
   CoMirror* h_mir = nullptr;
   CoMirror* d_mir = nullptr;
@@ -139,7 +139,6 @@ int engine_alloc(Engine& E) {
   RAKS_TRY(dev_alloc(c, E.ccnt, (size_t)nb * 4));
   RAKS_TRY(dev_alloc(c, E.cearly, (size_t)kMaxW * 8));
   RAKS_TRY(dev_alloc(c, E.ccur, 16));
-  RAKS_TRY(dev_alloc(c, E.cst, sizeof(RunStatus)));
   RAKS_TRY(dev_alloc(c, E.csel, (size_t)kSelParts * (kMaxW * 8 + 4)));
   RAKS_TRY(dev_alloc(c, E.dmin, (size_t)kCoSlots * kMaxW * kMaxKw * 4));
   if (!E.h_mir) {
@@ -210,7 +209,7 @@ int engine_create(Ctx* c, Engine** out) {
   if (!rc) rc = engine_alloc(*E);
   if (rc) {
     for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->tpre, &E->wtot, &E->stage,
-                      &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
+                      &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->csel, &E->dmin})
       dev_free(c, *b);
     if (E->h_mir) (void)hipHostFree(E->h_mir);
     drop_streams(*E);
@@ -540,7 +539,6 @@ int enqueue_cg(Engine& E, CoQuery* q) {
   cv.cand = P<uint64_t>(E.cand);
   cv.cursor = P<uint32_t>(E.ccur);
   cv.early = P<uint64_t>(E.cearly);
-  cv.st = P<RunStatus>(E.cst);
   cv.orig_id = P<int32_t>(c->orig_id);
   launch_co_cand(cv, E.v, s);
   SelectView sv = {};
@@ -548,12 +546,11 @@ int enqueue_cg(Engine& E, CoQuery* q) {
   sv.cand = P<uint64_t>(E.cearly);
   sv.ncand = P<uint32_t>(E.ccnt);
   sv.s_cand = P<uint64_t>(E.cand);
-  sv.always_staged = 1;
+  sv.n_early = P<uint32_t>(E.ccur);
   sv.nblocks = E.v.nblocks;
   sv.cpw = E.v.cpw;
   sv.part_keys = P<uint64_t>(E.csel);
   sv.part_n = reinterpret_cast<uint32_t*>(sv.part_keys + (size_t)kSelParts * kMaxW);
-  sv.st = P<RunStatus>(E.cst);
   sv.gst = st;
   sv.w = q->p.w;
   sv.sel_node = P<int32_t>(L->sel_node);
@@ -652,7 +649,7 @@ int poll_cg(Engine& E) {
     // which no level kernel reads or writes any more); slot and columns are
     // free once that is done
     if (q->p.M > 0) launch_co_dmin(E.v, q->slot, E.c->num_cu * 4, E.stream);
-    launch_co_rpg_final(E.v, q->slot, E.stream);
+    launch_co_rpg_final(E.v, q->slot, P<Status>(q->L->status), E.stream);
     q->fin = take_event(E);
     if (!q->fin) return fail(RAKS_EDEVICE, "event creation failed");
     HIP_OK(hipEventRecord(q->fin, E.stream));
@@ -931,7 +928,7 @@ void cohort_destroy(Ctx* c) {
   (void)hipStreamSynchronize(E->stream);
   (void)hipStreamSynchronize(E->cg_stream);
   for (DevBuf* b : {&E->H, &E->R, &E->slots, &E->acc, &E->tot, &E->tpre, &E->wtot, &E->stage,
-                    &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->cst, &E->csel, &E->dmin})
+                    &E->cand, &E->ccnt, &E->cearly, &E->ccur, &E->csel, &E->dmin})
     dev_free(c, *b);
   for (hipEvent_t e : E->ev_pool) (void)hipEventDestroy(e);
   for (hipEvent_t e : E->tev_pool) (void)hipEventDestroy(e);

@@ -954,23 +954,34 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
   __shared__ SelLds s_lds;
   __shared__ SelPart s_part;
   __shared__ uint32_t s_n, s_last;
-  const RunStatus* st = v.st;
-  const uint32_t total = st->ncand_total, last = st->ncand_level;
-  const uint32_t prev = total - last;
   const uint32_t w = (uint32_t)v.w;
+  // keys of earlier levels and of the last one
+  uint32_t prev, last = 0;
+  bool staged = true;
+  if (v.n_early) {
+    prev = *v.n_early;
+  } else {
+    const uint32_t total = v.st->ncand_total;
+    last = v.st->ncand_level;
+    prev = total - last;
+    staged = v.ncand && total >= w;
+  }
   const uint32_t want = w - min(w, prev);   // slots for the last level
-  const bool staged = v.ncand && (v.always_staged || total >= w);
   const int parts = gridDim.x, part = blockIdx.x;
+  const int per = (v.nblocks + kBlock - 1) / kBlock;
+  const int g0 = min(v.nblocks, (int)threadIdx.x * per), g1 = min(v.nblocks, g0 + per);
+  uint32_t at = 0;
+  if (staged) {
+    uint32_t sum = 0, tot;
+    for (int b = g0; b < g1; ++b) sum += v.ncand[b];
+    at = block_exclusive_scan<uint32_t, kBlock>(sum, s_lds.scan, &tot);
+    last = tot;
+  }
   // the part's keys: [lo, hi) of the last level's
   const uint32_t lo = (staged ? 0u : prev) + (uint32_t)((uint64_t)last * part / parts);
   const uint32_t hi = (staged ? 0u : prev) + (uint32_t)((uint64_t)last * (part + 1) / parts);
   if (staged) {
-    const int per = (v.nblocks + kBlock - 1) / kBlock;
-    const int b0 = min(v.nblocks, (int)threadIdx.x * per), b1 = min(v.nblocks, b0 + per);
-    uint32_t sum = 0, tot;
-    for (int b = b0; b < b1; ++b) sum += v.ncand[b];
-    uint32_t at = block_exclusive_scan<uint32_t, kBlock>(sum, s_lds.scan, &tot);
-    for (int b = b0; b < b1; ++b) {
+    for (int b = g0; b < g1; ++b) {
       s_part.pre[b] = at;
       const uint32_t n = v.ncand[b];
       if (lo < hi && lo >= at && lo < at + n) s_part.b0 = b;
@@ -1020,7 +1031,10 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectView v) {
     v.sel_sc[rank] = (int32_t)(key >> 48);
     v.sel_sumh[rank] = (int32_t)((key >> 32) & 0xFFFF);
   }
-  if (threadIdx.x == 0) v.gst->nsel = (int32_t)nsel;
+  if (threadIdx.x == 0) {
+    v.gst->nsel = (int32_t)nsel;
+    if (v.n_early) *v.n_early = 0;   // every part has read it
+  }
 }
 
 // Ranking of the results: RPGs by (key, S^c, CG rank); without marginal

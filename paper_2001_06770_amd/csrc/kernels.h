@@ -105,11 +105,11 @@ constexpr int kSelParts = 64;   // workgroups of the selection, at most
 struct SelectView {
   const int32_t* int_id;    // original id (in the keys) -> internal id
   const uint64_t* cand;     // keys: earlier levels first, then the last level's
-  // with `ncand`, and w central nodes or more (or always_staged), the last
-  // level's keys are where the scan workgroups staged them
+  // with `ncand`, and w central nodes or more (or n_early), the last level's
+  // keys are where the scan workgroups staged them
   const uint32_t* ncand;
   const uint64_t* s_cand;
-  int32_t always_staged;
+  uint32_t* n_early;        // cohort: keys of earlier levels (st is not read); left at 0
   int32_t nblocks, cpw;     // scan workgroups; nblocks also sets the launch's size
   uint64_t* part_keys;      // scratch [kSelParts][kMaxW], part_n [kSelParts]
   uint32_t* part_n;
