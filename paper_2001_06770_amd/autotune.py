@@ -6,8 +6,10 @@ path's parameters and keeps the fastest:
 * ``admit_below`` -- a batch admits waiting queries only while at most this
   many of the cohort's queries are still exploring (0: level-aligned waves,
   32: whenever a query fits);
-* ``expand_tile`` -- examined arcs per expansion tile (512, 1024, 2048);
-* ``expand_wg_per_cu`` -- workgroups per compute unit of the expansion;
+* ``expand_tile`` -- examined arcs that a wavefront of the expansion takes at a
+  time (512, 1024, 2048);
+* ``expand_wg_per_cu`` -- workgroups per compute unit of the expansion (at most
+  what fits);
 * ``cohort_cols`` -- columns of the cohort (16, 32, 64): fewer queries at once,
   with smaller per-node reached masks for the expansion's gathers.
 

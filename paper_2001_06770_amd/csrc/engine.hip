@@ -9,9 +9,10 @@
 //   level       scan, control, expansion for every slot; level l+1 is
 //               enqueued before the host reads level l's status (pinned);
 //   CG stage    when a query's central run has ended: its CG selection,
-//               recovery (Algorithm 2) and V_C on the cohort stream, so its
-//               marginal run's RPG check can start (the control step replays
-//               the levels it missed);
+//               recovery (Algorithm 2) and V_C on the CG stream, beside the
+//               next levels, so its marginal run's RPG check can start (from
+//               the level queued after the host has seen the outcome; the
+//               control step replays the levels it missed);
 //   hand-off    when both runs have ended and the CG stage succeeded, a post
 //               worker finishes the query on its lane's stream: final
 //               marginal decision, counters, ranking, RPG recovery, output,
@@ -301,7 +302,7 @@ uint8_t* seg_ptr(Engine& E, int seg, int c0) {
   return E.v.H + (size_t)seg * E.v.n_pad * 16 + c0;
 }
 
-// Borrows the cohort stream for the lane's helper calls (allocation layout
+// Borrows a stream of the engine for the lane's helper calls (allocation layout
 // uploads, recovery, selection) so that they are ordered with the level loop.
 struct Borrow {
   Lane* L;
