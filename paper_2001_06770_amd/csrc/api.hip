@@ -140,7 +140,7 @@ DevGraphView graph_view(const Lane* L) { return graph_view(L->ctx, *L->view); }
 std::vector<DevBuf*> lane_buffers(Lane* L) {
   std::vector<DevBuf*> v = {
       &L->Hc, &L->Hm, &L->Hq, &L->R, &L->tot, &L->brief, &L->cand, &L->s_item, &L->s_cand, &L->sel_node, &L->sel_sc,
-      &L->sel_sumh, &L->has_rpg, &L->sm, &L->key, &L->dmin, &L->ranked, &L->vc_cnt,
+      &L->sel_sumh, &L->has_rpg, &L->sm, &L->key, &L->dmin, &L->rpg_dm, &L->ranked, &L->vc_cnt,
       &L->vc_tmp, &L->vc_off, &L->vc_nodes, &L->hpool, &L->nl, &L->al, &L->items, &L->sort_a,
       &L->sort_b, &L->cg_nodes, &L->cg_arcs, &L->cg_cnt, &L->hdr, &L->out_nodes, &L->out_arcs,
       &L->mid, &L->bigf, &L->big_bm, &L->big_chunk, &L->big_slot};
@@ -567,6 +567,7 @@ int ensure_node_buffers(Lane* L) {
   RAKS_TRY(dev_alloc(c, L->cand, (size_t)kMaxW * 8));
   RAKS_TRY(dev_alloc(c, L->s_item, np * 16));
   RAKS_TRY(dev_alloc(c, L->s_cand, np * 8));
+  RAKS_TRY(dev_alloc(c, L->rpg_dm, ((size_t)kMaxW * kMaxKw + 1) * 4));
   return ensure_small_buffers(L);
 }
 
@@ -617,6 +618,9 @@ RunView run_view(Lane* L, int kind, int T, DevBuf& H, const QueryPlan& p) {
   r.sm = P<int32_t>(L->sm);
   r.key = P<int64_t>(L->key);
   r.dmin = P<uint8_t>(L->dmin);
+  r.rpg_groups = std::min(kRpgGroups, L->nblocks);
+  r.rpg_dm = P<uint32_t>(L->rpg_dm);
+  r.rpg_ticket = r.rpg_dm + kMaxW * kMaxKw;
   return r;
 }
 

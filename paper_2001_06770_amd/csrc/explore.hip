@@ -7,9 +7,10 @@
 //                   them, inspects every frontier node once (complete row ->
 //                   central node / PTC block, keywords with h <= level, level
 //                   slice of the row), stages its expansion entry and
-//                   central-node key in node order in its own range and
+//                   central-node key in its own range (in the order in which its
+//                   wavefronts reserve places, arc prefixes ascending) and
 //                   refreshes its reached mask; then writes its totals.  In a
-//                   marginal run one more workgroup checks the RPGs beside it
+//                   marginal run further workgroups check the RPGs beside it
 //                   (the check over each CG's V_C rows and Theorem 4 need
 //                   nothing of the scan);
 //   k_expand        Algorithm 1 for every (frontier, arc) pair, balanced by
@@ -96,6 +97,8 @@ struct InitView {
   int32_t* has_rpg;
   int32_t* sm;
   int64_t* key;
+  uint32_t* rpg_dm;      // [kMaxW][kMaxKw], null without a marginal run
+  uint32_t* rpg_ticket;
 };
 
 // Everything a query starts from, for both runs, in one launch (they were
@@ -117,6 +120,10 @@ __global__ __launch_bounds__(kBlock) void k_query_init(InitView v) {
     v.has_rpg[i] = 0;
     v.sm[i] = 0;
     v.key[i] = 0;
+  }
+  if (v.rpg_dm) {
+    for (int i = threadIdx.x; i < kMaxW * kMaxKw; i += kBlock) v.rpg_dm[i] = kInf;
+    if (threadIdx.x == 0) *v.rpg_ticket = 0;
   }
   if (threadIdx.x < 2 && (threadIdx.x == 1 || v.central)) {
     RunStatus s = {};
@@ -216,7 +223,7 @@ __host__ __device__ inline size_t rpg_lds_bytes(int w, int M) {
 }
 
 template <int TP>
-__device__ void rpg_check(const RunView& r, int level, int64_t* lds);
+__device__ void rpg_check(const RunView& r, int group, int64_t* lds);
 
 // Every workgroup takes cpw consecutive chunks of kScanNodes nodes; a wavefront
 // takes 256 consecutive nodes of a chunk, kScanPer per lane 64 apart, so that
@@ -244,11 +251,11 @@ __global__ __launch_bounds__(kBlock, TP == 4 ? 8 : (TP == 8 ? 6 : 5)) void k_fro
   if (level > r.st->end_level) return;
   int wg = blockIdx.x;
   if constexpr (!Central) {
-    if (wg == 0) {
-      rpg_check<TP>(r, level, s_dyn);
+    if (wg < r.rpg_groups) {
+      rpg_check<TP>(r, wg, s_dyn);
       return;
     }
-    --wg;
+    wg -= r.rpg_groups;
   }
   __shared__ uint64_t s_sum[(kBlock / kWave + 1) * 5];
   __shared__ unsigned long long s_res;   // entries << 32 | arcs reserved so far
@@ -384,11 +391,21 @@ __global__ __launch_bounds__(kBlock, TP == 4 ? 8 : (TP == 8 ? 6 : 5)) void k_fro
 // (Eq. 6 scaled by gamma_den).  Then the stop rules: every CG has an RPG, or
 // Theorem 4 with the k-th RPG in (key, S^c, CG rank) order.
 //
-// One workgroup beside the scan of level `level`: the hitting levels up to
-// `level` are all written.  Without frontier nodes nothing changed since the
-// last level's check, so its answer does not depend on the scan's either.
+// Workgroups beside the scan of the level: the hitting levels up to it are all
+// written.  Without frontier nodes nothing changed since the last level's check,
+// so its answer does not depend on the scan's either.
+//
+// The V_C rows' random gathers bound it.  Up to kRpgRows rows are the first
+// workgroup's alone; more are split over the others, whose minima join in device
+// memory (levels never change once written, so they only fall from level to
+// level), and the last one to finish applies the rules.  The expansion waits for
+// it: with 800k V_C nodes a marginal level took 1.58 ms with one workgroup of 1024
+// threads, 1.84 ms with one of 256, 0.10 ms so.
+constexpr uint32_t kRpgRows = 16 * kBlock;
+
 template <int TP>
-__device__ void rpg_check(const RunView& r, int level, int64_t* lds) {
+__device__ void rpg_check(const RunView& r, int group, int64_t* lds) {
+  constexpr int kAtOnce = 4;   // rows in flight per thread
   const int M = r.T;
   int64_t* s_key = lds;                                        // [w]
   uint32_t* s_dm = reinterpret_cast<uint32_t*>(s_key + r.w);   // [w][M]
@@ -396,7 +413,10 @@ __device__ void rpg_check(const RunView& r, int level, int64_t* lds) {
   int32_t* s_sm = s_has + r.w;
   int32_t* s_sc = s_sm + r.w;
   uint32_t* s_vc = reinterpret_cast<uint32_t*>(s_sc + r.w);    // [w + 1]
-  __shared__ int32_t s_nrpg, s_kth, s_minsc, s_stop, s_max;
+  __shared__ int32_t s_nrpg, s_kth, s_minsc, s_stop, s_max, s_last;
+  // the V_C lists do not change during the run: every workgroup gets the same number
+  auto groups_for = [&](uint32_t rows) { return min((uint32_t)r.rpg_groups, (rows + kRpgRows - 1) / kRpgRows); };
+  if (group > 0 && (uint32_t)group >= groups_for(r.vc_off[*r.nsel])) return;
   // everything the check reads in one round of loads: entries past nsel are
   // unset or stale and not used
   for (int i = threadIdx.x; i < r.w; i += kBlock) {
@@ -410,17 +430,44 @@ __device__ void rpg_check(const RunView& r, int level, int64_t* lds) {
   __syncthreads();
   // D_j of every CG without an RPG: minimum over its V_C rows
   const uint32_t total = s_vc[nsel];
-  for (uint32_t p = threadIdx.x; p < total; p += kBlock) {
-    const int32_t node = r.vc_nodes[p];
-    const int rr = upper_index<uint32_t>(s_vc, 0, nsel + 1, p);
-    if (s_has[rr]) continue;
-    uint8_t b[TP];
-    load_row<TP>(r.H, node, b);
+  const uint32_t groups = max(1u, groups_for(total));
+  const uint32_t p0 = (uint32_t)((uint64_t)total * group / groups);
+  const uint32_t p1 = (uint32_t)((uint64_t)total * (group + 1) / groups);
+  for (uint32_t p = p0 + threadIdx.x; p < p1; p += kAtOnce * kBlock) {
+    int32_t node[kAtOnce];
+    int rr[kAtOnce];
+    uint8_t b[kAtOnce][TP];
 #pragma unroll
-    for (int j = 0; j < TP; ++j)
-      if (j < M && b[j] != kInf) atomicMin(&s_dm[rr * M + j], (uint32_t)b[j]);
+    for (int k = 0; k < kAtOnce; ++k) node[k] = p + k * kBlock < p1 ? r.vc_nodes[p + k * kBlock] : -1;
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      rr[k] = node[k] >= 0 ? upper_index<uint32_t>(s_vc, 0, nsel + 1, p + k * kBlock) : 0;
+      if (s_has[rr[k]]) node[k] = -1;
+      if (node[k] >= 0) load_row<TP>(r.H, node[k], b[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      if (node[k] < 0) continue;
+#pragma unroll
+      for (int j = 0; j < TP; ++j)   // (INF: never below)
+        if (j < M && b[k][j] < s_dm[rr[k] * M + j]) atomicMin(&s_dm[rr[k] * M + j], (uint32_t)b[k][j]);
+    }
   }
   __syncthreads();
+  if (groups > 1) {
+    for (int i = threadIdx.x; i < nsel * M; i += kBlock)
+      if (s_dm[i] != kInf) atomicMin(&r.rpg_dm[i], s_dm[i]);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(r.rpg_ticket, 1u) == groups - 1;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    if (threadIdx.x == 0) *r.rpg_ticket = 0;
+    for (int i = threadIdx.x; i < nsel * M; i += kBlock)
+      s_dm[i] = __hip_atomic_load(&r.rpg_dm[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+  }
   for (int rr = threadIdx.x; rr < nsel; rr += kBlock) {
     if (!s_has[rr]) {
       bool all = true;
@@ -1153,6 +1200,8 @@ void launch_query_init(Status* gst, const RunView& c, int TPc, const SeedList& s
   v.has_rpg = c.has_rpg;
   v.sm = c.sm;
   v.key = c.key;
+  v.rpg_dm = m.rpg_dm;
+  v.rpg_ticket = m.rpg_ticket;
   uint64_t words = 0;
   for (int k = 0; k < 2; ++k) {
     const RunView& r = k ? m : c;
@@ -1181,8 +1230,8 @@ void launch_front_scan(const RunView& r, int TP, const DevGraphView& g, int leve
                      else k_front_scan<kTP, true, false><<<r.nblocks, kBlock, 0, s>>>(r, g, level));
   } else {
     const size_t lds = rpg_lds_bytes(r.w, r.T);
-    RAKS_TP_DISPATCH(TP, if (in) k_front_scan<kTP, false, true><<<r.nblocks + 1, kBlock, lds, s>>>(r, g, level);
-                     else k_front_scan<kTP, false, false><<<r.nblocks + 1, kBlock, lds, s>>>(r, g, level));
+    RAKS_TP_DISPATCH(TP, if (in) k_front_scan<kTP, false, true><<<r.nblocks + r.rpg_groups, kBlock, lds, s>>>(r, g, level);
+                     else k_front_scan<kTP, false, false><<<r.nblocks + r.rpg_groups, kBlock, lds, s>>>(r, g, level));
   }
 }
 

@@ -49,6 +49,7 @@ __device__ inline uint32_t count_le(const DevGraphView& g, int32_t v, int x) {
   return a - rs;
 }
 
+constexpr int kRpgGroups = 64;                // workgroups of the RPG check, at most
 constexpr uint32_t kHasFront = 0x80000000u;   // RunView::brief: the workgroup has frontier nodes
 
 // State of one exploration run (Section 4.2), laid out for one query.
@@ -88,6 +89,9 @@ struct RunView {
   int32_t* sm;               // [nsel]
   int64_t* key;              // [nsel]
   uint8_t* dmin;             // [nsel][kMaxKw]
+  int32_t rpg_groups;        // workgroups of the RPG check at most
+  uint32_t* rpg_dm;          // [nsel][T] D_j so far, where several of them check (k_query_init: INF)
+  uint32_t* rpg_ticket;      // of them, done; 0 between levels
 };
 
 // Bits per node of a run's reached masks with rows of TP bytes.

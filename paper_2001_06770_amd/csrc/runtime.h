@@ -91,7 +91,7 @@ struct Lane {
 
   int32_t n_pad = 0, nblocks = 0, cpw = 1;
   DevBuf Hc, Hm, R, tot, brief, cand, s_item, s_cand;
-  DevBuf sel_node, sel_sc, sel_sumh, has_rpg, sm, key, dmin, ranked;
+  DevBuf sel_node, sel_sc, sel_sumh, has_rpg, sm, key, dmin, ranked, rpg_dm;
   DevBuf vc_cnt, vc_tmp, vc_off, vc_nodes;
   // recovery storage, shared by both phases (sized for the larger one)
   DevBuf hpool, nl, al, items, sort_a, sort_b;
