@@ -331,9 +331,11 @@ int check_graph(Ctx* c, Lane* L) {
                          st, s);
   HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  // some arc is nobody's reverse
-  if (!L->h_status->err && 2 * L->h_status->pairs != c->A) L->h_status->err = 8;
-  if (L->h_status->err) {
+  // (the second: some arc is nobody's reverse)
+  if (L->h_status->err || 2 * L->h_status->pairs != c->A) {
+    launch_missing_reverse(g, st, s);
+    HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
     char msg[160];
     snprintf(msg, sizeof msg,
              "graph violates the input contract (bits 0x%x: 1 col range, 2 self-loop, "

@@ -234,7 +234,6 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
       const int32_t j = col[e];
       const uint16_t lab = label[e];
       if (j < 0 || j >= n) { err |= 1; continue; }
-      if ((uint32_t)j == i) { err |= 2; continue; }
       const uint32_t lo = row_ptr[i], hi = row_ptr[i + 1];
       const uint32_t jlo = row_ptr[j], jhi = row_ptr[j + 1];
       if (e > lo) {
@@ -242,6 +241,7 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
         const int32_t pc = col[e - 1];
         if (pl > lab || (pl == lab && pc >= j)) err |= 4;
       }
+      if ((uint32_t)j == i) { err |= 2; continue; }
       if (jhi - jlo > hi - lo || (jhi - jlo == hi - lo && (uint32_t)j > i)) continue;
       ++found;
       const uint32_t r = find_arc_dev(jlo, jhi, col, label, lab, (int32_t)i);
@@ -289,6 +289,22 @@ __global__ __launch_bounds__(kBlock) void k_check_and_count(const uint32_t* row_
     if (s_min < *(volatile uint64_t*)&st->cmin) atomicMin((unsigned long long*)&st->cmin, s_min);
     if (s_max > *(volatile uint64_t*)&st->cmax) atomicMax((unsigned long long*)&st->cmax, s_max);
   }
+}
+
+// For the message on a graph that breaks the contract: a search from every arc,
+// since those above do not tell whose reverse is missing beside other faults.
+__global__ __launch_bounds__(kBlock) void k_missing_reverse(const uint32_t* row_ptr,
+                                                            const int32_t* col,
+                                                            const uint16_t* label, int32_t n,
+                                                            uint32_t A, const int32_t* arc_src,
+                                                            Status* st) {
+  bool missing = false;
+  for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < A; e += (uint64_t)gridDim.x * kBlock) {
+    const int32_t j = col[e];
+    if (j < 0 || j >= n) continue;
+    missing |= find_arc_dev(row_ptr[j], row_ptr[j + 1], col, label, label[e], arc_src[e]) == kEmpty;
+  }
+  if (__syncthreads_or((int)missing) && threadIdx.x == 0) atomicOr(&st->err, 8);
 }
 
 __global__ __launch_bounds__(kBlock) void k_node_weight_range(const uint8_t* nw, int32_t n,
@@ -736,6 +752,11 @@ void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc
   else if (g.A > 0)
     k_check_and_count<4 * kBlock><<<grid_for((g.A - 1) / 4 + 1), kBlock, 0, s>>>(
         g.row_ptr_o, g.col, g.label, g.n, g.A, c_tmp, arc_src, rev, st);
+}
+
+void launch_missing_reverse(const DevGraphView& g, Status* st, hipStream_t s) {
+  if (g.A > 0)
+    k_missing_reverse<<<grid_for(g.A), kBlock, 0, s>>>(g.row_ptr_o, g.col, g.label, g.n, g.A, g.arc_src, st);
 }
 
 void launch_node_weight_range(const DevGraphView& g, const uint8_t* nw, Status* st,

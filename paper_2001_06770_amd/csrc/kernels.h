@@ -273,6 +273,8 @@ void launch_pack_vc(const uint32_t* vc_cnt, const int32_t* vc_tmp, const uint64_
 void launch_check_and_count(const DevGraphView& g, uint32_t* c_tmp, int32_t* arc_src, uint32_t* rev,
                             Status* st,
                             hipStream_t s);
+// st->err gets bit 8 if some arc has no reverse (after launch_check_and_count)
+void launch_missing_reverse(const DevGraphView& g, Status* st, hipStream_t s);
 // Degree order of the nodes (n > 0): both id maps and the row starts in the new
 // order, from the original row starts; maxd: the largest degree.
 size_t numbering_scratch(int64_t n);
