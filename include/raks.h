@@ -251,8 +251,9 @@ int raks_query(raks_ctx* ctx, const raks_query_desc* q, raks_results** out);
  * with a positive capacity, cap_results < k or an invalid query;
  * RAKS_ESTATE while serving runs, without a graph, or when the levels of the
  * query's alpha have not been built (a raks_query with that alpha builds
- * them); RAKS_ENOMEM when the query's device state would exceed the 256 MiB
- * (graphs of up to about 3M nodes fit), or when the results do not fit the
+ * them); RAKS_ENOMEM when the graph is beyond the 256 MiB (at 50 bytes per node
+ * and per run 4, 8 or 16 for the levels of up to as many keywords: from about
+ * 4.6M nodes on) or what the query recovers is, or when the results do not fit the
  * caller's arrays (then out->n_nodes / n_arcs give the sizes needed and out->n
  * is 0).  Event timing (raks_set_timing) does not cover this lane. */
 int raks_query_noalloc(raks_ctx* ctx, const raks_query_desc* q, raks_results_buf* out);

@@ -1427,6 +1427,16 @@ int query_plan_on_lane(Lane* L, const QueryPlan& p, raks_results** out, raks_res
                        double t0) {
   Ctx* c = L->ctx;
   auto gather = [&](int* ovf) { return buf ? collect_into(L, p, buf, ovf) : collect(L, p, out, ovf); };
+  if (L->no_alloc) {
+    // the graphs that the allocation-free entry point takes: a limit of their own,
+    // above what the lane's node buffers hold, that does not move with them
+    const size_t np = ((size_t)c->n + kScanNodes - 1) / kScanNodes * kScanNodes;
+    const size_t need = np * (kNoallocNode + p.TPc + (p.M > 0 ? p.TPm : 0));
+    if (need > c->na_scratch_bytes)
+      return fail(RAKS_ENOMEM, "allocation-free query: a graph of " + std::to_string(c->n) +
+                                   " nodes is beyond the " +
+                                   std::to_string(c->na_scratch_bytes >> 20) + " MiB scratch");
+  }
   RAKS_TRY(ensure_node_buffers(L));
   RAKS_TRY(dev_alloc(c, L->Hc, (size_t)L->n_pad * p.TPc));
   if (p.M > 0) RAKS_TRY(dev_alloc(c, L->Hm, (size_t)L->n_pad * p.TPm));

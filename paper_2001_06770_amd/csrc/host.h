@@ -37,6 +37,8 @@ struct Arena {
   size_t cap = 0, used = 0;
 };
 extern thread_local Arena* g_arena;
+// Bytes per node, beside the hitting levels, by which graphs are taken for it.
+constexpr size_t kNoallocNode = 50;
 
 int dev_alloc(Ctx* c, DevBuf& b, size_t bytes);
 void dev_free(Ctx* c, DevBuf& b);

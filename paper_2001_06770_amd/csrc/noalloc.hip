@@ -175,10 +175,6 @@ extern "C" int raks_query_noalloc(raks_ctx* c, const raks_query_desc* q, raks_re
   Arena a;
   a.base = static_cast<uint8_t*>(c->na_scratch);
   a.cap = c->na_scratch_bytes;
-  // the graphs this entry point takes are those whose node buffers fit at 50
-  // bytes per node beside the hitting levels; the lane's take 28
-  const size_t np = ((size_t)c->n + kScanNodes - 1) / kScanNodes * kScanNodes;
-  a.used = std::min(a.cap, (size_t)21 * np & ~size_t(255));
   int rc;
   {
     ArenaScope scope(&a);
