@@ -329,11 +329,13 @@ int check_graph(Ctx* c, Lane* L) {
   const DevGraphView g = graph_view(c, c->base);
   launch_check_and_count(g, P<uint32_t>(c->cweight), P<int32_t>(c->arc_src), P<uint32_t>(c->rev),
                          st, s);
+  HIP_OK(hipGetLastError());
   HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
   // (the second: some arc is nobody's reverse)
   if (L->h_status->err || 2 * L->h_status->pairs != c->A) {
     launch_missing_reverse(g, st, s);
+    HIP_OK(hipGetLastError());
     HIP_OK(hipMemcpyAsync(L->h_status, st, sizeof(Status), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     char msg[160];
