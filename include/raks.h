@@ -287,7 +287,7 @@ int raks_set_batch_mode(raks_ctx* ctx, int32_t mode);
 
 /* Tuning of the cohort path (chosen per workload by the package's autotuner).
  *   expand_wg_per_cu: workgroups per compute unit of the expansion launch
- *     (0 = 8; no more are launched than fit);
+ *     (0 = 6, which fit; more are not launched);
  *   expand_tile: examined arcs that a wavefront of the expansion takes at a
  *     time;
  *   admit_below: a batch admits waiting queries only while at most this many
@@ -347,9 +347,10 @@ int raks_serve_stop(raks_ctx* ctx);
 void raks_results_free(raks_results* r);
 
 /* Per-kernel device time, accumulated while timing is enabled
- * (raks_set_timing).  kernel ids: 0 expansion (Algorithm 1), 1 frontier
- * scan, 2 identification/control step with Frontier Enqueue, 3 recovery,
- * 4 other. */
+ * (raks_set_timing).  kernel ids: 0 expansion (Algorithm 1; on the single-query
+ * path with the level's control step), 1 frontier scan (with the RPG check of a
+ * marginal run there), 2 the cohort's control step; selection and ranking on the
+ * single-query path, 3 recovery, 4 other. */
 typedef struct {
     int64_t launches;
     double ms;               /* summed event-measured duration */

@@ -8,8 +8,7 @@ path's parameters and keeps the fastest:
   32: whenever a query fits);
 * ``expand_tile`` -- examined arcs that a wavefront of the expansion takes at a
   time (512, 1024, 2048);
-* ``expand_wg_per_cu`` -- workgroups per compute unit of the expansion (at most
-  what fits);
+* ``expand_wg_per_cu`` -- workgroups per compute unit of the expansion (6 fit);
 * ``cohort_cols`` -- columns of the cohort (16, 32, 64): fewer queries at once,
   with smaller per-node reached masks for the expansion's gathers.
 
@@ -35,8 +34,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 SPACE = {"cohort_cols": (16, 32, 64), "admit_below": (0, 4, 32), "expand_tile": (512, 1024, 2048),
-         "expand_wg_per_cu": (4, 8, 16)}
-DEFAULT = {"cohort_cols": 64, "admit_below": 32, "expand_tile": 1024, "expand_wg_per_cu": 8}
+         "expand_wg_per_cu": (2, 4, 6)}
+DEFAULT = {"cohort_cols": 64, "admit_below": 32, "expand_tile": 1024, "expand_wg_per_cu": 6}
 
 
 def tuning_path(workload: str) -> str:

@@ -1042,7 +1042,6 @@ FinalizeView finalize_view(Lane* L, int ph, const int32_t* n_valid, int C, const
   v.sort_a = P<uint32_t>(L->sort_a);
   v.sort_b = P<uint32_t>(L->sort_b);
   v.soff = reinterpret_cast<const uint64_t*>(lay + Ph.lay_soff);
-  v.write_output = ph;
   v.skip_bits = ph == 0 ? 1 : 3;
   v.big = P<uint32_t>(L->bigf);
   v.mid_z = (uint32_t)finalize_slices(L->ctx->n, L->ctx->A);
@@ -1979,7 +1978,7 @@ int raks_set_tuning(raks_ctx* c, const raks_tuning* t) {
       (t->cohort_cols != 0 && t->cohort_cols != 16 && t->cohort_cols != 32 && t->cohort_cols != 64))
     return fail(RAKS_EINVAL, "tuning values out of range");
   if (c->serve.running) return fail(RAKS_ESTATE, "serving is running");
-  c->co_wpc = t->expand_wg_per_cu ? t->expand_wg_per_cu : 8;
+  c->co_wpc = t->expand_wg_per_cu ? t->expand_wg_per_cu : 6;
   c->co_admit_below = t->admit_below;
   c->co_tile = t->expand_tile ? t->expand_tile : 1024;
   c->co_cols = t->cohort_cols ? t->cohort_cols : 64;

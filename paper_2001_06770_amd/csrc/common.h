@@ -32,7 +32,6 @@ enum EndReason : int { END_NONE = 0, END_EXHAUSTED = 1, END_STOP = 2, END_LEVEL_
 struct RunStatus {
   int32_t end_level;     // level at which the run ended; INT32_MAX while running
   int32_t end_reason;
-  int32_t expand_on;     // 1 if the expansion of the current level runs
   int32_t levels;        // identification passes made
   uint32_t nfront;       // |frontier| of the current level
   uint32_t nactive;      // staged entries (frontiers with arcs to examine at this level)

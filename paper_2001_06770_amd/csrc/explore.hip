@@ -614,9 +614,7 @@ __device__ void control_level(const RunView& r, int level, const LevelSums& ls, 
     if (end != END_NONE) {
       cur.end_level = level;
       cur.end_reason = end;
-      cur.expand_on = 0;
     } else {
-      cur.expand_on = 1;
       cur.e_arc += t[4];
       cur.e_alg += t[5];
       cur.gate_pass += t[6];

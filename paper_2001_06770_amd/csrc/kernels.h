@@ -235,7 +235,6 @@ struct FinalizeView {
   uint32_t* sort_b;
   const uint64_t* soff;
   // final output (marginal == 1 or no marginal keywords)
-  int32_t write_output;
   int32_t skip_bits;         // overflow bits that make this finalize pointless (phase repeats)
   uint32_t* big;             // [n_res] 1: the result's lists go to the bitmap path
   // long lists of RPGs and final results (list i: result i / 2, pass i % 2)
