@@ -574,8 +574,9 @@ __global__ __launch_bounds__(kCtlT) void k_co_control(CohortView v, int level, u
 // arcs of a level reach the same target and store the same bytes; the masks stay
 // as the scan left them, since plain stores to them from several XCDs at once
 // leave their caches with different values).  Per level, 32 queries on 2M
-// nodes: 167 us with a workgroup per tile of 1024 arcs, 159 us now; 12 queries
-// on 50M nodes and 1B arcs: 3.9 ms and 3.6 ms.
+// nodes: 167 us with a workgroup per tile of 1024 arcs, 157 us now; on 50M nodes
+// and 1B arcs 3.09 and 2.72 ms alone, and 3.5 to 4.0 ms beside the CG stages and
+// the finished queries' kernels, which share the memory's rate with it.
 constexpr int kCoExpWgs = 6;
 
 __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView g, int level,
@@ -713,10 +714,11 @@ __global__ __launch_bounds__(kBlock) void k_co_expand(CohortView v, DevGraphView
 
 // One pass: the last level's keys are staged at each scan workgroup's nodes, as
 // on the single path, with their number; the few of earlier levels go to a
-// list.  The rows' bytes bound it (a count, a prefix and a second pass that
-// wrote took 84 us beside the levels of 2M nodes and 3.9 ms beside those of
-// 50M; this one takes 35 us and 1.5 ms).  The selection sums the numbers up: a
-// launch of one workgroup for that took 13 us and 0.33 ms there.
+// list.  The rows' bytes bound it: 0.19 ms alone on 50M nodes.  Beside the levels
+// it waits for its share of the memory's rate: 79 us on 2M nodes and 4.2 ms on 50M
+// (a count, a prefix and a second pass that wrote took 84 us and 3.9 ms beside an
+// expansion that left more of it).  The selection sums the numbers up: a launch of
+// one workgroup for that took 13 us and 0.33 ms there.
 __global__ __launch_bounds__(kBlock) void k_co_cand(CoCandView cv, int32_t n, int32_t cpw) {
   __shared__ uint32_t s_red[kBlock / kWave + 1];
   const int64_t wg0 = (int64_t)blockIdx.x * cpw * kScanNodes;
@@ -869,8 +871,8 @@ __global__ __launch_bounds__(kCtlT) void k_co_rpg_final(CohortView v, int q, Sta
 // node expands.  The columns stay in NW registers as bytes and a level is
 // compared with all of them at once, so no array is indexed by a variable (with
 // arrays and a sorted list of the levels in scratch memory a query on 2M nodes
-// took 248 us, on 50M nodes 7.9 ms; now 75 us and 3.0 ms, beside the level loop).  512
-// workgroups at most, two per CU: each ends with ten additions to the same words,
+// took 248 us, on 50M nodes 7.9 ms; now 79 us and 3.3 ms, beside the level loop).  At
+// most 768 workgroups, three per CU: each ends with ten additions to the same words,
 // which device memory performs one at a time.
 constexpr int kFinT = 512;
 

@@ -580,7 +580,12 @@ __global__ __launch_bounds__(kBlock) void k_lr_nodes(RecoverView v) {
 // Beyond big_list entries the host runs the bitmap path over device memory
 // below.  (The longer lists used to be radix sorted by the one workgroup in
 // device memory: 1 ms for 46k arcs, 24 ms for 1.1M; the two kernels take 0.06 and
-// 0.7 ms on 40M arcs.)
+// 0.7 ms on 40M arcs.)  A slice reads its whole list, so there are few large ones;
+// their 128 KB wait for an empty CU beside other queries' kernels (34 us in a batch
+// on 2M nodes, 0.5 ms on 50M, whether or not a list is long), yet slices of 2^18
+// and 2^19 ids in 32 and 64 KB changed batches, served mixes and lanes by less than
+// their runs differ, and queries with long lists on 400M arcs by up to 11 % for the
+// worse.
 constexpr uint32_t kRankSort = 2 * kBlock;
 constexpr int kRawParts = 8;                       // k_finalize: workgroups per CG
 constexpr uint32_t kSliceBits = 1u << 20;          // 128 KB of LDS

@@ -11,7 +11,9 @@ dispatch of the kernel, scaled by the factor a plain device copy gives for it
 FETCH_SIZE and writes as 1 GiB of WRITE_SIZE), and divided by the number of
 launches the benchmark timed in that run (its JSON line, ``roofline.launches``),
 so that it compares with the line's per-launch algorithmic bytes.  The profiled
-command runs without warm-up, so every dispatch belongs to the timed steps;
+command runs without warm-up, so every dispatch belongs to the timed steps or,
+on a workload without stored counters, to the pass that takes them afterwards
+(``--passes 2`` for one timed step: all passes launch the same).  Other
 dispatches that are not timed are expansion launches queued past a run's end,
 which exit at once.  The record
 carries the SHA-256 of the kernel's source file: the benchmark uses it only
@@ -25,6 +27,7 @@ usage:
   python -m paper_2001_06770_amd.profile_summary table --fetch F.csv --write W.csv [--top N]
   python -m paper_2001_06770_amd.profile_summary traffic --kernel NAME --source FILE.hip
       --workload W --fetch F.csv --write W.csv --bench-json B.json --out OUT.json
+      [--passes N]
 """
 from __future__ import annotations
 
@@ -119,8 +122,8 @@ def traffic(args) -> dict:
     launches = bench_line(args.bench_json)["roofline"]["launches"]
     with open(os.path.join(HERE, "csrc", args.source), "rb") as f:
         sha = hashlib.sha256(f.read()).hexdigest()
-    fb = FETCH_SCALE * fetch * 1024.0 / launches
-    wb = WRITE_SCALE * write * 1024.0 / launches
+    fb = FETCH_SCALE * fetch * 1024.0 / (launches * args.passes)
+    wb = WRITE_SCALE * write * 1024.0 / (launches * args.passes)
     return {"kernel": args.kernel, "workload": args.workload,
             "bytes_per_launch": fb + wb, "fetch_bytes_per_launch": fb,
             "write_bytes_per_launch": wb, "dispatches": [nf, nw], "timed_launches": launches,
@@ -141,6 +144,7 @@ def main(argv=None):
     t = sub.add_parser("traffic")
     for k in ("kernel", "source", "workload", "fetch", "write", "bench_json", "out"):
         t.add_argument("--" + k.replace("_", "-"), required=True)
+    t.add_argument("--passes", type=int, default=1)
     args = ap.parse_args(argv)
     if args.cmd == "stats":
         print(stats_table(args.csv, args.top))
