@@ -863,9 +863,12 @@ int engine_loop(Engine& E) {
       if (e != hipSuccess && e != hipErrorNotReady)
         return fail(RAKS_EDEVICE, std::string("cohort stream failed: ") + hipGetErrorString(e));
       if (e == hipSuccess) {
-        // the stream is idle: every CG stage has published its outcome
+        // the stream was idle: every CG stage sent so far has published its
+        // outcome; those that ran out of a capacity are sent again here
+        const uint64_t sent = E.cg_no;
         RAKS_TRY(poll_cg(E));
-        if (cg_outstanding(E)) return fail(RAKS_EDEVICE, "a CG stage outcome was not published");
+        if (E.cg_no == sent && cg_outstanding(E))
+          return fail(RAKS_EDEVICE, "a CG stage outcome was not published");
         continue;
       }
       std::this_thread::sleep_for(std::chrono::microseconds(20));
